@@ -14,7 +14,7 @@
 //  * workgroups are numbered so that all M-tiles of one weight panel land on the same XCD (ids are
 //    dealt to the 8 XCDs round-robin): the panel is fetched from HBM once per L2.
 //
-// fp32 path: a plain LDS-tiled FMA kernel, used by the small all-fp32 configuration.
+// fp32 path: one FMA chain per output, operands through LDS; used by the small all-fp32 configuration.
 #include "gemm.h"
 
 namespace fard {
@@ -725,17 +725,23 @@ hipError_t launch_wm(hipStream_t s, const GemmArgs& a) {
 }
 
 // ---------------------------------------------------------------------------------- fp32 path
-// A workgroup owns 16 columns and RM rows; its 16 groups of 16 lanes split every chunk of 256 k (16 consecutive k each, lane =
-// column) and their partial sums meet in LDS.  The products of this path have a handful of rows and a few hundred columns:
-// a launch is bound by memory round trips, so a chunk's weights are all requested at once (16 loads a thread) beside the
-// activation rows, which go through LDS.  (A 16 x 16 tile stepping through K 16 at a time, two barriers and a round trip a
-// step, took 13.3 us at 256 x 256 and up to 8 rows; this takes 3.2-4.2.)
+// A workgroup owns 16 columns and RM rows.  Every output is one chain of fused multiply-adds over k = 0 .. K - 1 in that order
+// (then + bias, * gate, + old value, each rounded): the results do not depend on the tile, the row count or the launch.
+// The products of this path have a handful of rows and a few hundred columns, so a launch is bound by memory round trips:
+// the 256 x 16 weights of a chunk are all requested at once (16 loads a thread) beside the activation rows, the next chunk's
+// while this one is summed, and both go through LDS with k innermost, so that a thread reads four k of either at once.  Up to 16
+// rows x 256 x 256 take 3.0-3.2 us, 9 x 256 x 1024 (k) 7.3 (16 x 16 tiles that step through K 16 at a time, two barriers and a
+// round trip a step: 10.4 and 35.6); 8192 x 4096 x 1024 2.04 ms (4.25).  K split over the lanes is ahead of the chain by
+// 0.5 us for up to 4 rows, and gives other results.
 template <int RM, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  constexpr int KC = 256, LA = KC + 4;
+  constexpr int KC = 256, LA = KC + 4;                       // (rows of 260 floats: sixteen of them start in different banks)
   constexpr int NC = SWIGLU ? 2 : 1;
+  constexpr int RT = RM > 16 ? RM / 16 : 1;                  // rows of a thread
+  // k that a thread reads at once; a workgroup that has its compute unit to itself reads the next G during the sums of these
+  constexpr int G = RM > 16 ? 4 : SWIGLU ? 16 : 32;
   __shared__ __attribute__((aligned(16))) float As[RM * LA];
-  __shared__ float red[16][NC * RM * 16];
+  __shared__ __attribute__((aligned(16))) float Ws[NC * 16 * LA];
   const int M = eff_rows(a.M, a.m_dev);
   const int m0 = blockIdx.y * RM;
   if (m0 >= M) return;
@@ -744,23 +750,21 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   const int col = blockIdx.x * 16 + c, wc = col < ncols ? col : ncols - 1;   // columns past N: valid reads, never stored
   const float* A = (const float*)a.A;
   const float* W = (const float*)a.W + wc;
-  float acc[NC][RM];
+  // thread tid < 16 RM sums rows tid / 16 + 16 r of column tid % 16; what its epilogue reads is requested first
+  const bool owner = tid < 16 * RM && col < ncols;
+  float bias = 0.f, old[RT], gate[RT];
 #pragma unroll
-  for (int n = 0; n < NC; ++n)
-#pragma unroll
-    for (int r = 0; r < RM; ++r) acc[n][r] = 0.f;
-  // what the epilogue reads is requested first: thread tid < RM * 16 finishes row tid / 16, column tid % 16
-  static_assert(RM * 16 <= 256, "one output per thread");
-  const int orow = m0 + (tid >> 4), occ = blockIdx.x * 16 + (tid & 15);
-  const bool owner = tid < RM * 16 && orow < M && occ < ncols;
-  float* dst = (float*)a.out + (size_t)orow * a.ldo + occ;
-  float bias = 0.f, old = 0.f, gate = 1.f;
-  if (!SWIGLU && owner) {
-    if (a.bias) bias = a.bias[occ];
-    if (a.epi == EPI_RESID || a.epi == EPI_GATE_RESID) old = *dst;
-    if (a.epi == EPI_GATE_RESID) gate = a.gate[(size_t)orow * a.ldg + occ];
+  for (int r = 0; r < RT; ++r) {
+    const int row = m0 + ks + 16 * r;
+    old[r] = 0.f;
+    gate[r] = 1.f;
+    if (!SWIGLU && owner && row < M) {
+      if (a.epi == EPI_RESID || a.epi == EPI_GATE_RESID) old[r] = ((const float*)a.out)[(size_t)row * a.ldo + col];
+      if (a.epi == EPI_GATE_RESID) gate[r] = a.gate[(size_t)row * a.ldg + col];
+    }
   }
-  // weights of this thread's 16 k and this chunk's activations (past K: row K - 1, against zeroed activations)
+  if (!SWIGLU && owner && a.bias) bias = a.bias[col];
+  // weights of 16 k of this thread's column, and one k of every activation row (past K: row K - 1, against zeroed activations)
   float w[NC][16], av[RM];
   auto load = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
@@ -775,48 +779,89 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
       av[r] = k < a.K ? A[(size_t)gr * a.lda + k] : 0.f;
     }
   };
-  load(0);
-  for (int k0 = 0; k0 < a.K; k0 += KC) {
-    if (k0 > 0) __syncthreads();                           // the previous chunk is consumed
-#pragma unroll
-    for (int r = 0; r < RM; ++r) As[r * LA + tid] = av[r];
-    float wc0[NC][16];
-#pragma unroll
-    for (int n = 0; n < NC; ++n)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) wc0[n][i] = w[n][i];
-    __syncthreads();
-    if (k0 + KC < a.K) load(k0 + KC);                      // on its way while this chunk is summed
-#pragma unroll
-    for (int r = 0; r < RM; ++r)
-#pragma unroll
-      for (int i = 0; i < 16; i += 4) {
-        const f32x4 x = *(const f32x4*)(&As[r * LA + ks * 16 + i]);
-#pragma unroll
-        for (int n = 0; n < NC; ++n)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[n][r] = fmaf(x[e], wc0[n][i + e], acc[n][r]);
-      }
-  }
+  float acc[NC][RT];
 #pragma unroll
   for (int n = 0; n < NC; ++n)
 #pragma unroll
-    for (int r = 0; r < RM; ++r) red[ks][(n * RM + r) * 16 + c] = acc[n][r];
-  __syncthreads();
-  if (!owner) return;
-  float v = 0.f, u = 0.f;
+    for (int r = 0; r < RT; ++r) acc[n][r] = 0.f;
+  // G consecutive k from LDS (chunk position k) into register set i, and their share of the sums; the other set is read meanwhile
+  f32x4 wv[2][NC][G / 4], xv[2][RT][G / 4];
+  auto read = [&](int i, int k) __attribute__((always_inline)) {
 #pragma unroll
-  for (int g = 0; g < 16; ++g) {
-    v += red[g][tid];
-    if constexpr (SWIGLU) u += red[g][RM * 16 + tid];
+    for (int g = 0; g < G / 4; ++g) {
+#pragma unroll
+      for (int n = 0; n < NC; ++n) wv[i][n][g] = *(const f32x4*)(&Ws[(n * 16 + c) * LA + k + 4 * g]);
+#pragma unroll
+      for (int r = 0; r < RT; ++r) xv[i][r][g] = *(const f32x4*)(&As[(ks + 16 * r) * LA + k + 4 * g]);
+    }
+  };
+  auto sum = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int g = 0; g < G / 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NC; ++n)
+#pragma unroll
+          for (int r = 0; r < RT; ++r) acc[n][r] = fmaf(xv[i][r][g][e], wv[i][n][g][e], acc[n][r]);
+  };
+  load(0);
+  for (int k0 = 0; k0 < a.K; k0 += KC) {
+    if (k0 > 0) __syncthreads();                             // the previous chunk is consumed
+#pragma unroll
+    for (int r = 0; r < RM; ++r) As[r * LA + tid] = av[r];
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+#pragma unroll
+      for (int i = 0; i < 16; i += 4) {
+        const f32x4 v = {w[n][i], w[n][i + 1], w[n][i + 2], w[n][i + 3]};
+        *(f32x4*)(&Ws[(n * 16 + c) * LA + ks * 16 + i]) = v;
+      }
+    __syncthreads();
+    if (k0 + KC < a.K) load(k0 + KC);                        // on its way while this chunk is summed
+    if (tid < 16 * RM) {
+      const int left = a.K - k0 < KC ? a.K - k0 : KC, k_end = (left + G - 1) / G * G;   // (zeroed activations past K)
+      if constexpr (RM > 16) {
+#pragma unroll 8
+        for (int k = 0; k < k_end; k += G) {
+          read(0, k);
+          sum(0);
+        }
+      } else {
+        // (the reads stand under no condition, or the sums would wait for both sets; past the chunk they re-read its end)
+        read(0, 0);
+        for (int k = 0; k < k_end; k += 2 * G) {
+          read(1, k + G);
+          __builtin_amdgcn_sched_barrier(0);
+          sum(0);
+          __builtin_amdgcn_sched_barrier(0);
+          read(0, k + 2 * G < KC ? k + 2 * G : KC - G);
+          __builtin_amdgcn_sched_barrier(0);
+          if (k + G < k_end) sum(1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
   }
-  if constexpr (SWIGLU) {
-    *dst = silu(v) * u;
-  } else {
-    v += bias;
-    if (a.epi == EPI_STORE || a.epi == EPI_STORE_F32) v = apply_act(v, a.act);
-    else v = old + v * gate;
-    *dst = v;
+  if (!owner) return;
+#pragma unroll
+  for (int r = 0; r < RT; ++r) {
+    const int row = m0 + ks + 16 * r;
+    if (row >= M) return;
+    float* dst = (float*)a.out + (size_t)row * a.ldo + col;
+    if constexpr (SWIGLU) {
+      *dst = silu(acc[0][r]) * acc[1][r];
+    } else {
+      float v = acc[0][r] + bias;
+      if (a.epi == EPI_STORE || a.epi == EPI_STORE_F32) {
+        v = apply_act(v, a.act);
+      } else {
+#pragma clang fp contract(off)
+        const float g = v * gate[r];
+        v = old[r] + g;
+      }
+      *dst = v;
+    }
   }
 }
 
@@ -879,15 +924,23 @@ hipError_t launch_gemm_bf16_planes(hipStream_t s, const GemmArgs& a) {
 hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a) {
   if (a.M <= 0) return hipSuccess;
   const int ncols = a.epi == EPI_SWIGLU ? a.N / 2 : a.N;
-  const bool few = a.M <= 4;
-  const dim3 grid((ncols + 15) / 16, few ? (a.M + 3) / 4 : (a.M + 7) / 8);
-  if (a.epi == EPI_SWIGLU) {
-    if (few) gemm_f32_kernel<4, true><<<grid, 256, 0, s>>>(a);
-    else gemm_f32_kernel<8, true><<<grid, 256, 0, s>>>(a);
-  } else {
-    if (few) gemm_f32_kernel<4, false><<<grid, 256, 0, s>>>(a);
-    else gemm_f32_kernel<8, false><<<grid, 256, 0, s>>>(a);
-  }
+  const unsigned cols = (unsigned)((ncols + 15) / 16);
+  // The fewest rows a workgroup with which the launch still is one or two workgroups per compute unit: fewer rows read less LDS
+  // per compute unit, more rows fetch the weights less often.  Measured with 4 / 8 / 16 / 32 rows (us): 9 x 256 x 256
+  // 3.1 / 3.4 / 3.9 / 5.6, 32 x 1024 x 256 3.7 / 3.4 / 3.9 / 5.7, 72 x 1024 x 256 6.2 / 5.6 / 5.0 / 5.7, 9 x 4096 x 1024
+  // 14.6 / 10.8 / 11.3 / 15.1, 1024 x 1024 x 256 60 / 38 / 28 / 23.
+  auto groups = [&](int rm) { return (long)cols * ((a.M + rm - 1) / rm); };
+#define FARD_F32(RM)                                                                          \
+  do {                                                                                        \
+    const dim3 grid(cols, (unsigned)((a.M + (RM) - 1) / (RM)));                               \
+    if (a.epi == EPI_SWIGLU) gemm_f32_kernel<RM, true><<<grid, 256, 0, s>>>(a);               \
+    else gemm_f32_kernel<RM, false><<<grid, 256, 0, s>>>(a);                                  \
+  } while (0)
+  if (groups(4) <= 256) FARD_F32(4);
+  else if (groups(8) <= 512) FARD_F32(8);
+  else if (groups(16) <= 640) FARD_F32(16);
+  else FARD_F32(32);
+#undef FARD_F32
   return hipGetLastError();
 }
 

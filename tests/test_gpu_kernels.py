@@ -254,6 +254,34 @@ def test_gemm_f32_edges(ctx_f32, M, K, N, act):
     assert rel_inf(out.cpu().numpy(), ref) < 1e-5
 
 
+def _fma_chain(A, W):
+    """sum_k A[:, k] W[k, :] as float32 fused multiply-adds in the order of k.  The float64 product of two float32 is exact;
+    the float64 sum is rounded to odd, so that the rounding to float32 that follows is that of the exact sum."""
+    acc = np.zeros((A.shape[0], W.shape[1]), np.float32)
+    for k in range(A.shape[1]):
+        p, a = A[:, k:k + 1].astype(np.float64) * W[k].astype(np.float64), acc.astype(np.float64)
+        s = p + a
+        b = s - p
+        err = (p - (s - b)) + (a - b)
+        bits = s.view(np.int64)
+        bits += np.where((err != 0) & (bits & 1 == 0), np.where((err > 0) == (s > 0), 1, -1), 0)
+        acc = s.astype(np.float32)
+    return acc
+
+
+# workgroups of 4, 8, 16 and 32 rows; K inside, at and past a 256-k chunk
+@pytest.mark.parametrize("M,K,N", [(9, 256, 1024), (4, 1000, 48), (72, 300, 256), (72, 255, 1024), (300, 272, 1000)])
+def test_gemm_f32_sums_k_in_order(ctx_f32, M, K, N):
+    """Every output is one chain of fused multiply-adds over k, whatever the tile: equal bits."""
+    ctx, _ = ctx_f32
+    A = gen.normal(14, f"A{M}{K}", (M, K), 1.0, DT_F32)
+    W = gen.normal(14, f"W{K}{N}", (K, N), 0.05, DT_F32)
+    b = gen.normal(14, f"b{N}", (N,), 0.1, DT_F32)
+    out = ctx.spec_gemm(ctx.dev_store(A), ctx.dev_store(W), ctx.dev_f32(b), 0)
+    ctx.sync()
+    assert np.array_equal(out.cpu().numpy(), _fma_chain(A, W) + b)
+
+
 # ----------------------------------------------------------------------------- entropy pre-filter
 def _check_prefilter(ctx, feat, tau, dtype_tol=1e-3):
     from oracle import entropy as ent
