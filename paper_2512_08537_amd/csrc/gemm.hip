@@ -730,7 +730,7 @@ hipError_t launch_wm(hipStream_t s, const GemmArgs& a) {
 // The products of this path have a handful of rows and a few hundred columns, so a launch is bound by memory round trips:
 // the 256 x 16 weights of a chunk are all requested at once (16 loads a thread) beside the activation rows, the next chunk's
 // while this one is summed, and both go through LDS with k innermost, so that a thread reads four k of either at once.  Up to 16
-// rows x 256 x 256 take 3.0-3.2 us, 9 x 256 x 1024 (k) 7.3 (16 x 16 tiles that step through K 16 at a time, two barriers and a
+// rows x 256 x 256 take 3.0-3.3 us, 9 x 256 x 1024 (k) 7.3 (16 x 16 tiles that step through K 16 at a time, two barriers and a
 // round trip a step: 10.4 and 35.6); 8192 x 4096 x 1024 2.04 ms (4.25).  K split over the lanes is ahead of the chain by
 // 0.5 us for up to 4 rows, and gives other results.
 template <int RM, bool SWIGLU>
@@ -764,7 +764,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
     }
   }
   if (!SWIGLU && owner && a.bias) bias = a.bias[col];
-  // weights of 16 k of this thread's column, and one k of every activation row (past K: row K - 1, against zeroed activations)
+  // weights of 16 k of this thread's column, and one k of every activation row (past K: row K - 1, which goes to LDS as zeros:
+  // a zeroed activation alone would make NaN of an infinite weight)
   float w[NC][16], av[RM];
   auto load = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
@@ -808,6 +809,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   load(0);
   for (int k0 = 0; k0 < a.K; k0 += KC) {
     if (k0 > 0) __syncthreads();                             // the previous chunk is consumed
+    if (a.K - k0 < KC) {
+#pragma unroll
+      for (int n = 0; n < NC; ++n)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (k0 + ks * 16 + i >= a.K) w[n][i] = 0.f;
+    }
 #pragma unroll
     for (int r = 0; r < RM; ++r) As[r * LA + tid] = av[r];
 #pragma unroll
@@ -820,7 +828,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
     __syncthreads();
     if (k0 + KC < a.K) load(k0 + KC);                        // on its way while this chunk is summed
     if (tid < 16 * RM) {
-      const int left = a.K - k0 < KC ? a.K - k0 : KC, k_end = (left + G - 1) / G * G;   // (zeroed activations past K)
+      const int left = a.K - k0 < KC ? a.K - k0 : KC, k_end = (left + G - 1) / G * G;   // (zeros past K)
       if constexpr (RM > 16) {
 #pragma unroll 8
         for (int k = 0; k < k_end; k += G) {

@@ -282,6 +282,21 @@ def test_gemm_f32_sums_k_in_order(ctx_f32, M, K, N):
     assert np.array_equal(out.cpu().numpy(), _fma_chain(A, W) + b)
 
 
+@pytest.mark.parametrize("M,K,N", [(3, 17, 32), (9, 257, 1024), (72, 300, 256), (72, 255, 1024), (300, 270, 1000)])
+def test_gemm_f32_infinite_weight_in_the_last_row(ctx_f32, M, K, N):
+    """The rest of a chunk past K adds nothing: an infinite weight gives an infinity of its sign, never NaN."""
+    ctx, _ = ctx_f32
+    A = gen.normal(17, f"A{M}{K}", (M, K), 1.0, DT_F32)
+    W = gen.normal(17, f"W{K}{N}", (K, N), 0.05, DT_F32)
+    W[K - 1, ::3] = np.inf
+    A[A[:, K - 1] == 0, K - 1] = 1.0
+    out = ctx.spec_gemm(ctx.dev_store(A), ctx.dev_store(W), None, 0)
+    ctx.sync()
+    got = out.cpu().numpy()
+    assert np.array_equal(got[:, ::3], np.where(A[:, K - 1:] > 0, np.inf, -np.inf) * np.ones((1, got[:, ::3].shape[1])))
+    assert np.isfinite(np.delete(got, np.s_[::3], axis=1)).all()
+
+
 # ----------------------------------------------------------------------------- entropy pre-filter
 def _check_prefilter(ctx, feat, tau, dtype_tol=1e-3):
     from oracle import entropy as ent
