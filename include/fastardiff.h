@@ -288,6 +288,12 @@ int spec_generate(fard_ctx* ctx, const float* x_first, const int32_t* first_id, 
 int spec_gemm(fard_ctx* ctx, const void* A, const void* W, const float* bias, int32_t M, int32_t K,
               int32_t N, int32_t act, void* out);
 
+/* Which LDS-tiled GEMM variant a bf16 product with tight, 16-byte aligned operands takes (host only, for tests): 0: 256 x 256
+ * outputs per workgroup, 1: 192 x 128, 2: 128 x 128 (two 64-k stages of LDS), 3: 192 x 128, 4: 128 x 128 (four stages);
+ * -1: another kernel.  epi: 0 out = act(A W + b) in storage type, 1 the same in fp32, 2 out += A W + b,
+ * 3 out += gate (A W + b), 4 SwiGLU over N = 2 F interleaved columns; act as in spec_gemm. */
+int spec_gemm_tile_variant(int32_t M, int32_t K, int32_t N, int32_t epi, int32_t act);
+
 /* One small-batch GEMM through the narrow-tile kernel (bf16 contexts), for tests and kernel timing: the
  * draft steps and head decodes of a round (Alg. 1 Steps 1-2) run their GEMMs through it.  All pointers
  * are device memory.  A storage type [M,K]; W storage type [K,N] row-major (re-laid on every call);

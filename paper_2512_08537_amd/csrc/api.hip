@@ -1990,6 +1990,13 @@ int spec_gemm(fard_ctx* c, const void* A, const void* W, const float* bias, int3
   return FARD_OK;
 }
 
+int spec_gemm_tile_variant(int32_t M, int32_t K, int32_t N, int32_t epi, int32_t act) {
+  if (M < 1 || K < 1 || N < 1 || K % 64 != 0 || N % 32 != 0 || epi < 0 || epi > 4 || act < 0 || act > 2 || routes_narrow(M, N, K, epi)) return -1;
+  GemmArgs a{};                                              // (null pointers count as aligned)
+  a.M = M; a.N = N; a.K = K; a.epi = epi; a.act = act; a.lda = K; a.ldo = epi == EPI_SWIGLU ? N / 2 : N; a.ldg = N;
+  return gemm_tile_variant(a);
+}
+
 int spec_gemm_narrow(fard_ctx* c, const void* A, const void* W, const float* bias, const float* gate, int32_t M,
                      int32_t K, int32_t N, int32_t epi, int32_t act, void* out, void* out_bf16) {
   if (check_ctx(c)) return FARD_EINVAL;

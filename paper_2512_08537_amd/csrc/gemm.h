@@ -71,9 +71,9 @@ inline size_t packed_elems(int K, int N) { return (size_t)K * (size_t)N; }
 hipError_t launch_gemm_bf16(hipStream_t s, const GemmArgs& a);
 hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a);
 
-// Tiles with both operands through LDS (gemm_tile.hip), where its rule finds one ahead: hundreds of rows and more.
-bool gemm_tile_better(const GemmArgs& a);
-hipError_t launch_gemm_tile(hipStream_t s, const GemmArgs& a);
+// Tiles with both operands through LDS (gemm_tile.hip): the variant that its rule finds ahead (hundreds of rows and more), -1 for none.
+int gemm_tile_variant(const GemmArgs& a);
+hipError_t launch_gemm_tile(hipStream_t s, const GemmArgs& a, int variant);
 
 // XCD groups along M of a tiled launch: every XCD has its own L2 and fetches what its workgroups read.  With xm groups
 // along M and 8 / xm along the panels an XCD reads 1 / xm of the activations and xm / 8 of the weights; take the split

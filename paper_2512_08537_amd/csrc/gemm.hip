@@ -900,7 +900,7 @@ hipError_t launch_gemm_bf16(hipStream_t s, const GemmArgs& a) {
   if (a.epi == EPI_SWIGLU && a.N % 64 != 0) return hipErrorInvalidValue;
   if (a.M <= 32) return launch_wm<1>(s, a);
   if (a.M <= 64) return launch_wm<2>(s, a);
-  if (gemm_tile_better(a)) return launch_gemm_tile(s, a);
+  if (const int v = gemm_tile_variant(a); v >= 0) return launch_gemm_tile(s, a, v);
   // thousands of rows: 128-row tiles reuse every weight fragment a third more often than 96-row tiles and win once
   // they still make several rounds of 256-column workgroups over the chip (measured: + 5-15 % from about 900
   // workgroups on, - 13-37 % below)

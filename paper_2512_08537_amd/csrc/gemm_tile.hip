@@ -22,6 +22,7 @@
 #include "gemm.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace fard {
 
@@ -293,59 +294,83 @@ __global__ __launch_bounds__(256, 2 * NS * stage_bytes(WI, WJ) <= 160 * 1024 ? 2
 #undef TILE_PART
 }
 
-// Which tile, if any.  The time of a tile variant follows from its workgroups, since compute units run whole tiles: with T
-// tiles some compute unit runs ceil(T / 256) of them.  Variants whose LDS lets two workgroups share a compute unit take
-// `pair` for two tiles side by side and `one` for the odd one out.  Measured over 300 to 18432 rows against 1024 to 27648
-// columns (K 1024 to 13824, and only there is it used); n stages of 64 k, microseconds, model within 10 % (15 % where a last round is nearly empty):
-//   tile       stages  one            pair           measured at
-//   256 x 256  2       1.5 n + 15                    2560 x 5120 x 5120 138, 6144 x 27648 x 5120 1541
-//   192 x 128  2       0.7 n + 6      1.42 n + 9     4128 x 3840 x 1280 48, 8256 x 5120 x 1280 133
-//   128 x 128  2       0.62 n + 3.5   0.95 n + 6     8256 x 5120 x 1280 141, 1500 x 5120 x 13824 216
-//   192 x 128  4       0.68 n + 7.5                  4128 x 1280 x 5120 62 (two stages: 66)
-//   128 x 128  4       0.53 n + 4.5                  3366 x 1024 x 4096 38 (two stages: 45)
+// ---- which tile, if any
+// Both kernels are priced in microseconds and the cheapest is taken.  The prices were fitted to 2215 products timed on every
+// tile and on the streaming kernel (100 pairs of 512 to 58368 columns and a K of 1024 to 13824, 256 to 8192 rows, every epilogue;
+// beyond those sizes they are extrapolated): a tile's price is within 4 % of the measured time for half of them and within
+// 12 % for 95 %.  Over all of them what is chosen takes 0.7 % more than the fastest choice would; it is more than 3 % behind
+// the streaming kernel at 10, by up to 13 % (485 x 2752 x 8320 with SwiGLU), and the streaming kernel alone would take 18 % more.
+//
+// Compute units run whole tiles, and the tiles are dealt to the XCDs in fixed groups, so that a launch takes as many rounds as
+// the fullest XCD's share has multiples of its 32 compute units: 255 tiles of 256 x 256 (4128 x 3840 x 1280) are two rounds, since
+// one XCD gets 36 of them.  Tiles whose LDS lets two workgroups share a compute unit take `pair` for two rounds and `one` for an
+// odd one; a launch that leaves compute units idle finds more of the L2 and of the clock.  Measured with all compute units busy:
+//   tile       stages  microseconds for n stages of 64 k: one, pair
+//   256 x 256  2       1.64 n + 12
+//   192 x 128  2       0.85 n + 4.2    1.4 n + 4.9
+//   128 x 128  2       0.745 n + 2.2   0.98 n + 3.3
+//   192 x 128  4       0.74 n + 6
+//   128 x 128  4       0.6 n + 3.5
 // Four stages are for a tile that has its compute unit to itself: with two, 64 k are multiplied faster than the next 64
-// arrive.  A GELU takes 1 us per 64 x 64 outputs of a tile that is alone, 0.15 us where a second workgroup's MFMAs cover it
-// (3366 x 4096 x 1024: 52 us on 256 x 256 tiles, 44.5 on 128 x 128; without GELU 3366 x 3840 x 1280 44 and 42).
+// arrive.  The epilogue's own work, per 64 x 64 outputs, weighs most where no second workgroup's MFMAs cover it.
 struct TileVariant {
   int wi, wj, ns;
   double one_n, one_0, pair_n, pair_0;                       // pair_n 0: one workgroup per compute unit
+  double gelu, silu, resid, f32;                             // epilogue, per 64 x 64 outputs
 };
 constexpr TileVariant VARIANTS[] = {
-    {4, 4, 2, 1.5, 15.0, 0.0, 0.0}, {3, 2, 2, 0.7, 6.0, 1.42, 9.0},  {2, 2, 2, 0.62, 3.5, 0.95, 6.0},
-    {3, 2, 4, 0.68, 7.5, 0.0, 0.0}, {2, 2, 4, 0.53, 4.5, 0.0, 0.0},
+    {4, 4, 2, 1.64, 12.0, 0.0, 0.0, 0.9, 0.55, 0.4, 0.2},   {3, 2, 2, 0.85, 4.2, 1.4, 4.9, 0.65, 0.45, 0.45, 0.4},
+    {2, 2, 2, 0.745, 2.2, 0.98, 3.3, 0.65, 0.45, 0.45, 0.4}, {3, 2, 4, 0.74, 6.0, 0.0, 0.0, 0.8, 0.45, 0.4, 0.3},
+    {2, 2, 4, 0.6, 3.5, 0.0, 0.0, 0.8, 0.45, 0.4, 0.3},
 };
+constexpr int N_VARIANTS = (int)(sizeof(VARIANTS) / sizeof(VARIANTS[0]));
 
-// Index into VARIANTS, -1 where the streaming kernel stays.  Its time is taken from the rates that it reaches over the same
-// sizes (TFLOP/s, plus 5 us): 900-1100 with a SwiGLU epilogue; wide products with a long K 480-620 at 450 rows, 570-650 at
-// 900, 690-870 at 1500, 850-1190 from 2100 on; 450-650 with a long K and few columns; with a short K 550-650, 200-400 where
-// it adds to the residual stream.  Examples, streaming -> chosen (us): 3366 x 1024 x 4096 62 -> 38, 3366 x 1024 x 1024
-// 23.4 -> 15.8, 3366 x 4096 x 1024 48 -> 44.5, 2304 x 1280 x 1280 27 -> 17.4, 2304 x 5120 x 1280 48.5 -> 42, 4128 x 1280 x 5120
-// 84 -> 62, 1500 x 5120 x 5120 114 -> 85; it keeps 2304 x 1024 x 4096 (34 against 36) and 1100 x 1280 x 5120 (39 against 43).
-int tile_variant(const GemmArgs& a) {
-  if (a.epi > EPI_SWIGLU || a.M < 256 || a.K < 1024 || a.K % (2 * TBK) != 0 || a.N % 32 != 0) return -1;
-  if (a.lda % 8 != 0 || a.ldo % 8 != 0 || (a.epi == EPI_GATE_RESID && a.ldg % 4 != 0) || (a.epi == EPI_SWIGLU && a.N % 64 != 0))
-    return -1;
-  // sixteen bytes a lane, in and out
-  if ((((uintptr_t)a.A | (uintptr_t)a.W | (uintptr_t)a.out | (uintptr_t)a.bias | (uintptr_t)a.gate) & 15) != 0) return -1;
-  const bool resid = a.epi == EPI_RESID || a.epi == EPI_GATE_RESID;
-  double rate;
-  if (a.epi == EPI_SWIGLU) rate = 900.0;
-  else if (a.K >= 4096 && a.N >= 4096) rate = std::min(900.0, 500.0 + 0.2 * a.M);
-  else if (a.K >= 2048) rate = 650.0;
-  else rate = resid ? 400.0 : 600.0;
-  double best = 2e-6 * a.M * a.N * a.K / rate + 5.0;
-  int choice = -1;
-  for (int v = 0; v < (int)(sizeof(VARIANTS) / sizeof(VARIANTS[0])); ++v) {
-    const TileVariant& t = VARIANTS[v];
-    if (a.K % (t.ns * TBK) != 0) continue;
-    const long tiles = (long)((a.M + 64 * t.wi - 1) / (64 * t.wi)) * ((a.N + 64 * t.wj - 1) / (64 * t.wj));
-    const long k = (tiles + 255) / 256;
-    const double n = a.K / TBK;
-    double us = t.pair_n > 0.0 ? (k / 2) * (t.pair_n * n + t.pair_0) + (k % 2) * (t.one_n * n + t.one_0) : k * (t.one_n * n + t.one_0);
-    if (a.act == ACT_GELU) us += (t.pair_n > 0.0 ? 0.15 : 1.0) * t.wi * t.wj * k;
-    if (us < best) { best = us; choice = v; }
+inline int up(int a, int b) { return (a + b - 1) / b; }
+inline bool is_resid(const GemmArgs& a) { return a.epi == EPI_RESID || a.epi == EPI_GATE_RESID; }
+
+double tile_us(const GemmArgs& a, const TileVariant& t) {
+  const int m_tiles = up(a.M, 64 * t.wi), n_tiles = up(a.N, 64 * t.wj), xm = xcd_groups_along_m(a, m_tiles);
+  const long k = (up(m_tiles, xm) * (long)up(n_tiles, 8 / xm) + 31) / 32;
+  const double n = a.K / TBK, one = t.one_n * n + t.one_0;
+  double us = t.pair_n > 0.0 ? (k / 2) * (t.pair_n * n + t.pair_0) + (k % 2) * one : k * one;
+  // (few rows: the weights come from memory, and idle compute units help less)
+  const double busy = std::min(1.0, (double)m_tiles * n_tiles / (256.0 * k));
+  us *= 1.0 - (a.M > 640 ? 0.33 : 0.2) * (1.0 - busy);
+  const double epi = a.act == ACT_GELU ? t.gelu : a.act == ACT_SILU ? t.silu : is_resid(a) ? t.resid : a.epi == EPI_STORE_F32 ? t.f32 : 0.0;
+  return us + k * t.wi * t.wj * epi + 1.5;
+}
+
+// The streaming kernel (launch_wm's choice of tile and K splits).  It is only ahead where it has what the tiles lack: 32-row tiles,
+// K splits, or few rows; everywhere else it was never more than 3 % faster than the best tile, and takes no part (infinite).
+double streaming_us(const GemmArgs& a) {
+  const double n = a.K / 64.0;
+  const bool resid = is_resid(a);
+  auto t = [&](int bm, int bn) { return (double)up(a.M, bm) * up(a.N, bn); };
+  // rounds of w workgroups per compute unit: a share x of a last round's missing workgroups costs nothing
+  auto rounds = [](double w, double x) { return w <= 1.0 ? 1.0 : x * w + (1.0 - x) * std::ceil(w); };
+  constexpr double NEVER = 1e9;
+  if (a.epi == EPI_SWIGLU) {
+    if (a.M <= 640 && a.K % 256 == 0 && t(64, 128) <= 288) return 5.0 + rounds(t(64, 128) / 256, 0.5) * (0.31 * n + 1.0);
+    if (t(t(128, 256) >= 900 ? 128 : 96, 256) >= 512) return a.M > 640 ? NEVER : 5.0 + rounds(t(96, 256) / 256, 0.5) * (0.8 * n + 4.0);
+    return 4.0 + std::ceil(t(96, 64) / 256) * (0.31 * n + 7.0);
   }
-  return choice;
+  if (!resid && a.M <= 640) {
+    const double w = t(64, 128) / 256;
+    return 5.5 + rounds(w, 0.7) * (0.34 * n + 0.3) + (a.act == ACT_GELU ? 1.5 * w : a.epi == EPI_STORE_F32 ? 1.2 * w : 0.0);
+  }
+  if (t(96, 128) < 128 && t(32, 128) >= 64) {
+    const double sp = resid ? std::min(std::max(std::ceil(256 / t(32, 128)), 1.0), std::min((double)up(a.K, 256), 4.0)) : 1.0;
+    const double w = t(32, 128) * sp / 256;
+    return (resid ? 4.5 : 3.0) + rounds(w, 0.6) * (0.25 * n / sp + (resid ? 0.8 : 0.5)) + (a.epi == EPI_GATE_RESID ? w : 0.0);
+  }
+  if (a.M > 640 && t(128, 128) > (a.K % 256 ? 320 : 192)) return NEVER;
+  const double gate = a.epi == EPI_GATE_RESID ? 1.0 : 0.0;
+  if (resid && !(t(64, 128) >= 512 || (t(64, 128) >= 256 && a.K <= 2048))) {
+    const double t96 = t(96, 128), sp = t96 < 256 ? std::ceil(256 / t96) : 1.0;
+    return 5.0 * gate + (sp == 1.0 ? 10.0 + rounds(t96 / 256, 0.5) * 0.46 * n : 20.0 + rounds(t96 * sp / 256, 0.5) * 0.3 * n / sp);
+  }
+  const double w = t(64, 128) / 256;
+  return 5.5 + std::max(rounds(w, 0.5), 1.5) * (0.29 * n + (resid ? 3.2 : 1.5) + 3.0 * gate) + (a.act == ACT_GELU ? 0.7 * w : 0.0);
 }
 
 template <int WI, int WJ, int NS>
@@ -367,10 +392,27 @@ hipError_t launch_tile(hipStream_t s, const GemmArgs& a) {
 
 }  // namespace
 
-bool gemm_tile_better(const GemmArgs& a) { return tile_variant(a) >= 0; }
+// Index into VARIANTS, -1 where the streaming kernel stays.  Examples, streaming -> chosen (us): 3366 x 1024 x 4096 61 -> 38, 3366 x
+// 1024 x 1024 24 -> 16, 4128 x 3840 x 1280 67 -> 50, 2304 x 1280 x 1280 27 -> 17, 1100 x 27648 x 5120 SwiGLU 326 -> 328, 1700 x 5120 x
+// 5120 136 -> 111; it keeps 1500 x 1024 x 4096 (34 against 34), 1100 x 1280 x 5120 (39 against 42) and 576 x 5120 x 13824 (104 against 134).
+int gemm_tile_variant(const GemmArgs& a) {
+  if (a.epi > EPI_SWIGLU || a.M < 256 || a.K < 1024 || a.K % (2 * TBK) != 0 || a.N % 32 != 0) return -1;
+  if (a.lda % 8 != 0 || a.ldo % 8 != 0 || (a.epi == EPI_GATE_RESID && a.ldg % 4 != 0) || (a.epi == EPI_SWIGLU && a.N % 64 != 0))
+    return -1;
+  // sixteen bytes a lane, in and out
+  if ((((uintptr_t)a.A | (uintptr_t)a.W | (uintptr_t)a.out | (uintptr_t)a.bias | (uintptr_t)a.gate) & 15) != 0) return -1;
+  double best = streaming_us(a);
+  int choice = -1;
+  for (int v = 0; v < N_VARIANTS; ++v) {
+    if (a.K % (VARIANTS[v].ns * TBK) != 0) continue;
+    const double us = tile_us(a, VARIANTS[v]);
+    if (us < best) { best = us; choice = v; }
+  }
+  return choice;
+}
 
-hipError_t launch_gemm_tile(hipStream_t s, const GemmArgs& a) {
-  switch (tile_variant(a)) {
+hipError_t launch_gemm_tile(hipStream_t s, const GemmArgs& a, int variant) {
+  switch (variant) {
     case 0: return launch_tile<4, 4, 2>(s, a);
     case 1: return launch_tile<3, 2, 2>(s, a);
     case 2: return launch_tile<2, 2, 2>(s, a);
