@@ -133,8 +133,10 @@ __device__ __forceinline__ void tile_sync() {
     tile_sync();                                              \
   } while (0)
 
-// ---- rows: statistics, and dq.  Four waves x 32 queries of one (b, h).
-template <int DH>
+// ---- rows: statistics, and dq.  Four waves x 32 queries of one (b, h); a wave past R only loads.  SHORT, up to 32 rows: a wave has
+// a (b, h) and its keys to itself, or three of four waves would have no queries (64 x 40 (8) x 24 x 128, statistics alone: 18.6 us
+// with one (b, h) per workgroup, 13.0 with the unstaged kernels described above, 8.5 now).
+template <int DH, bool SHORT>
 __global__ __launch_bounds__(256, 3) void ent_rows_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k, int BH, int H, int Hkv,
                                                           int R, int Rp, float scale, float cc, float* __restrict__ lse2,
                                                           float* __restrict__ cch, float* __restrict__ partial,
@@ -142,13 +144,15 @@ __global__ __launch_bounds__(256, 3) void ent_rows_kernel(const bf16* __restrict
   __shared__ __attribute__((aligned(1024))) char b0[WR * DH * 2];
   __shared__ __attribute__((aligned(1024))) char b1[WR * DH * 2];
   __shared__ float part[4];
-  // the longest walks first
-  const int n_groups = Rp / GR;
-  const int bh = blockIdx.x % BH, grp = n_groups - 1 - blockIdx.x / BH;
-  const int b = bh / H, h = bh - b * H, bkv = b * Hkv + h / (H / Hkv);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the longest walks first
+  const int n_groups = Rp / GR, slot = SHORT ? 4 * blockIdx.x + wave : blockIdx.x % BH;
+  const bool live = slot < BH;
+  const int bh = live ? slot : BH - 1, grp = SHORT ? 0 : n_groups - 1 - blockIdx.x / BH;
+  const int b = bh / H, h = bh - b * H, bkv = b * Hkv + h / (H / Hkv);
   const int c = lane & 31, hh = lane >> 5;
-  const int q0 = grp * GR + 32 * wave, query = q0 + c;
+  const int q0 = SHORT ? 0 : grp * GR + 32 * wave, query = q0 + c;
+  const int last = q0 < R ? q0 : -1;                         // first row of the last key block
   const int end = grp * GR + GR < R ? grp * GR + GR : R;     // keys that this workgroup's queries see
   const bf16* kbase = k + (size_t)bkv * R * DH;
   const float s2 = scale * LOG2E;
@@ -171,8 +175,8 @@ __global__ __launch_bounds__(256, 3) void ent_rows_kernel(const bf16* __restrict
   float m = M_START, l = 0.f, a = 0.f;
   auto stats = [&](const char* buf, int r0) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (int sub = 0; sub < WR; sub += 32) {
-      if (r0 + sub > q0) break;
+    for (int sub = 0; sub < (SHORT ? 32 : WR); sub += 32) {
+      if (r0 + sub > last) break;
       const f32x16 acc = scores(buf, sub, r0 + sub);
       float mx = acc[0];
 #pragma unroll
@@ -189,7 +193,15 @@ __global__ __launch_bounds__(256, 3) void ent_rows_kernel(const bf16* __restrict
       }
     }
   };
-  ENT_WALK(0, end, issue, stats);
+  char* own_keys = (wave < 2 ? b0 : b1) + (wave & 1) * (32 * DH * 2);
+  if constexpr (SHORT) {
+    walk_load<DH>(own_keys, kbase, 0, R, 0, lane);           // rows 0 .. 15
+    walk_load<DH>(own_keys, kbase, 0, R, 1, lane);
+    tile_sync();
+    stats(own_keys, 0);
+  } else {
+    ENT_WALK(0, end, issue, stats);
+  }
   {
     const float mo = other_half(m), lo = other_half(l), ao = other_half(a);
     const float mn = fmaxf(m, mo), d1 = mn - m, d2 = mn - mo;
@@ -199,14 +211,15 @@ __global__ __launch_bounds__(256, 3) void ent_rows_kernel(const bf16* __restrict
     m = mn;
   }
   const float ll = __builtin_amdgcn_logf(l);
-  const bool valid = query < R;
+  const bool valid = live && query < R;
   const float hv = valid ? LN2 * (ll - a / l) : 0.f;
   const float ls = valid ? m + ll : 1e30f;                   // rows past R: probability 0 in the second kernel
-  if (hh == 0) {
-    lse2[(size_t)bh * Rp + query] = ls;
-    cch[(size_t)bh * Rp + query] = cc * hv;
-    if (valid && h_out) h_out[(size_t)bh * R + query] = hv;
+  // (SHORT: the second halves of the waves fill the rest of the 64-row tile that the dk kernel reads)
+  if (SHORT ? live : hh == 0) {
+    lse2[(size_t)bh * Rp + query + 32 * hh] = hh == 0 ? ls : 1e30f;
+    cch[(size_t)bh * Rp + query + 32 * hh] = hh == 0 ? cc * hv : 0.f;
   }
+  if (hh == 0 && valid && h_out) h_out[(size_t)bh * R + query] = hv;
   const float hs = wave_sum(hh == 0 ? hv : 0.f);
   if (lane == 0) part[wave] = hs;
   __syncthreads();
@@ -221,8 +234,8 @@ __global__ __launch_bounds__(256, 3) void ent_rows_kernel(const bf16* __restrict
   const float c1 = cc * LN2, c2 = cc * hv;
   auto grads = [&](const char* buf, int r0) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (int sub = 0; sub < WR; sub += 32) {
-      if (r0 + sub > q0) break;
+    for (int sub = 0; sub < (SHORT ? 32 : WR); sub += 32) {
+      if (r0 + sub > last) break;
       const f32x16 acc = scores(buf, sub, r0 + sub);
       bf16x8 g[2];
 #pragma unroll
@@ -233,14 +246,15 @@ __global__ __launch_bounds__(256, 3) void ent_rows_kernel(const bf16* __restrict
       grad_product<DH>(buf, sub, g, out, lane);
     }
   };
-  ENT_WALK(0, end, issue, grads);
+  if constexpr (SHORT) grads(own_keys, 0);
+  else ENT_WALK(0, end, issue, grads);
   float* dq_b = dq + (size_t)bh * R * DH;
 #pragma unroll
   for (int d = 0; d < DH / 32; ++d)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int row = q0 + 8 * (e >> 2) + 4 * hh + (e & 3);
-      if (row < R) dq_b[(size_t)row * DH + 32 * d + c] = out[d][e];
+      if (live && row < R) dq_b[(size_t)row * DH + 32 * d + c] = out[d][e];
     }
 }
 
@@ -261,6 +275,7 @@ __global__ __launch_bounds__(256, DH == 128 ? 2 : 3) void ent_dk_kernel(const bf
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 31, hh = lane >> 5;
   const int k0 = grp * GR + 32 * wave;
+  const int own = k0 < R ? k0 : 1 << 30;                     // first row of the first query block; a wave past R only loads
   const float s2 = scale * LOG2E, c1 = cc * LN2;
   Frag<DH> kf;
   load_rows<DH>(kf, k + (size_t)bkv * R * DH, k0 + c, R, hh);
@@ -285,7 +300,7 @@ __global__ __launch_bounds__(256, DH == 128 ? 2 : 3) void ent_dk_kernel(const bf
     auto grads = [&](const char* buf, int r0) __attribute__((always_inline)) {
 #pragma unroll 1
       for (int sub = 0; sub < WR; sub += 32) {
-        if (r0 + sub < k0) continue;
+        if (r0 + sub < own) continue;
         f32x16 acc = score_tile<DH>(buf, sub, kf, lane);
         if (r0 + sub == k0) {
 #pragma unroll
@@ -380,8 +395,9 @@ hipError_t entropy_loss_t(hipStream_t s, const bf16* q, const bf16* k, int B, in
   float* partial = (float*)(base + lay.partial);
   const float scale = 1.0f / sqrtf((float)DH);
   const float cc = scale / ((float)B * (float)H * (float)R);
-  const int n_part = B * H * n_groups;
-  ent_rows_kernel<DH><<<n_part, 256, 0, s>>>(q, k, B * H, H, Hkv, R, Rp, scale, cc, lse2, cch, partial, h_rows, dq);
+  const int n_part = R <= 32 ? (B * H + 3) / 4 : B * H * n_groups;
+  if (R <= 32) ent_rows_kernel<DH, true><<<n_part, 256, 0, s>>>(q, k, B * H, H, Hkv, R, Rp, scale, cc, lse2, cch, partial, h_rows, dq);
+  else ent_rows_kernel<DH, false><<<n_part, 256, 0, s>>>(q, k, B * H, H, Hkv, R, Rp, scale, cc, lse2, cch, partial, h_rows, dq);
   sum_partials_kernel<<<1, 1024, 0, s>>>(partial, n_part, -1.0f / (float)((long)B * H * R), loss);
   if (dk)
     ent_dk_kernel<DH><<<B * Hkv * n_groups, 256, 0, s>>>(q, k, B * Hkv, H, Hkv, R, Rp, scale, cc, lse2, cch, dk);

@@ -60,6 +60,8 @@ def test_entropy_loss_and_gradients_match_oracle(ctx, B, H, Hkv, R, dh, std):
     (1, 2, 1, 63, 128), (2, 2, 2, 65, 32),       # one row short of, and past, a 64-row tile of the walk
     (1, 3, 1, 127, 64), (2, 4, 2, 128, 128), (1, 2, 2, 129, 32),   # around the 128 rows of a workgroup
     (1, 4, 1, 385, 128),                         # an odd number of row groups, grouped heads
+    (1, 1, 1, 1, 32), (3, 3, 1, 7, 64), (2, 5, 5, 31, 128), (5, 2, 1, 32, 32), (1, 6, 2, 24, 128),   # up to 32 rows: four heads a workgroup
+    (1, 6, 2, 33, 128),                          # just above
 ])
 def test_entropy_loss_around_tile_edges(ctx, B, H, Hkv, R, dh):
     """Same bars as above."""
