@@ -28,6 +28,8 @@
 // operand.  The 16-byte pieces of a row are stored XOR-ed with twr(row), so that neither kind of read meets bank conflicts.
 #include "kernels.h"
 
+#include <algorithm>
+
 namespace fard {
 
 namespace {
@@ -336,8 +338,8 @@ __global__ __launch_bounds__(256, DH == 128 ? 2 : 3) void ent_dk_kernel(const bf
 }
 
 // Smooth-L1: per-workgroup partial sums (fixed order), gradient per element.  Bound: the memory's read and write of 8 to 12
-// bytes an element.  VEC elements a lane and step: 16 bytes of
-// input where all pointers allow that, else one (42 M bf16 elements: 128 us with one, 71 us, 4.7 TB/s, with eight).
+// bytes an element.  VEC elements a lane and step: 16 bytes of input where all pointers allow that and n is large, else one
+// (42 M bf16 elements: 141 us with one, 72 us, 4.7 TB/s, with eight).
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void smooth_l1_kernel(const T* __restrict__ pred, const T* __restrict__ target, long n, float beta,
                                                         float* __restrict__ partial, float* __restrict__ dpred) {
@@ -429,7 +431,11 @@ hipError_t launch_smooth_l1(hipStream_t s, int is_bf16, const void* pred, const 
                             int n_part, float* loss, float* dpred) {
   if (n < 1 || n_part < 1 || !(beta > 0.f)) return hipErrorInvalidValue;
   const uintptr_t in = (uintptr_t)pred | (uintptr_t)target;
-  const bool vec = (in & 15) == 0 && ((uintptr_t)dpred & 15) == 0;
+  // Below two workgroups of 16-byte pieces per compute unit the lanes' serial elements cost more than narrow accesses: 20000 bf16
+  // elements 5.6 us with eight a lane, 4.8 with one; 131072 5.7 and 4.8, 524288 6.0 and 5.8, 1 M 6.6 and 6.6, 3 M 9.0 and 9.8.
+  const int per = is_bf16 ? 8 : 4;
+  const bool vec = (in & 15) == 0 && ((uintptr_t)dpred & 15) == 0 && n / per > 512 * 256;
+  if (vec) n_part = (int)std::min<long>(n_part, (n / per + 255) / 256);
 #define FARD_L1(T, VEC) smooth_l1_kernel<T, VEC><<<n_part, 256, 0, s>>>((const T*)pred, (const T*)target, n, beta, partial, dpred)
   if (is_bf16) {
     if (vec) FARD_L1(bf16, 8); else FARD_L1(bf16, 1);

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from synth import gen
-from synth.configs import DT_BF16
+from synth.configs import DT_BF16, DT_F32
 from tests.harness import build_case, make_ctx, rel_inf
 
 pytestmark = pytest.mark.gpu
@@ -75,12 +75,25 @@ def test_entropy_loss_around_tile_edges(ctx, B, H, Hkv, R, dh):
     assert rel_inf(dq.cpu().numpy(), dqo) < 2e-2 and rel_inf(dk.cpu().numpy(), dko) < 2e-2
 
 
-@pytest.mark.parametrize("n,shift", [(7, 0), (8, 0), (4099, 0), (4099, 1), (4096, 3)])
-def test_smooth_l1_tails_and_unaligned_inputs(ctx, n, shift):
-    """Fewer elements than one 16-byte piece, a tail after the last piece, and inputs that start inside a piece (one element at
-    a time there).  float32 sums of n terms below 2: bar 1e-5."""
+@pytest.fixture(scope="module")
+def ctx_f32():
+    c = make_ctx(build_case("ln-gelu-f32", seed=3))
+    yield c
+    c.close()
+
+
+# below and above the size from which 16 bytes a lane are taken (1048576 bf16, 524288 float32 elements), tails after the last piece,
+# inputs that start inside a piece (one element at a time there), and more than one step of the grid on every path
+_L1_BF16 = [(7, 0), (8, 0), (4099, 0), (4099, 1), (4096, 3), (600001, 1), (1048583, 0), (1048584, 0), (4300003, 0)]
+_L1_F32 = [(5, 0), (4099, 0), (600001, 1), (524291, 0), (524292, 0), (2200003, 0)]
+
+
+@pytest.mark.parametrize("kind,n,shift", [("bf16", *c) for c in _L1_BF16] + [("f32", *c) for c in _L1_F32])
+def test_smooth_l1_tails_and_unaligned_inputs(request, kind, n, shift):
+    """Sums of positive float32 terms, at most 16 in a lane and then 20 levels of partial sums: below 36 x 2^-24; bar 1e-5."""
     from oracle import losses
-    p, t = gen.normal(16, f"p{n}", (n + shift,), 1.0, DT_BF16), gen.normal(16, f"t{n}", (n + shift,), 1.0, DT_BF16)
+    ctx, dt = (request.getfixturevalue("ctx"), DT_BF16) if kind == "bf16" else (request.getfixturevalue("ctx_f32"), DT_F32)
+    p, t = gen.normal(16, f"p{n}", (n + shift,), 1.0, dt), gen.normal(16, f"t{n}", (n + shift,), 1.0, dt)
     loss, dp = ctx.spec_smooth_l1(ctx.dev_store(p)[shift:], ctx.dev_store(t)[shift:])
     ctx.sync()
     lo, dpo = losses.smooth_l1(p[shift:], t[shift:])
