@@ -344,7 +344,8 @@ template <typename T, int VEC>
 __global__ __launch_bounds__(256) void smooth_l1_kernel(const T* __restrict__ pred, const T* __restrict__ target, long n, float beta,
                                                         float* __restrict__ partial, float* __restrict__ dpred) {
   typedef T tvec __attribute__((ext_vector_type(VEC)));
-  typedef float fvec __attribute__((ext_vector_type(VEC)));
+  typedef float fvec __attribute__((ext_vector_type(VEC < 4 ? VEC : 4)));   // (the gradient is 16-byte aligned, no more)
+  constexpr int GV = VEC < 4 ? VEC : 4;
   __shared__ float part[4];
   float s = 0.f;
   const float inv_n = 1.0f / (float)n;
@@ -358,10 +359,13 @@ __global__ __launch_bounds__(256) void smooth_l1_kernel(const T* __restrict__ pr
   const long i0 = (long)blockIdx.x * 256 + threadIdx.x;
   for (long i = i0; i < nv; i += step) {
     const tvec p = ((const tvec*)pred)[i], t = ((const tvec*)target)[i];
-    fvec g;
+    fvec g[VEC / GV];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) g[e] = one(to_f32(p[e]), to_f32(t[e]));
-    if (dpred) ((fvec*)dpred)[i] = g;
+    for (int e = 0; e < VEC; ++e) g[e / GV][e % GV] = one(to_f32(p[e]), to_f32(t[e]));
+    if (dpred) {
+#pragma unroll
+      for (int h = 0; h < VEC / GV; ++h) ((fvec*)dpred)[i * (VEC / GV) + h] = g[h];
+    }
   }
   if (VEC > 1 && i0 < n - nv * VEC) {
     const long i = nv * VEC + i0;

@@ -101,6 +101,24 @@ def test_smooth_l1_tails_and_unaligned_inputs(request, kind, n, shift):
     assert rel_inf(dp.cpu().numpy(), dpo) < 1e-5
 
 
+def test_smooth_l1_gradient_buffer_on_sixteen_bytes(ctx):
+    """The wide path asks 16-byte alignment of the gradient: a buffer that starts in the middle of 32 bytes, its neighbours intact."""
+    from oracle import losses
+    from paper_2512_08537_amd import binding
+    import torch
+    n = 1048584
+    p, t = gen.normal(18, "p", (n,), 1.0, DT_BF16), gen.normal(18, "t", (n,), 1.0, DT_BF16)
+    dp_, dt_ = ctx.dev_store(p), ctx.dev_store(t)
+    buf, loss = torch.full((n + 8,), 7.0, device="cuda:0"), torch.zeros(1, device="cuda:0")
+    assert buf[4:].data_ptr() % 32 == 16
+    torch.cuda.synchronize()
+    assert binding.lib.spec_smooth_l1(ctx.h, dp_.data_ptr(), dt_.data_ptr(), n, 1.0, loss.data_ptr(), buf[4:].data_ptr()) == 0
+    ctx.sync()
+    got = buf.cpu().numpy()
+    assert rel_inf(got[4:n + 4], losses.smooth_l1(p, t)[1]) < 1e-5
+    assert (got[:4] == 7.0).all() and (got[n + 4:] == 7.0).all()
+
+
 def test_entropy_loss_outputs_are_optional_and_errors(ctx):
     from paper_2512_08537_amd.binding import FardError
     from oracle import losses
