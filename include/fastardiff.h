@@ -294,6 +294,15 @@ int spec_gemm(fard_ctx* ctx, const void* A, const void* W, const float* bias, in
  * 3 out += gate (A W + b), 4 SwiGLU over N = 2 F interleaved columns; act as in spec_gemm. */
 int spec_gemm_tile_variant(int32_t M, int32_t K, int32_t N, int32_t epi, int32_t act);
 
+/* One GEMM through the named variant of spec_gemm_tile_variant, whatever the choice would be (bf16 contexts), for tests and
+ * kernel timing.  Device pointers, 16-byte aligned: A storage type [M,K]; W storage type [K,N] row-major (re-laid on every
+ * call); bias fp32 [N] or NULL; gate fp32 [M,N] for epi 3.  out: storage type [M,N] for epi 0, fp32 [M,N] for epi 1 to 3, storage
+ * type [M,N/2] for epi 4, out[m, 32 b + j] = silu(A W)[m, 64 b + j] (A W)[m, 64 b + 32 + j].
+ * Errors: FARD_ESHAPE unless N % 32 == 0 (epi 4: 64) and K % 128 == 0 (variants 3 and 4: 256), FARD_EINVAL for bad selectors,
+ * NULLs or alignment. */
+int spec_gemm_tile(fard_ctx* ctx, const void* A, const void* W, const float* bias, const float* gate, int32_t M, int32_t K,
+                   int32_t N, int32_t epi, int32_t act, int32_t variant, void* out);
+
 /* One small-batch GEMM through the narrow-tile kernel (bf16 contexts), for tests and kernel timing: the
  * draft steps and head decodes of a round (Alg. 1 Steps 1-2) run their GEMMs through it.  All pointers
  * are device memory.  A storage type [M,K]; W storage type [K,N] row-major (re-laid on every call);

@@ -72,6 +72,7 @@ _SIGS = {
                       _vp],
     "spec_gemm": [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _vp],
     "spec_gemm_tile_variant": [_i32, _i32, _i32, _i32, _i32],
+    "spec_gemm_tile": [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp],
     "spec_gemm_narrow": [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp],
     "spec_gemm_norm": [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _f32, _i32, _vp],
     "spec_graph_enable": [_vp, _i32],
@@ -396,6 +397,13 @@ class Context:
         N = W.shape[1]
         out = self.empty((M, N), self.tdtype)
         self._chk(lib.spec_gemm(self.h, _ptr(A), _ptr(W), _ptr(bias), M, K, N, act, _ptr(out)))
+        return out
+
+    def spec_gemm_tile(self, A, W, out, variant, bias=None, gate=None, epi=0, act=0):
+        """out: preallocated (bf16 for epi 0 and 4, fp32 for epi 1..3, updated in place for epi 2, 3)."""
+        M, K = A.shape
+        N = W.shape[1]
+        self._chk(lib.spec_gemm_tile(self.h, _ptr(A), _ptr(W), _ptr(bias), _ptr(gate), M, K, N, epi, act, variant, _ptr(out)))
         return out
 
     def spec_gemm_narrow(self, A, W, out, bias=None, gate=None, epi=0, act=0, out_bf16=None):

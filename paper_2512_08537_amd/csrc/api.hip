@@ -1997,6 +1997,36 @@ int spec_gemm_tile_variant(int32_t M, int32_t K, int32_t N, int32_t epi, int32_t
   return gemm_tile_variant(a);
 }
 
+int spec_gemm_tile(fard_ctx* c, const void* A, const void* W, const float* bias, const float* gate, int32_t M, int32_t K, int32_t N,
+                   int32_t epi, int32_t act, int32_t variant, void* out) {
+  if (check_ctx(c)) return FARD_EINVAL;
+  if (!c->bf16) return fail(c, FARD_EINVAL, "spec_gemm_tile needs a bf16 context");
+  if (M < 0 || K < 1 || N < 1) return fail(c, FARD_ESHAPE, "M >= 0, K, N >= 1 required");
+  if (M == 0) return FARD_OK;
+  if (!A || !W || !out) return fail(c, FARD_EINVAL, "null argument");
+  if (act < 0 || act > 2 || epi < 0 || epi > 4 || variant < 0 || variant > 4) return fail(c, FARD_EINVAL, "selector");
+  if (epi == 3 && !gate) return fail(c, FARD_EINVAL, "epi 3 needs gate");
+  if (N % (epi == 4 ? 64 : 32) != 0 || K % (variant < 3 ? 128 : 256) != 0)
+    return fail(c, FARD_ESHAPE, "tile GEMM needs N % 32 == 0 (SwiGLU: 64), K % 128 == 0 (variants 3 and 4: 256)");
+  if ((((uintptr_t)A | (uintptr_t)out | (uintptr_t)bias | (uintptr_t)gate) & 15) != 0) return fail(c, FARD_EINVAL, "16-byte alignment required");
+  const size_t bytes = (size_t)K * N * 2;
+  if (bytes > c->gemm_tmp_bytes) {
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (c->gemm_tmp) (void)hipFree(c->gemm_tmp);
+    c->gemm_tmp = nullptr;
+    c->gemm_tmp_bytes = 0;
+    HIPCHK(c, hipMalloc(&c->gemm_tmp, bytes));
+    c->gemm_tmp_bytes = bytes;
+  }
+  HIPCHK(c, launch_pack_weight(c->stream, W, 1, N, K, N, c->gemm_tmp, 0, 1));
+  GemmArgs a;
+  a.A = A; a.lda = K; a.W = c->gemm_tmp; a.bias = bias; a.out = out; a.ldo = epi == EPI_SWIGLU ? N / 2 : N; a.gate = gate; a.ldg = N;
+  a.M = M; a.N = N; a.K = K; a.m_dev = nullptr; a.act = act; a.epi = epi;
+  { Bracket br(c, CLS_GEMM, 2.0 * M * (double)N * K, (double)K * N * 2);
+    HIPCHK(c, launch_gemm_tile(c->stream, a, variant)); }
+  return FARD_OK;
+}
+
 int spec_gemm_narrow(fard_ctx* c, const void* A, const void* W, const float* bias, const float* gate, int32_t M,
                      int32_t K, int32_t N, int32_t epi, int32_t act, void* out, void* out_bf16) {
   if (check_ctx(c)) return FARD_EINVAL;

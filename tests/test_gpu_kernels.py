@@ -59,8 +59,9 @@ def test_gemm_bf16_matches_fp64(ctx_bf16, M, K, N, act):
 @pytest.mark.parametrize("M,K,N", [(1025, 2048, 9728), (1050, 2176, 9760), (5000, 2304, 2048), (4900, 2048, 2080)])
 @pytest.mark.parametrize("act", [0, 1, 2])
 def test_gemm_bf16_square_tiles(ctx_bf16, M, K, N, act):
-    """The 256 x 256 tile kernel: one row or a few past a tile, a last column tile of one or two 32-column blocks, 32 to 36
-    k-stages.  Integer operands: every partial sum is exact in float32, so the result is the rounded integer."""
+    """Large products as the dispatch sends them (to one of the LDS-tiled kernels): one row or a few past a tile, a last column tile
+    of one or two 32-column blocks, 32 to 36 k-stages.  Integer operands: every partial sum is exact in float32, so the result
+    is the rounded integer."""
     from oracle import transformer as otf
     ctx, _ = ctx_bf16
     g = np.random.default_rng(M + N)
@@ -81,14 +82,67 @@ def test_gemm_bf16_square_tiles(ctx_bf16, M, K, N, act):
 
 # rows and columns a little past a tile, the shortest K and stage counts that are not a multiple of four among them
 @pytest.mark.parametrize("M,K,N,act", [
-    (3367, 1152, 4096, 0), (4129, 1024, 3104, 0),                                # 256 x 256
-    (1025, 1152, 4096, 0), (4129, 1280, 1056, 2), (8257, 1024, 1056, 1),         # 192 x 128
-    (3367, 1152, 1056, 0), (1537, 1152, 4096, 2),                                # 128 x 128, two stages
-    (4129, 5120, 1280, 0),                                                       # 192 x 128, four stages
-    (769, 1024, 3104, 0), (2305, 1024, 1056, 2), (2305, 2560, 1312, 0)])         # 128 x 128, four stages
+    (3367, 1152, 4096, 0), (4129, 1024, 3104, 0), (1025, 1152, 4096, 0), (4129, 1280, 1056, 2), (8257, 1024, 1056, 1),
+    (3367, 1152, 1056, 0), (1537, 1152, 4096, 2), (4129, 5120, 1280, 0), (769, 1024, 3104, 0), (2305, 1024, 1056, 2),
+    (2305, 2560, 1312, 0)])
 def test_gemm_bf16_tile_variants(ctx_bf16, M, K, N, act):
-    """Every tile of gemm_tile.hip.  Integer operands as above: exact in float32, then one bf16 rounding."""
+    """The dispatch among the LDS-tiled kernels (which one: test_gemm_rule).  Integer operands as above: exact in float32, then
+    one bf16 rounding."""
     test_gemm_bf16_square_tiles(ctx_bf16, M, K, N, act)
+
+
+# 64-row and 64-column units of a tile, LDS stages
+_TILES = {0: (4, 4, 2), 1: (3, 2, 2), 2: (2, 2, 2), 3: (3, 2, 4), 4: (2, 2, 4)}
+
+
+@pytest.mark.parametrize("epi,act", [(0, 0), (0, 1), (0, 2), (1, 0), (1, 1), (2, 0), (3, 0), (4, 0)])
+@pytest.mark.parametrize("variant", sorted(_TILES))
+def test_gemm_every_tile_with_every_epilogue(ctx_bf16, variant, epi, act):
+    """The named variant: rows one past two tiles and a few short of one, a last column tile of one 32-column block (SwiGLU: one
+    pair), the fewest stages and three times as many.  Integer operands (exact in float32); rows past M stay as they were."""
+    from oracle import transformer as otf
+    import torch
+    ctx, _ = ctx_bf16
+    wi, wj, ns = _TILES[variant]
+    g = np.random.default_rng(8 * variant + epi)
+    for M, K, N in [(128 * wi + 1, 192 * ns, 64 * wj + (64 if epi == 4 else 32)), (64 * wi - 5, 64 * ns, 128 * wj)]:
+        A, W = g.integers(-2, 3, (M, K)).astype(np.float32), g.integers(-1, 2, (K, N)).astype(np.float32)
+        b = None if epi == 4 else g.integers(-4, 5, (N,)).astype(np.float32)
+        gate = g.integers(-2, 3, (M, N)).astype(np.float32) if epi == 3 else None
+        cols = N // 2 if epi == 4 else N
+        old = g.integers(-8, 9, (M + 3, cols)).astype(np.float32)
+        out = torch.from_numpy(old).to(ctx.dev).to(torch.bfloat16 if epi in (0, 4) else torch.float32)
+        ctx.spec_gemm_tile(ctx.dev_store(A), ctx.dev_store(W), out, variant, bias=None if b is None else ctx.dev_f32(b),
+                           gate=None if gate is None else ctx.dev_f32(gate), epi=epi, act=act)
+        ctx.sync()
+        got = out.float().cpu().numpy()
+        assert np.array_equal(got[M:], old[M:])
+        acc = A @ W                                       # float32: exact for these values
+        if epi == 4:
+            gu = acc.reshape(M, N // 64, 2, 32).astype(np.float64)
+            ref = (otf.silu(gu[:, :, 0]) * gu[:, :, 1]).reshape(M, cols)
+        elif epi >= 2:
+            ref = old[:M] + (acc + b) * (1 if gate is None else gate)
+        else:
+            ref = {0: lambda v: v, 1: otf.gelu_erf, 2: otf.silu}[act]((acc + b).astype(np.float64))
+        if act == 0 and epi < 4:
+            assert np.array_equal(got[:M], gen.bf16_round(ref.astype(np.float32)) if epi == 0 else ref.astype(np.float32))
+        else:
+            # one bf16 rounding where the output is bf16, and the activation's own error of about 1e-6 of its argument
+            assert np.all(np.abs(got[:M] - ref) <= (2.0 ** -8 if epi != 1 else 0.0) * np.abs(ref) + 4e-4)
+
+
+def test_gemm_tile_refuses_what_it_cannot_take(ctx_bf16):
+    from paper_2512_08537_amd.binding import FardError
+    import torch
+    ctx, _ = ctx_bf16
+    z = lambda *s: torch.zeros(s, device=ctx.dev, dtype=torch.bfloat16)
+    for M, K, N, kw in [(64, 192, 64, dict(variant=0)), (64, 128, 64, dict(variant=4)), (64, 128, 48, dict(variant=0)),
+                        (64, 128, 96, dict(variant=0, epi=4)), (64, 128, 64, dict(variant=5)), (64, 128, 64, dict(variant=0, epi=3))]:
+        with pytest.raises(FardError):
+            ctx.spec_gemm_tile(z(M, K), z(K, N), z(M, N), **kw)
+    with pytest.raises(FardError):
+        ctx.spec_gemm_tile(z(64 * 128 + 4)[4:].view(64, 128), z(128, 64), z(64, 64), 0)
 
 
 def test_diffhead_decode_of_many_rows():
@@ -108,6 +162,11 @@ def test_diffhead_decode_of_many_rows():
     mu_o, x_o = ohd.decode(rc.head, case.W, z, eps)
     assert rel_inf(mu.cpu().numpy(), mu_o) < 2e-2
     assert rel_inf(x.cpu().numpy(), x_o) < 2e-2
+    # a device-side count inside a tile: the rows below it are the same
+    mu2, x2 = ctx.diffhead_decode(ctx.dev_store(z), ctx.dev_f32(eps), n_rows=ctx.dev_i32(np.array([1501], np.int32)))
+    ctx.sync()
+    assert np.array_equal(mu2.cpu().numpy()[:1501], mu.cpu().numpy()[:1501])
+    assert np.array_equal(x2.cpu().numpy()[:1501], x.cpu().numpy()[:1501])
     ctx.close()
 
 

@@ -159,9 +159,8 @@ def test_prefill_config1_full_size_sampled_samples():
 
 
 def test_prefill_of_thousands_of_rows_through_wide_layers():
-    """8 x 1024 rows through a 3840-wide layer: every GEMM of the layer (store, residual and SwiGLU epilogues) has
-    enough 256-column panels and 128-row tiles to take the streaming kernel's 128-row variant with XCD groups along M,
-    and the attention runs 86 passes of 12 rows (5 query heads per kv head) in one launch.  Sampled samples against the
+    """8 x 1024 rows through a 3840-wide layer: every GEMM of the layer (store, residual and SwiGLU epilogues) takes one of the
+    LDS-tiled kernels with XCD groups along M, and the attention runs 86 passes of 12 rows (5 query heads per kv head) in one launch.  Sampled samples against the
     oracle's single causal forward."""
     from synth.configs import (RoundCfg, TfCfg, HeadCfg, ACT_SWIGLU, NORM_RMS, POS_ROPE)
     tgt = TfCfg(n_layers=1, d_model=3840, n_heads=30, n_kv_heads=6, d_head=128, d_ff=2048,
@@ -218,8 +217,8 @@ def test_prefill_with_more_rows_than_a_round_through_k_slice_planes():
 
 
 def test_prefill_of_many_rows_through_tile_gemms():
-    """32 samples of up to 100 rows (2304 and more at once) through a 1024-wide layer: every product of the layer takes
-    one of the tile kernels, the residual epilogue among them; a tile spans several samples."""
+    """32 samples of up to 100 rows (2304 and more at once) through a 1024-wide layer: products of store, GELU and residual
+    epilogues that the dispatch shares out among the LDS-tiled kernels and the streaming one; a tile spans several samples."""
     from synth.configs import RoundCfg, TfCfg, HeadCfg
     from synth import configs as cf
     tf_ = TfCfg(n_layers=2, d_model=1024, n_heads=16, n_kv_heads=16, d_head=64, d_ff=4096, act=cf.ACT_GELU,
