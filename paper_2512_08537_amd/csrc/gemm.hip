@@ -691,11 +691,9 @@ hipError_t launch_wm(hipStream_t s, const GemmArgs& a) {
   if constexpr (WM >= 3) {
     // Hundreds to thousands of rows: MFMA-bound tiles, many per compute unit.  An 8-step weight ring (not 16) keeps
     // 64x256, 64x128 and 96x128 tiles within 256 registers, so two workgroups share a compute unit and one's epilogue
-    // and ramp overlap the other's MFMA loop; measured over the verify and prefill shapes (TFLOP/s, 16-step ring of
-    // the same or the previously routed tile -> 8-step): 6144 x 7168 x 5120 966 -> 1184 and 6144 x 5120 x 5120
-    // 804 -> 1062 (64x256), 6144 x 5120 x 13824 953 -> 1064 (128x128), SwiGLU 6144 x 27648 x 5120 1176 -> 1255
-    // (128x256), 8256 x 5120 x 1280 624 -> 890, 4128 x 3072 x 1024 447 -> 761 and 2304 x 5120 x 1280 685 -> 807
-    // (64x128), 576 x 5120 x 1280 442 -> 540 (96x128).
+    // and ramp overlap the other's MFMA loop.  The lines between the tiles are from a sweep over 576 to 8256 rows of 1024 to
+    // 5120 channels, when every such product came here.  Now it is what the LDS-tiled kernel (gemm_tile.hip) refuses, a K
+    // below 1024 or of no whole 128s and operands off 16 bytes, and what its prices leave: some hundreds of rows.
     auto t = [&](int bm, int bn) { return ((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
     // A few hundred rows against a matrix whose 96-row tiles would leave half the chip idle: 32 x 128 tiles (136
     // registers: three workgroups per compute unit), for residual epilogues with K split over enough workgroups to

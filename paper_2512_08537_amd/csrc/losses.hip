@@ -18,9 +18,9 @@
 // products: the scores read rows (16 bytes a lane), the gradients read the same tile transposed (ds_read_b64_tr_b16: a
 // group of 16 lanes reads 4 rows x 16 columns and gets a column of 4 a lane).  Bound: the vector instructions around the exponentials (about 7 an
 // element and walk) and the LDS reads beside the MFMAs.  With a wave fetching its fragments from memory by itself, a row a
-// lane, and transposed copies of q and k written beforehand, the grouped 8 x 40 (8) x 1024 x 128 loss took 304 us for the
-// statistics, 602 for dq, 819 for dk and 74 for the copies; now 178 (statistics and dq) and 155.  32 x 16 x 256 x 64: 21 + 34 +
-// 40 + 23 us, now 23 and 17.
+// lane, and transposed copies of q and k written beforehand, the grouped 8 x 40 (8) x 1024 x 128 loss took 285 us for the
+// statistics, 564 for dq, 810 for dk and 59 for the copies; now 180 (statistics and dq) and 164 (medians of kernel traces).  32 x
+// 16 x 256 x 64: 20 + 34 + 40 + 11 us, now 21 and 16.
 //
 // Layouts.  Register e of lane half hh of a score tile holds row 8 (e / 4) + 4 hh + e % 4 of the operand whose rows are in the
 // registers.  Registers 8 t .. 8 t + 7 are, as they stand, an operand fragment of the second product: its contraction slot

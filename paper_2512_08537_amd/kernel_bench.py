@@ -136,7 +136,7 @@ def losses():
         ctx.spec_profile_enable(False)
         us = p["ms"] / iters * 1e3
         tf = p["flops"] / (p["ms"] * 1e-3) / 1e12
-        print(json.dumps({"kernel": "spec_entropy_loss (statistics, dq, dk passes + two transposes)", "B": B, "H": H, "H_kv": Hkv, "R": R,
+        print(json.dumps({"kernel": "spec_entropy_loss (statistics with dq, loss sum, dk)", "B": B, "H": H, "H_kv": Hkv, "R": R,
                           "d_head": dh, "us_per_call": round(us, 1), "flops": p["flops"] / iters, "achieved_TFLOPs": round(tf, 1),
                           "frac_mfma": round(tf / 2500.0, 4), "loss": round(float(out[0].item()), 5)}), flush=True)
     ctx.close()
