@@ -30,8 +30,8 @@ CLASSES = ("gemm", "attention", "entropy", "other", "gemm_narrow")     # spec_pr
 
 
 def hbm_traffic_per_launch(config, kernel_class):
-    """HBM bytes per launch of a GEMM kernel class ("gemm": the streaming kernels, "gemm_narrow") from the committed
-    rocprofv3 --pmc summary of this benchmark (FETCH_SIZE and WRITE_SIZE, scaled by a plain copy kernel).  The summary
+    """HBM bytes per launch of a GEMM kernel class ("gemm": the streaming and LDS-tiled kernels, "gemm_narrow") from the
+    committed rocprofv3 --pmc summary of this benchmark (FETCH_SIZE and WRITE_SIZE, scaled by a plain copy kernel).  The summary
     names the kernel sources it was measured on (`sources_sha16`); None when no summary covers the configuration or the
     sources have changed since."""
     from paper_2512_08537_amd.build import sources_hash
@@ -145,7 +145,7 @@ def measure(cfg_idx, args, headline):
         step()
     prof = {name: ctx.spec_profile_read(i) for i, name in enumerate(CLASSES)}
     ctx.spec_profile_enable(False)
-    # the dominant kernel class: the streaming GEMM kernels (every GEMM above a few hundred rows; at configs[3] the
+    # the dominant kernel class: the streaming and LDS-tiled GEMM kernels (above a few hundred rows; at configs[3] the
     # weight stream of the 72-row verify stage) or the narrow-tile GEMM kernel (draft steps, head decodes, and at
     # configs[1] nearly every GEMM), whichever the round spends more time in; the other one is in `kernels`
     # An event pair around every launch adds the dispatch gap to each bracket: the brackets of a round sum to more
@@ -168,8 +168,9 @@ def measure(cfg_idx, args, headline):
     intensity = g["flops"] / max(g["bytes"], 1.0)
     hbm_bound = intensity < peak * 1e12 / (PEAK_HBM_GBS * 1e9)
     roofline = {"bound": "hbm" if hbm_bound else ("mfma" if rc.dtype == 1 else "alu"),
-                "kernel": ("streaming GEMM kernels (gemm_bf16_kernel, gemm_bf16_res_kernel: all instances)" if dom == "gemm"
-                           else "narrow-tile GEMM kernel (gemm_narrow_kernel: all instances)"),
+                "kernel": ("streaming and LDS-tiled GEMM kernels (gemm_bf16_kernel, gemm_bf16_res_kernel, gemm_tile_kernel: all "
+                           "instances)" if dom == "gemm" else
+                           "narrow-tile GEMM kernel (gemm_narrow_kernel: all instances)"),
                 "share_of_round_kernel_time": round(net_ms[dom] / max(sum(net_ms.values()), 1e-9), 4),
                 "achieved": round(g_gbs, 1) if hbm_bound else round(g_tflops, 3),
                 "peak": PEAK_HBM_GBS if hbm_bound else peak, "unit": "GB/s" if hbm_bound else "TFLOP/s",
