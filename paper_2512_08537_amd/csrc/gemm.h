@@ -103,6 +103,8 @@ hipError_t launch_gemm_bf16_planes(hipStream_t s, const GemmArgs& a);
 // and N are about 1024.
 bool narrow_supported(const GemmArgs& a);
 hipError_t launch_gemm_narrow(hipStream_t s, const GemmArgs& a);
+// The instances for whole K shares and fixed epilogues (narrow_exact.hip); false: none fits, nothing was launched.
+bool launch_narrow_exact(hipStream_t s, const GemmArgs& a, hipError_t* err);
 
 // Re-lay a row-major [K, N] matrix (src_is_bf16: bf16 else fp32; leading dimension ld) into MFMA
 // fragment order.  Destination n-block index = nb_offset + nb * nb_stride (lets two matrices be

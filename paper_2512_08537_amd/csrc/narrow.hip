@@ -357,6 +357,8 @@ bool narrow_supported(const GemmArgs& a) {
 
 hipError_t launch_gemm_narrow(hipStream_t s, const GemmArgs& a) {
   if (!narrow_supported(a)) return hipErrorInvalidValue;
+  hipError_t err = hipSuccess;
+  if (launch_narrow_exact(s, a, &err)) return err;
   const int kz = (a.epi == EPI_PARTIAL && a.k_slices > 1) ? a.k_slices : 1;
   const int steps = ((a.K / 32 + kz - 1) / kz + 3) / 4;      // 32-k steps of the busiest wave
   // rows beyond one workgroup's tile go to further workgroups (blockIdx.y) that re-read the weight columns
