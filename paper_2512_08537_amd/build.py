@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfastardiff.so")
-SOURCES = ["gemm.hip", "gemm_tile.hip", "narrow.hip", "narrow_exact.hip", "attn.hip", "rowops.hip", "losses.hip", "probe.hip", "api.hip"]
+SOURCES = ["gemm.hip", "gemm_tile.hip", "narrow.hip", "narrow_exact.hip", "head_chain.hip", "attn.hip", "rowops.hip", "losses.hip", "probe.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-munsafe-fp-atomics",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU ops

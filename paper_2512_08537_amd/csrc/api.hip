@@ -200,6 +200,7 @@ struct HeadW {
   // bf16 path: per block j the mod GEMM also yields c0_j = shift_j W1_j and c1_j = (1 + scale_j) W1_j (columns
   // fold_base + 2 w j and + w), so that the block's modulated norm can be folded into its first GEMM; 0: not built
   int fold_base = 0;
+  HeadBlockW* table = nullptr;             // the blocks' weights and biases for head_chain.hip (with fold_base)
 };
 struct Prof {
   bool on = false;
@@ -252,6 +253,10 @@ struct fard_ctx {
   // workspace
   float *h = nullptr, *x_in = nullptr, *ent_heads = nullptr, *h_row = nullptr;
   void* hv = nullptr;            // head: bf16 rows h (1 + scale of the next block), written by a block's second GEMM
+  void* xch = nullptr;           // head_chain.hip: exchange words of up to xch_rows rows, and the decode count in their tags
+  int xch_rows = 0;
+  unsigned* epoch = nullptr;
+  int compute_units = 0, queues = 4;
   float* hmom = nullptr;         // head: [rows][w / 16] (mean, centred squares) of h per 16-column tile
   void *u = nullptr, *qkv = nullptr, *ao = nullptr, *ff = nullptr, *z = nullptr, *ztmp = nullptr;
   RowMaps maps{};
@@ -670,6 +675,13 @@ int load_head(fard_ctx* c, Loader& ld) {
     if ((rc = ld.vec(q + "b1", w, 0.f, false, &hw.B[j].b1))) return rc;
     if ((rc = ld.vec(q + "b2", w, 0.f, false, &hw.B[j].b2))) return rc;
   }
+  if (fold) {
+    std::vector<HeadBlockW> t(Nb);
+    for (int j = 0; j < Nb; ++j) t[j] = {hw.B[j].w1, hw.B[j].w2, hw.B[j].b1, hw.B[j].b2};
+    if ((rc = dalloc<HeadBlockW>(c, &hw.table, Nb))) return rc;
+    HIPCHK(c, hipMemcpyAsync(hw.table, t.data(), sizeof(HeadBlockW) * Nb, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));            // (the host array goes away)
+  }
   if ((rc = ld.table("head.out.w", (int64_t)w * D, &hw.out_w))) return rc;
   if ((rc = ld.vec("head.out.b", D, 0.f, false, &hw.out_b))) return rc;
 
@@ -794,6 +806,21 @@ int alloc_workspace(fard_ctx* c) {
   if ((rc = dalloc_bytes(c, &c->a2, (size_t)((M + 15) / 16 * 16) * w * c->esz))) return rc;   // (whole 16-row tiles)
   if ((rc = dalloc_bytes(c, &c->hv, (size_t)((M + 15) / 16 * 16) * w * c->esz))) return rc;
   if ((rc = dalloc<float>(c, &c->hmom, (size_t)(w / 16 + 1) * M * 2))) return rc;
+  if (c->head.table != nullptr) {
+    int dev = 0;
+    HIPCHK(c, hipGetDevice(&dev));
+    HIPCHK(c, hipDeviceGetAttribute(&c->compute_units, hipDeviceAttributeMultiprocessorCount, dev));
+    if (const char* q = getenv("GPU_MAX_HW_QUEUES")) c->queues = std::max(c->queues, atoi(q));
+    c->xch_rows = M;
+    while (c->xch_rows > 0 && !head_chain_fits(c->xch_rows, w, g.head.n_blocks, g.head.n_steps, c->compute_units, c->queues)) c->xch_rows -= 1;
+    if (c->xch_rows > 0) {
+      const size_t words = head_chain_bytes(c->xch_rows, w) / 4;
+      if ((rc = dalloc_bytes(c, &c->xch, words * 4))) return rc;
+      if ((rc = dalloc<unsigned>(c, &c->epoch, 1))) return rc;
+      HIPCHK(c, launch_fill_f32(c->stream, (float*)c->xch, 0.f, words));
+      HIPCHK(c, launch_fill_i32(c->stream, (int*)c->epoch, 0, 1));
+    }
+  }
   if ((rc = dalloc<int>(c, &c->alive, g.max_batch))) return rc;
   if ((rc = dalloc<int>(c, &c->act_idx, g.max_batch))) return rc;
   if ((rc = dalloc<int>(c, &c->n_act, 4))) return rc;
@@ -1102,9 +1129,11 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
   hipStream_t s = c->stream;
   const int w = hc.width, D = hc.d_latent, Nb = hc.n_blocks, S = hc.n_steps;
   HIPCHK(c, gemm(c, z, hc.d_cond, hw.c_w, hw.c_b, c->cz, w, n, w, hc.d_cond, n_dev, EPI_STORE_F32, ACT_NONE));
+  // few rows: all blocks of a sampler step in one launch, the modulated norms folded around every block's first product
+  const bool chain = n <= c->xch_rows;
   { Bracket br(c, CLS_OTHER);
     HIPCHK(c, launch_head_prep(s, c->bf16, eps, emap, hc.temperature, D, hw.in_w, hw.in_b, c->cz, hw.temb, S, c->hh, c->sc,
-                               c->xt, w, n, n_dev)); }
+                               c->xt, w, n, n_dev, chain ? c->epoch : nullptr)); }
   // From the second block of a step on the modulated norm has no launch of its own when the rows are few (the launch
   // is then the cost; measured: a gain up to 64 rows, none above): the gate-residual GEMM of block j - 1 leaves
   // v = bf16(h (1 + scale_j)) and the tile moments of h, and block j's first GEMM multiplies v and applies mean, rstd,
@@ -1115,13 +1144,23 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
   const bool g1_narrow = c->bf16 && routes_narrow(n, w, w, EPI_STORE), g2_narrow = c->bf16 && routes_narrow(n, w, w, EPI_GATE_RESID);
   const bool a2_tiled = g1_narrow && g2_narrow;
   // the modulations of all S steps in one GEMM over S n rows (rows past the device-side count are unused)
-  const int mod_cols = fold ? hw.mod_n : (hw.fold_base > 0 ? hw.fold_base : hw.mod_n);
+  const int mod_cols = fold || chain ? hw.mod_n : (hw.fold_base > 0 ? hw.fold_base : hw.mod_n);
   HIPCHK(c, gemm(c, c->sc, w, hw.mod_all, hw.mod_b_all, c->mod, hw.mod_n, S * n, mod_cols, w, nullptr, EPI_STORE_F32, ACT_NONE));
   for (int k = 0; k < S; ++k) {
     const float t = 1.0f - (float)k / (float)S;
     const float t_next = 1.0f - (float)(k + 1) / (float)S;
     const float* modk = c->mod + (size_t)k * n * hw.mod_n;
-    for (int j = 0; j < Nb; ++j) {
+    if (chain) {
+      HeadChainArgs a;
+      a.hh = c->hh;
+      a.blocks = hw.table; a.n_blocks = Nb;
+      a.mod = modk; a.ldm = hw.mod_n; a.fold_base = hw.fold_base;
+      a.xch = c->xch; a.epoch = c->epoch; a.tag_base = 1 + 2 * Nb * k;
+      a.n = n; a.n_dev = n_dev;
+      Bracket br(c, CLS_GEMM_NARROW, 4.0 * Nb * n * (double)w * w, 2.0 * Nb * ((double)w * w * 2 + (double)n * w * 2));
+      HIPCHK(c, launch_head_chain(s, a, w));
+    }
+    for (int j = 0; j < Nb && !chain; ++j) {
       const float* mj = modk + (size_t)3 * w * j;
       const bool folded = fold && j > 0;
       if (!folded) {

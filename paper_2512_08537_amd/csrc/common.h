@@ -48,6 +48,7 @@ constexpr int DPP_SWAP1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int DPP_SWAP2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int DPP_HALF_MIRROR = 0x141; // lane i of a group of 8 reads lane 7 - i
 constexpr int DPP_MIRROR = 0x140;      // lane i of a row of 16 reads lane 15 - i
+constexpr int DPP_ROW_FIRST = 0x150;   // every lane of a row of 16 reads its lane 0
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }

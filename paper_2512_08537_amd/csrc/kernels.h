@@ -143,11 +143,11 @@ hipError_t launch_entropy_step(hipStream_t s, const float* ent_heads, int n_head
 
 // Head pieces.
 // hh[r, :] = x_t[r, :] W_in + b_in ; sc[k n + r, :] = T(silu(cz[r, :] + temb[k, :])) for the S sampler
-// times k.  x_t comes from xsrc[xmap ? xmap[r] : r] * xscale.
+// times k.  x_t comes from xsrc[xmap ? xmap[r] : r] * xscale.  epoch (optional): one more decode begins (launch_head_chain).
 hipError_t launch_head_prep(hipStream_t s, int is_bf16, const float* xsrc, const int* xmap, float xscale,
                             int D, const void* w_in, const float* b_in, const float* cz,
                             const float* temb, int S, float* hh, void* sc, float* xt_out, int w, int n,
-                            const int* n_dev);
+                            const int* n_dev, unsigned* epoch = nullptr);
 
 struct HeadStepArgs {
   const float* hh; int w;            // residual stream of the head [n, w]
@@ -167,6 +167,24 @@ struct HeadStepArgs {
   int n; const int* n_dev;
 };
 hipError_t launch_head_out(hipStream_t s, int is_bf16, const HeadStepArgs& a);
+
+// All residual blocks of one sampler step for a few rows in one launch (head_chain.hip): hh [n, w] is updated in place.
+struct HeadBlockW {                   // one block's packed weights [w, w] and biases [w]
+  const void *w1, *w2;
+  const float *b1, *b2;
+};
+struct HeadChainArgs {
+  float* hh;
+  const HeadBlockW* blocks; int n_blocks;            // device table
+  const float* mod; int ldm, fold_base;              // the step's modulation rows: shift, scale, gate of block j at 3 w j; c0, c1 at fold_base + 2 w j
+  void* xch;                                         // head_chain_bytes(n, w) bytes, zeroed once
+  const unsigned* epoch;                             // advanced by head_prep before every decode
+  int tag_base;                                      // >= 1; a decode's steps use disjoint ranges of 2 n_blocks below 4096
+  int n; const int* n_dev;
+};
+size_t head_chain_bytes(int rows, int w);
+bool head_chain_fits(int n, int w, int n_blocks, int n_steps, int compute_units, int queues);
+hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w);
 
 // out[n] = act(sum_k in[k] W[k, n] + b[n]) for one fp32 vector (time embedding at init).
 hipError_t launch_matvec(hipStream_t s, int is_bf16, const float* in, const void* W, const float* b,

@@ -928,7 +928,8 @@ __global__ __launch_bounds__(256) void head_prep_kernel(const float* __restrict_
                                                         const float* __restrict__ b_in, const float* __restrict__ cz,
                                                         const float* __restrict__ temb, int S, float* __restrict__ hh,
                                                         T* __restrict__ sc, float* __restrict__ xt_out, int w, int n,
-                                                        const int* n_dev) {
+                                                        const int* n_dev, unsigned* __restrict__ epoch) {
+  if (epoch != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *epoch += 1;
   const int ne = eff_rows(n, n_dev);
   const int r = blockIdx.y;
   if (r >= ne) return;
@@ -1477,15 +1478,15 @@ hipError_t launch_entropy_step(hipStream_t s, const float* ent_heads, int n_head
 
 hipError_t launch_head_prep(hipStream_t s, int is_bf16, const float* xsrc, const int* xmap, float xscale, int D,
                             const void* w_in, const float* b_in, const float* cz, const float* temb, int S, float* hh,
-                            void* sc, float* xt_out, int w, int n, const int* n_dev) {
+                            void* sc, float* xt_out, int w, int n, const int* n_dev, unsigned* epoch) {
   if (n <= 0) return hipSuccess;
   dim3 grid((w + 255) / 256, n);
   if (is_bf16)
     head_prep_kernel<bf16><<<grid, 256, 0, s>>>(xsrc, xmap, xscale, D, (const bf16*)w_in, b_in, cz, temb, S, hh,
-                                                (bf16*)sc, xt_out, w, n, n_dev);
+                                                (bf16*)sc, xt_out, w, n, n_dev, epoch);
   else
     head_prep_kernel<float><<<grid, 256, 0, s>>>(xsrc, xmap, xscale, D, (const float*)w_in, b_in, cz, temb, S, hh,
-                                                 (float*)sc, xt_out, w, n, n_dev);
+                                                 (float*)sc, xt_out, w, n, n_dev, epoch);
   return hipGetLastError();
 }
 

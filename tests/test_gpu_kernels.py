@@ -543,6 +543,36 @@ def test_diffhead_decode_of_72_rows_in_tile_order():
     ctx.close()
 
 
+@pytest.mark.parametrize("w,n,live", [(1024, 1, 1), (1024, 4, 3), (1024, 5, 5), (1024, 8, 1), (1024, 9, 9), (1024, 16, 16),
+                                      (1024, 17, 17), (1024, 32, 16), (1280, 3, 3), (1280, 8, 7), (1280, 16, 13), (1280, 17, 17),
+                                      (1536, 2, 2), (1536, 8, 8), (1536, 9, 0), (1536, 16, 16), (1536, 17, 17)])
+def test_diffhead_decode_with_resident_blocks(w, n, live):
+    """Widths and row counts on both sides of the rule that takes all blocks of a sampler step in one launch: against the
+    oracle, with a device-side row count, bit-equal on a second decode with other rows in between."""
+    from oracle import head as ohd
+    from synth.configs import RoundCfg, TfCfg, HeadCfg
+    tf = TfCfg(n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, d_head=64, d_ff=256, max_pos=32)
+    rc = RoundCfg(name="head-chain", target=tf, draft=tf, head=HeadCfg(3, w, 128, n_steps=2), K=8, max_batch=4, max_ctx=32,
+                  entropy_layer=1, batch=4, n_ctx=8)
+    case = build_case(rc, seed=9)
+    ctx = make_ctx(case)
+    D, S = rc.head.d_latent, rc.head.n_steps
+    z = gen.normal(17, f"z{w}.{n}", (n, rc.head.d_cond), 1.0, rc.dtype)
+    eps = gen.noise(17, f"e{w}.{n}", (S + 1, n, D))
+    cnt = ctx.dev_i32(np.array([live], np.int32))
+    mu, x = (t.clone() for t in ctx.diffhead_decode(ctx.dev_store(z), ctx.dev_f32(eps), n_rows=cnt))
+    ctx.diffhead_decode(ctx.dev_store(-z), ctx.dev_f32(eps))
+    mu2, x2 = ctx.diffhead_decode(ctx.dev_store(z), ctx.dev_f32(eps), n_rows=cnt)
+    ctx.sync()
+    assert np.array_equal(mu.cpu().numpy()[:live], mu2.cpu().numpy()[:live])
+    assert np.array_equal(x.cpu().numpy()[:live], x2.cpu().numpy()[:live])
+    if live:
+        mu_o, x_o = ohd.decode(rc.head, case.W, z[:live], eps[:, :live])
+        assert rel_inf(mu.cpu().numpy()[:live], mu_o) < 2e-2
+        assert rel_inf(x.cpu().numpy()[:live], x_o) < 2e-2
+    ctx.close()
+
+
 def test_head_closed_form_zero_weights():
     """All head weights zero except the output bias: mu = temperature*eps0 - b_out (1 step)."""
     case = build_case("ln-gelu-bf16", seed=1)
