@@ -1027,7 +1027,7 @@ __global__ __launch_bounds__(256) void head_out_kernel(HeadStepArgs a) {
       if (!a.last) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-          const int c = ((int)threadIdx.x + 256 * j < w) ? (int)threadIdx.x + 256 * j : (int)threadIdx.x;
+          const int c = ((int)threadIdx.x + 256 * j < w) ? (int)threadIdx.x + 256 * j : 0;   // (a row may have fewer columns than the workgroup threads)
           bjn[j] = a.b_in[c];
 #pragma unroll
           for (int k = 0; k < 16; ++k) wvn[j][k] = w_in[(size_t)k * w + c];
