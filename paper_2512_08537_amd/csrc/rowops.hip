@@ -2,11 +2,14 @@
 // pre-filter, head sampler pieces, accept test.  Memory-bound or tiny; one wave or one
 // workgroup per row, fp32 arithmetic, vector loads where rows are long.
 #include "kernels.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace fard {
 
 namespace {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // ================================================================== row maps
 __global__ __launch_bounds__(256) void build_rows_kernel(const int* n_base, int add, int B, int K, int D,
@@ -171,22 +174,17 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return t;
 }
 
-// both sums of a 256-thread workgroup in one round (two barriers)
-__device__ __forceinline__ void block_sum2(float& a, float& b, float* red) {
-  a = wave_sum(a);
-  b = wave_sum(b);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) { red[wave] = a; red[4 + wave] = b; }
-  __syncthreads();
-  a = red[0] + red[1] + red[2] + red[3];
-  b = red[4] + red[5] + red[6] + red[7];
+template <typename T>
+__device__ __forceinline__ f32x4 load4f(const T* p);
+template <>
+__device__ __forceinline__ f32x4 load4f<float>(const float* p) { return *(const f32x4*)p; }
+template <>
+__device__ __forceinline__ f32x4 load4f<bf16>(const bf16* p) {
+  const bf16x4 t = *(const bf16x4*)p;
+  return f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
 }
 
-// One workgroup per row.  The row is read once with 16-byte loads and stays in registers for the
-// statistics and the output pass (d <= 256 * 4 * NORM_VPT); everything a thread needs is requested
-// before the first reduction so that the loads overlap.
-constexpr int NORM_VPT = 8;         // largest instance; the launcher picks the smallest VPT that covers d
+constexpr int NORM_MAX_D = 8192;
 template <typename T>
 __device__ __forceinline__ void store4(T* p, float a, float b, float c, float d);
 template <>
@@ -200,102 +198,106 @@ __device__ __forceinline__ void store4<bf16>(bf16* p, float a, float b, float c,
   *(bf16x4*)p = v;
 }
 
-template <typename T, int VPT>
-__global__ __launch_bounds__(256) void norm_kernel(const float* __restrict__ h, int d, int M, const int* m_dev,
-                                                   int norm_type, float eps, const float* __restrict__ g,
-                                                   const float* __restrict__ b, const float* __restrict__ shift,
-                                                   const float* __restrict__ scale, int ldm,
-                                                   const int* __restrict__ in_map, T* __restrict__ out,
-                                                   const float* __restrict__ parts, int n_parts, size_t part_stride,
-                                                   float* __restrict__ h_wb, int out_tiled) {
-  __shared__ float red[8];
-  const int Me = eff_rows(M, m_dev);
+// Both sums of a workgroup of up to 16 waves behind one barrier (red: 2 floats a wave, not used before in the kernel).
+__device__ __forceinline__ void block_sum2(float& a, float& b, float* red) {
+  a = wave_sum(a);
+  b = wave_sum(b);
+  if ((threadIdx.x & 63) == 0) *(f32x2*)(red + 2 * (threadIdx.x >> 6)) = f32x2{a, b};
+  __syncthreads();
+  const int nw = blockDim.x >> 6;
+  a = b = 0.f;
+  for (int i = 0; i < nw; ++i) {
+    const f32x2 t = *(const f32x2*)(red + 2 * i);
+    a += t[0];
+    b += t[1];
+  }
+}
+
+// One workgroup per row, a thread per VPT pieces of four columns; the row stays in registers.  Few rows: bound by the
+// launch's own chain of dependent reads, so everything a thread needs (row, planes, gain and bias or the row's modulation,
+// the device-side row count) is requested before the first wait.  (One row of 1024 took 3.7 us with gain and bias asked for
+// behind the reduction and the planes in a run-time loop.)  MOD: y = n (1 + ga[r]) + be[r] instead of n ga + be.  NP: planes
+// of the preceding GEMM's K slices to add to the row first (deferred residual update, written back to h_wb), -1: n_parts.
+template <typename T, int VPT, bool MOD, int NP>
+__global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void norm_kernel(const float* h, const float* __restrict__ ga,
+                                                                     const float* __restrict__ be, T* __restrict__ out, int d,
+                                                                     int ldm, int M, const int* m_dev, const int* __restrict__ in_map,
+                                                                     const float* __restrict__ parts, int n_parts, size_t part_stride,
+                                                                     float* h_wb, int rms, float eps, int out_tiled) {
+  __shared__ __attribute__((aligned(8))) float red[32];
   const int r = blockIdx.x;
-  if (r >= Me) return;
-  const float* row = h + (size_t)(in_map ? in_map[r] : r) * d;
+  // (rows past the device-side count are read, not written: the buffers hold M rows, and a stale index is clamped to them)
+  unsigned src = (unsigned)r;
+  if (in_map != nullptr) {
+    src = (unsigned)in_map[r];
+    src = src < (unsigned)M ? src : (unsigned)M - 1;
+  }
+  const size_t ro = (size_t)src * d;
   const int n4 = d >> 2;                                   // d % 4 == 0 (checked on the host)
-  f32x4 x[VPT];
-  float s = 0.f;
+  const float pivot = h[ro];
+  f32x4 x[VPT], gv[VPT], bv[VPT];
+  // (an absent gain or bias is a re-read of the row: a select on the address, not a branch)
+  const float* gp = ga != nullptr ? ga + (MOD ? (size_t)r * ldm : 0) : h + ro;
+  const float* bp = be != nullptr ? be + (MOD ? (size_t)r * ldm : 0) : h + ro;
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
-    const int c4 = threadIdx.x + i * 256;
-    x[i] = (c4 < n4) ? ((const f32x4*)row)[c4] : f32x4{0.f, 0.f, 0.f, 0.f};
+    const int c4 = threadIdx.x + i * blockDim.x;
+    const int cc = (c4 < n4 ? c4 : 0) * 4;
+    x[i] = *(const f32x4*)(h + ro + cc);
+    gv[i] = *(const f32x4*)(gp + cc);
+    bv[i] = *(const f32x4*)(bp + cc);
   }
-  // the row's modulation (AdaLN) is requested with the row itself: one memory round trip instead of a second one after
-  // the reduction
-  f32x4 scv[VPT], shv[VPT];
-  if (scale) {
+  if constexpr (NP > 0) {
+    f32x4 t[NP][VPT];
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-      const int c4 = threadIdx.x + i * 256;
-      const int cc = c4 < n4 ? c4 : 0;
-      scv[i] = *(const f32x4*)(scale + (size_t)r * ldm + cc * 4);
-      shv[i] = *(const f32x4*)(shift + (size_t)r * ldm + cc * 4);
-    }
-  }
-  if (n_parts > 0) {
-    // deferred residual update: the preceding GEMM left K-slice partial sums; fold them in (and write the row back).
-    // Four planes at a time, all their loads requested before the first is added: plane by plane the kernel waited for
-    // memory once per plane (10-14 us for a 5120-wide row with 5 planes).
-    const size_t ro = (size_t)(in_map ? in_map[r] : r) * d;
-    for (int p0 = 0; p0 < n_parts; p0 += 4) {
-      f32x4 t[4][VPT];
+    for (int q = 0; q < NP; ++q)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int p = p0 + q < n_parts ? p0 + q : n_parts - 1;
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-          const int c4 = threadIdx.x + i * 256;
-          t[q][i] = *(const f32x4*)(parts + (size_t)p * part_stride + ro + (c4 < n4 ? c4 : 0) * 4);
-        }
+      for (int i = 0; i < VPT; ++i) {
+        const int c4 = threadIdx.x + i * blockDim.x;
+        t[q][i] = *(const f32x4*)(parts + q * part_stride + ro + (c4 < n4 ? c4 : 0) * 4);
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (p0 + q < n_parts) {
+    for (int q = 0; q < NP; ++q)
 #pragma unroll
-          for (int i = 0; i < VPT; ++i) x[i] += t[q][i];
-        }
-      }
-    }
+      for (int i = 0; i < VPT; ++i) x[i] += t[q][i];
   }
-  // one reduction round for both moments, taken about a pivot (the row's first element) so that
+  if constexpr (NP < 0) {
+    for (int q = 0; q < n_parts; ++q)
+#pragma unroll
+      for (int i = 0; i < VPT; ++i) {
+        const int c4 = threadIdx.x + i * blockDim.x;
+        x[i] += *(const f32x4*)(parts + q * part_stride + ro + (c4 < n4 ? c4 : 0) * 4);
+      }
+  }
+  const int Me = eff_rows(M, m_dev);
+  if (r >= Me) return;
+  // one reduction round for both moments, taken about a pivot (the stored row's first element) so that
   // E[(x-p)^2] - E[x-p]^2 does not cancel for rows with a large mean
-  const float pivot = row[0];
-  float q = 0.f;
+  float s = 0.f, q = 0.f;
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
-    const int c4 = threadIdx.x + i * 256;
-    if (c4 < n4) {
+    if ((int)(threadIdx.x + i * blockDim.x) < n4) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) { const float t = x[i][e] - pivot; s += t; q = fmaf(t, t, q); }
     }
   }
   block_sum2(s, q, red);
-  if (n_parts > 0 && h_wb != nullptr) {
-    // the completed row goes back only now: every thread has read the pivot (element 0 of the old row) before the
-    // barriers of the reduction
-    const size_t ro = (size_t)(in_map ? in_map[r] : r) * d;
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-      const int c4 = threadIdx.x + i * 256;
-      if (c4 < n4) *(f32x4*)(h_wb + ro + c4 * 4) = x[i];
-    }
-  }
   const float m1 = s / (float)d, m2 = q / (float)d;
-  const float mean = (norm_type == 0) ? pivot + m1 : 0.f;
+  const float mean = rms ? 0.f : pivot + m1;
   // RMS norm: E[x^2] = E[(x-p)^2] + 2 p E[x-p] + p^2
-  const float var = (norm_type == 0) ? fmaxf(m2 - m1 * m1, 0.f) : fmaxf(m2 + 2.f * pivot * m1 + pivot * pivot, 0.f);
+  const float var = rms ? fmaxf(m2 + 2.f * pivot * m1 + pivot * pivot, 0.f) : fmaxf(m2 - m1 * m1, 0.f);
   const float rstd = 1.0f / sqrtf(var + eps);
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
-    const int c4 = threadIdx.x + i * 256;
+    const int c4 = threadIdx.x + i * blockDim.x;
     if (c4 >= n4) continue;
+    // the completed row goes back only here: every thread has the pivot (element 0 of the old row) since the barrier
+    if (NP != 0 && h_wb != nullptr) *(f32x4*)(h_wb + ro + c4 * 4) = x[i];
     f32x4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = (x[i][e] - mean) * rstd;
-    if (g) { const f32x4 v = ((const f32x4*)g)[c4]; y *= v; }
-    if (b) { const f32x4 v = ((const f32x4*)b)[c4]; y += v; }
-    if (scale) y = y * (1.0f + scv[i]) + shv[i];
+    if (ga != nullptr) y = MOD ? y * (1.0f + gv[i]) : y * gv[i];
+    if (be != nullptr) y += bv[i];
     store4<T>(out + (out_tiled ? tile_offset(r, c4 * 4, d) : (size_t)r * d + c4 * 4), y[0], y[1], y[2], y[3]);
   }
 }
@@ -921,32 +923,44 @@ __global__ __launch_bounds__(256) void catchup_pack_kernel(const int* __restrict
 
 // ================================================================== head pieces
 // First sampler step: hh = x_t W_in + b_in, x_t kept, and the conditioning silu(cz + temb_k) of all S steps
-// (step k in rows [k n, (k + 1) n) of sc), so that one GEMM produces the modulations of every step.
+// (step k in rows [k n, (k + 1) n) of sc), so that one GEMM produces the modulations of every step.  A thread takes four
+// columns (w % 4 == 0, D <= 16; checked at launch).
 template <typename T>
-__global__ __launch_bounds__(256) void head_prep_kernel(const float* __restrict__ xsrc, const int* __restrict__ xmap,
-                                                        float xscale, int D, const T* __restrict__ w_in,
-                                                        const float* __restrict__ b_in, const float* __restrict__ cz,
-                                                        const float* __restrict__ temb, int S, float* __restrict__ hh,
-                                                        T* __restrict__ sc, float* __restrict__ xt_out, int w, int n,
-                                                        const int* n_dev, unsigned* __restrict__ epoch) {
+__global__ __launch_bounds__(256) void head_prep_kernel(const float* __restrict__ cz, const T* __restrict__ w_in,
+                                                        const float* __restrict__ b_in, const float* __restrict__ temb, int w,
+                                                        int n, int D, int S, const float* __restrict__ xsrc,
+                                                        const int* __restrict__ xmap, float xscale, float* __restrict__ hh,
+                                                        T* __restrict__ sc, float* __restrict__ xt_out, const int* n_dev,
+                                                        unsigned* __restrict__ epoch) {
   if (epoch != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *epoch += 1;
+  const int r = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * 4, cc = c < w ? c : 0;
+  const f32x4 czv = *(const f32x4*)(cz + (size_t)r * w + cc);
+  f32x4 wv[16], v = *(const f32x4*)(b_in + cc);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) wv[k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * w + cc);
   const int ne = eff_rows(n, n_dev);
-  const int r = blockIdx.y;
   if (r >= ne) return;
-  const int c = blockIdx.x * 256 + threadIdx.x;
   const float* xr = xsrc + (size_t)(xmap ? xmap[r] : r) * D;
+  float xv[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) xv[k] = xr[k < D ? k : 0];
   if (c < w) {
-    const float czv = cz[(size_t)r * w + c];
-    hh[(size_t)r * w + c] = in_proj<T>(b_in[c], xr, xscale, D, w_in, w, c);
-    for (int k = 0; k < S; ++k) sc[((size_t)k * n + r) * w + c] = from_f32<T>(silu(czv + temb[(size_t)k * w + c]));
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v += (k < D) ? wv[k] * (xv[k] * xscale) : f32x4{0.f, 0.f, 0.f, 0.f};
+    *(f32x4*)(hh + (size_t)r * w + c) = v;
+    for (int k = 0; k < S; ++k) {
+      const f32x4 t = czv + *(const f32x4*)(temb + (size_t)k * w + c);
+      store4<T>(sc + ((size_t)k * n + r) * w + c, silu(t[0]), silu(t[1]), silu(t[2]), silu(t[3]));
+    }
   }
   if (xt_out && blockIdx.x == 0 && (int)threadIdx.x < D) xt_out[(size_t)r * D + threadIdx.x] = xr[threadIdx.x] * xscale;
 }
 
-// One workgroup per row: final AdaLN, output projection to D <= 16 components, sampler update, and (when
-// another step follows) the input projection of the new x_t into hh.  The row, its modulation and the
-// projection rows are fetched with 16-byte loads issued up front (w <= 256 * 4 * HO_VPT).
-constexpr int HO_VPT = 2;
+// One workgroup per row: final AdaLN, output projection to D <= 16 components, sampler update, and (when another step
+// follows) the input projection of the new x_t into hh.  A thread has four columns (w <= 2048); everything it needs of the
+// row, its modulation, both projections and the sampler update is requested before the first wait.  The 16 sums over the
+// columns go by quads of lanes, then 16 threads a component through LDS.  (With every sum over the wave by itself, the next
+// step's projection read two bytes at a time and the noise row asked for in the middle a row of 1024 took 6.9 us.)
 template <typename T>
 __device__ __forceinline__ void load_w16(const T* p, float (&o)[16]);
 template <>
@@ -968,82 +982,48 @@ __device__ __forceinline__ void load_w16<bf16>(const bf16* p, float (&o)[16]) {
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void head_out_kernel(HeadStepArgs a) {
-  __shared__ float red[8];
-  __shared__ float part[4][16];
+template <typename T, bool D16, bool LAST>
+__global__ __launch_bounds__(512) void head_out_kernel(const float* hh, const float* __restrict__ scale,
+                                                       const float* __restrict__ shift, int w, int ldm, int D, int n,
+                                                       const T* __restrict__ w_out, const T* __restrict__ w_in, HeadStepArgs a) {
+  __shared__ __attribute__((aligned(8))) float red[32];
+  __shared__ float part[128 * 17];                         // [quad of threads][component]
   __shared__ float xs[16];
-  const int ne = eff_rows(a.n, a.n_dev);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = blockIdx.x;
+  const int tid = threadIdx.x, r = blockIdx.x, n4 = w >> 2;
+  const bool on = tid < n4;
+  const int c = (on ? tid : 0) * 4;
+  const float pivot = hh[(size_t)r * w];
+  const f32x4 x = *(const f32x4*)(hh + (size_t)r * w + c);
+  const f32x4 sc = *(const f32x4*)(scale + (size_t)r * ldm + c), sh = *(const f32x4*)(shift + (size_t)r * ldm + c);
+  float wo[4][16];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (D16) {
+      load_w16<T>(w_out + (size_t)(c + e) * 16, wo[e]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) wo[e][k] = to_f32(w_out[(size_t)(c + e) * D + (k < D ? k : 0)]);
+    }
+  }
+  f32x4 wi[LAST ? 1 : 16], bi;
+  if constexpr (!LAST) {
+    bi = *(const f32x4*)(a.b_in + c);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) wi[k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * w + c);
+  }
+  // threads 16 k .. 16 k + 15 finish component k
+  const int k = (tid >> 4) & 15, kc = k < D ? k : 0;
+  const bool need_eps = LAST || a.renoise;
+  const float p_bout = a.b_out[kc], p_xt = a.xt[(size_t)r * D + kc];
+  const int ne = eff_rows(n, a.n_dev);
   if (r >= ne) return;
-  const int w = a.w, D = a.D, n4 = w >> 2;
-  const float* row = a.hh + (size_t)r * w;
-  const float* scp = a.scale + (size_t)r * a.ldm;
-  const float* shp = a.shift + (size_t)r * a.ldm;
-  f32x4 x[HO_VPT], sc[HO_VPT], sh[HO_VPT];
-#pragma unroll
-  for (int i = 0; i < HO_VPT; ++i) {
-    const int c4 = threadIdx.x + i * 256;
-    const bool ok = c4 < n4;
-    const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-    x[i] = ok ? ((const f32x4*)row)[c4] : z4;
-    sc[i] = ok ? ((const f32x4*)scp)[c4] : z4;
-    sh[i] = ok ? ((const f32x4*)shp)[c4] : z4;
-  }
-  // Operands of the later phases (output projection, sampler update, next step's input projection) are requested
-  // here, before the first barrier, when they fit in registers (bf16, D = 16, w <= 2048): the kernel then waits
-  // for memory once instead of once per phase.
-  constexpr bool CAN_PRE = sizeof(T) == 2;
-  constexpr int NJ = 4 * HO_VPT;                          // columns per thread of the next step's input projection
-  const bool pre = CAN_PRE && D == 16 && w <= 256 * NJ;
-  const T* W = (const T*)a.w_out;
-  const T* w_in = (const T*)a.w_in;
-  bf16x8 wq[HO_VPT][4][2];
-  T wvn[NJ][16];
-  float bjn[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) bjn[j] = 0.f;
-  float p_xt = 0.f, p_eps = 0.f, p_bout = 0.f;
-  size_t p_oi = 0;
-  if constexpr (CAN_PRE) {
-    if (pre) {
-#pragma unroll
-      for (int i = 0; i < HO_VPT; ++i) {
-        const int c4 = threadIdx.x + i * 256;
-        const int cc = (c4 < n4) ? c4 : 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int hq = 0; hq < 2; ++hq) wq[i][e][hq] = ((const bf16x8*)(W + (size_t)(cc * 4 + e) * 16))[hq];
-      }
-      if (threadIdx.x < 16) {
-        const int k = threadIdx.x;
-        p_bout = a.b_out[k];
-        p_xt = a.xt[(size_t)r * 16 + k];
-        p_oi = (size_t)(a.omap ? a.omap[r] : r) * 16 + k;
-        if (a.last || a.renoise) p_eps = a.eps_next[(size_t)(a.emap ? a.emap[r] : r) * 16 + k];
-      }
-      if (!a.last) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          const int c = ((int)threadIdx.x + 256 * j < w) ? (int)threadIdx.x + 256 * j : 0;   // (a row may have fewer columns than the workgroup threads)
-          bjn[j] = a.b_in[c];
-#pragma unroll
-          for (int k = 0; k < 16; ++k) wvn[j][k] = w_in[(size_t)k * w + c];
-        }
-      }
-    }
-  }
+  const int er = a.emap ? a.emap[r] : r, orow = LAST && a.omap ? a.omap[r] : r;
+  const float p_eps = need_eps ? a.eps_next[(size_t)er * D + kc] : 0.f;
   // both moments in one reduction round, about a pivot (see norm_kernel)
-  const float pivot = row[0];
   float s = 0.f, q = 0.f;
+  if (on) {
 #pragma unroll
-  for (int i = 0; i < HO_VPT; ++i) {
-    if ((int)threadIdx.x + i * 256 < n4) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { const float t = x[i][e] - pivot; s += t; q = fmaf(t, t, q); }
-    }
+    for (int e = 0; e < 4; ++e) { const float t = x[e] - pivot; s += t; q = fmaf(t, t, q); }
   }
   block_sum2(s, q, red);
   const float m1 = s / (float)w;
@@ -1051,95 +1031,46 @@ __global__ __launch_bounds__(256) void head_out_kernel(HeadStepArgs a) {
   const float rstd = 1.0f / sqrtf(fmaxf(q / (float)w - m1 * m1, 0.f) + 1e-6f);
   float acc[16];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) acc[k] = 0.f;
+  for (int j = 0; j < 16; ++j) acc[j] = 0.f;
 #pragma unroll
-  for (int i = 0; i < HO_VPT; ++i) {
-    const int c4 = threadIdx.x + i * 256;
-    if (c4 >= n4) continue;
+  for (int e = 0; e < 4; ++e) {
+    const float y = on ? (x[e] - mean) * rstd * (1.0f + sc[e]) + sh[e] : 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float y = (x[i][e] - mean) * rstd * (1.0f + sc[i][e]) + sh[i][e];
-      const int c = c4 * 4 + e;
-      if (CAN_PRE && pre) {
+    for (int j = 0; j < 16; ++j) acc[j] += y * wo[e][j];
+  }
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc[k] += y * (float)wq[i][e][k >> 3][k & 7];
-      } else if (D == 16) {
-        float wr[16];
-        load_w16<T>(W + (size_t)c * 16, wr);
+  for (int j = 0; j < 16; ++j) {
+    acc[j] += dpp_move<DPP_SWAP1>(acc[j]);
+    acc[j] += dpp_move<DPP_SWAP2>(acc[j]);
+  }
+  if ((tid & 3) == 0) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc[k] += y * wr[k];
+    for (int j = 0; j < 16; ++j) part[(tid >> 2) * 17 + j] = acc[j];
+  }
+  __syncthreads();
+  if (tid < 256) {
+    float v = 0.f;
+    for (int g = tid & 15; g < (int)blockDim.x >> 2; g += 16) v += part[g * 17 + k];
+    v = row16_sum(v) + p_bout;
+    const float x0 = p_xt - a.t * v;
+    if ((tid & 15) == 0 && k < D) {
+      if constexpr (LAST) {
+        a.mu[(size_t)orow * D + k] = x0;
+        a.x[(size_t)orow * D + k] = x0 + a.sigma * p_eps;
       } else {
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-          if (k < D) acc[k] += y * to_f32(W[(size_t)c * D + k]);
+        const float e = a.renoise ? p_eps : p_xt + (1.0f - a.t) * v;
+        const float xn = (1.0f - a.t_next) * x0 + a.t_next * e;
+        a.xt[(size_t)r * D + k] = xn;
+        xs[k] = xn;
       }
     }
   }
+  if constexpr (!LAST) {
+    __syncthreads();
+    // input projection of the next step
 #pragma unroll
-  for (int k = 0; k < 16; ++k) acc[k] = wave_sum(acc[k]);
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < 16; ++k) part[wave][k] = acc[k];
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < D) {
-    const int k = threadIdx.x;
-    const float v = part[0][k] + part[1][k] + part[2][k] + part[3][k] + (pre ? p_bout : a.b_out[k]);
-    const size_t xi = (size_t)r * D + k;
-    const size_t ei = pre ? 0 : (size_t)(a.emap ? a.emap[r] : r) * D + k;
-    const size_t oi = pre ? p_oi : (size_t)(a.omap ? a.omap[r] : r) * D + k;
-    const float xt = pre ? p_xt : a.xt[xi];
-    const float x0 = xt - a.t * v;
-    if (a.last) {
-      a.mu[oi] = x0;
-      a.x[oi] = x0 + a.sigma * (pre ? p_eps : a.eps_next[ei]);
-    } else {
-      const float e = a.renoise ? (pre ? p_eps : a.eps_next[ei]) : xt + (1.0f - a.t) * v;
-      const float xn = (1.0f - a.t_next) * x0 + a.t_next * e;
-      a.xt[xi] = xn;
-      xs[k] = xn;
-    }
-  }
-  if (a.last) return;
-  __syncthreads();
-  // input projection of the next step
-  if (CAN_PRE && pre) {
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int c = threadIdx.x + 256 * j;
-      if (c >= w) continue;
-      float v = bjn[j];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) v += xs[k] * (float)wvn[j][k];
-      a.hh_next[(size_t)r * w + c] = v;
-    }
-  } else if (D <= 16) {
-    // 4 columns per thread and pass, all 64 weight loads in flight together
-    float xr[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) xr[k] = (k < D) ? xs[k] : 0.f;
-    for (int c0 = threadIdx.x; c0 < w; c0 += 1024) {
-      float wv[4][16], bj[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = (c0 + 256 * j < w) ? c0 + 256 * j : c0;
-        bj[j] = a.b_in[c];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) wv[j][k] = to_f32(w_in[(size_t)(k < D ? k : 0) * w + c]);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = c0 + 256 * j;
-        if (c >= w) continue;
-        float v = bj[j];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v += xr[k] * wv[j][k];
-        a.hh_next[(size_t)r * w + c] = v;
-      }
-    }
-  } else {
-    for (int c = threadIdx.x; c < w; c += 256)
-      a.hh_next[(size_t)r * w + c] = in_proj<T>(a.b_in[c], (const float*)xs, 1.0f, D, w_in, w, c);
+    for (int j = 0; j < 16; ++j) bi += (j < D) ? wi[j] * xs[j < D ? j : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
+    if (on) *(f32x4*)(a.hh_next + (size_t)r * w + c) = bi;
   }
 }
 
@@ -1257,78 +1188,85 @@ __global__ __launch_bounds__(256) void add_parts_kernel(float* __restrict__ h, c
   }
 }
 
-template <typename T>
-__device__ __forceinline__ f32x4 load4f(const T* p);
-template <>
-__device__ __forceinline__ f32x4 load4f<float>(const float* p) { return *(const f32x4*)p; }
-template <>
-__device__ __forceinline__ f32x4 load4f<bf16>(const bf16* p) {
-  const bf16x4 t = *(const bf16x4*)p;
-  return f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
-}
-
 // embed + the first norm of layer 0 in one launch: one workgroup per row computes h[r, :] as embed_kernel does,
 // keeps it in registers, writes it, and writes u[r, :] = norm(h[r, :]) g + b (what norm_kernel would).
 template <typename T, int VPT>
-__global__ __launch_bounds__(256) void embed_norm_kernel(const float* __restrict__ x, int ldx, int D, const T* __restrict__ w_in,
-                                                         const float* __restrict__ b_in, const T* __restrict__ pos_table,
-                                                         const int* __restrict__ row_pos, const T* __restrict__ cond_table,
-                                                         const int* __restrict__ cond_id, float* __restrict__ h, int d, int M,
-                                                         const int* m_dev, int norm_type, float eps, const float* __restrict__ g,
-                                                         const float* __restrict__ b, T* __restrict__ u, int u_tiled) {
-  __shared__ float red[8];
-  const int Me = eff_rows(M, m_dev);
+__global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void embed_norm_kernel(const float* __restrict__ x, const T* __restrict__ w_in,
+                                                         const float* __restrict__ b_in, int ldx, int D, int d,
+                                                         const T* __restrict__ pos_table, const int* __restrict__ row_pos,
+                                                         const T* __restrict__ cond_table, const int* __restrict__ cond_id,
+                                                         float* h, int M, const int* m_dev, int norm_type, float eps,
+                                                         const float* __restrict__ g, const float* __restrict__ b, T* __restrict__ u,
+                                                         int u_tiled) {
+  __shared__ float red[2][16];
   const int r = blockIdx.x;
-  if (r >= Me) return;
-  const int n4 = d >> 2;
-  const int id = cond_id ? cond_id[r] : -1;
-  const int pos = (pos_table && id < 0) ? row_pos[r] : 0;
-  f32x4 v[VPT];
-  float s = 0.f;
+  const int n4 = d >> 2, nw = blockDim.x >> 6;
+  // (everything but the position row and an id's row is requested before the first wait; an absent vector is a re-read of
+  // the row's place in h, which holds d floats whatever they are)
+  const float* xz = h + (size_t)r * d;
+  const int id0 = cond_id ? cond_id[r] : -1;
+  const int pos0 = pos_table ? row_pos[r] : 0;
   float xr[16];                                            // D <= 16 (checked on the host)
 #pragma unroll
-  for (int k = 0; k < 16; ++k) xr[k] = (k < D) ? x[(size_t)r * ldx + k] : 0.f;
+  for (int k = 0; k < 16; ++k) xr[k] = x[(size_t)r * ldx + (k < D ? k : 0)];
+  f32x4 v[VPT], gv[VPT], bv[VPT], w[VPT][16];
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
-    const int c4 = threadIdx.x + i * 256;
-    v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int c4 = threadIdx.x + i * blockDim.x;
+    const int cc = (c4 < n4 ? c4 : 0) * 4;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) w[i][k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * d + cc);
+    v[i] = *(const f32x4*)((b_in ? b_in : xz) + cc);
+    gv[i] = *(const f32x4*)((g ? g : xz) + cc);
+    bv[i] = *(const f32x4*)((b ? b : xz) + cc);
+  }
+  const int Me = eff_rows(M, m_dev);
+  if (r >= Me) return;
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) {
+    const int c4 = threadIdx.x + i * blockDim.x;
+    const int cc = (c4 < n4 ? c4 : 0) * 4;
+    if (id0 >= 0) {
+      v[i] = load4f<T>(cond_table + (size_t)id0 * d + cc);
+    } else {
+      if (b_in == nullptr) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (pos_table) v[i] += load4f<T>(pos_table + (size_t)pos0 * d + cc);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[i] += (k < D) ? w[i][k] * xr[k] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     if (c4 < n4) {
-      if (id >= 0) {
-        v[i] = load4f<T>(cond_table + (size_t)id * d + c4 * 4);
-      } else {
-        // four columns at a time: all 16 weight loads of the group are issued before the first use
-        f32x4 w[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) w[k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * d + c4 * 4);
-        if (b_in) v[i] = ((const f32x4*)b_in)[c4];
-        if (pos_table) v[i] += load4f<T>(pos_table + (size_t)pos * d + c4 * 4);
-#pragma unroll
-        for (int k = 0; k < 16; ++k) v[i] += w[k] * xr[k];
-      }
-      *(f32x4*)(h + (size_t)r * d + c4 * 4) = v[i];
+      *(f32x4*)(h + (size_t)r * d + cc) = v[i];
       s += v[i][0] + v[i][1] + v[i][2] + v[i][3];
     }
   }
-  float mean = 0.f;
-  if (norm_type == 0) mean = block_sum(s, red) / (float)d;
+  auto sum = [&](float t, float* lds) {
+    t = wave_sum(t);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = t;
+    __syncthreads();
+    t = 0.f;
+    for (int i = 0; i < nw; ++i) t += lds[i];
+    return t;
+  };
+  const float mean = norm_type == 0 ? sum(s, red[0]) / (float)d : 0.f;
   float q = 0.f;
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
-    if ((int)threadIdx.x + i * 256 < n4) {
+    if ((int)(threadIdx.x + i * blockDim.x) < n4) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) { const float t = v[i][e] - mean; q += t * t; }
     }
   }
-  const float rstd = 1.0f / sqrtf(block_sum(q, red) / (float)d + eps);
+  const float rstd = 1.0f / sqrtf(sum(q, red[1]) / (float)d + eps);
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
-    const int c4 = threadIdx.x + i * 256;
+    const int c4 = threadIdx.x + i * blockDim.x;
     if (c4 >= n4) continue;
     f32x4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = (v[i][e] - mean) * rstd;
-    if (g) y *= ((const f32x4*)g)[c4];
-    if (b) y += ((const f32x4*)b)[c4];
+    if (g) y *= gv[i];
+    if (b) y += bv[i];
     store4<T>(u + (u_tiled ? tile_offset(r, c4 * 4, d) : (size_t)r * d + c4 * 4), y[0], y[1], y[2], y[3]);
   }
 }
@@ -1338,23 +1276,17 @@ hipError_t launch_embed_norm(hipStream_t s, int is_bf16, const float* x, int ldx
                              int d, int M, const int* m_dev, int norm_type, float eps, const float* g, const float* b, void* u,
                              int u_tiled) {
   if (M <= 0) return hipSuccess;
-  if (d % 4 != 0 || d > 256 * 4 * NORM_VPT || (u_tiled && (!is_bf16 || d % 32 != 0))) return hipErrorInvalidValue;
-#define FARD_EN(VPT)                                                                                                       \
-  do {                                                                                                                     \
-    if (is_bf16)                                                                                                           \
-      embed_norm_kernel<bf16, VPT><<<M, 256, 0, s>>>(x, ldx, D, (const bf16*)w_in, b_in, (const bf16*)pos_table, row_pos,  \
-                                                     (const bf16*)cond_table, cond_id, h, d, M, m_dev, norm_type, eps, g, b, \
-                                                     (bf16*)u, u_tiled);                                                   \
-    else                                                                                                                   \
-      embed_norm_kernel<float, VPT><<<M, 256, 0, s>>>(x, ldx, D, (const float*)w_in, b_in, (const float*)pos_table, row_pos, \
-                                                      (const float*)cond_table, cond_id, h, d, M, m_dev, norm_type, eps, g, b, \
-                                                      (float*)u, 0);                                                       \
-  } while (0)
-  const int n4 = d >> 2;
-  if (n4 <= 256) FARD_EN(1);
-  else if (n4 <= 512) FARD_EN(2);
-  else if (n4 <= 1024) FARD_EN(4);
-  else FARD_EN(8);
+  if (d % 4 != 0 || d > NORM_MAX_D || (u_tiled && (!is_bf16 || d % 32 != 0))) return hipErrorInvalidValue;
+  const int n4 = d >> 2, vpt = n4 <= 512 ? 1 : 2, threads = ((n4 + vpt - 1) / vpt + 63) / 64 * 64;
+#define FARD_EN(TV, VPT)                                                                                                   \
+  embed_norm_kernel<TV, VPT><<<M, threads, 0, s>>>(x, (const TV*)w_in, b_in, ldx, D, d, (const TV*)pos_table, row_pos,      \
+                                                   (const TV*)cond_table, cond_id, h, M, m_dev, norm_type, eps, g, b, (TV*)u, \
+                                                   u_tiled)
+  if (is_bf16) {
+    if (vpt == 1) FARD_EN(bf16, 1); else FARD_EN(bf16, 2);
+  } else {
+    if (vpt == 1) FARD_EN(float, 1); else FARD_EN(float, 2);
+  }
 #undef FARD_EN
   return hipGetLastError();
 }
@@ -1371,19 +1303,33 @@ hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M,
                        const int* in_map, void* out, const float* parts, int n_parts, size_t part_stride, float* h_wb,
                        int out_tiled) {
   if (M <= 0) return hipSuccess;
-  if (d % 4 != 0 || d > 256 * 4 * NORM_VPT || ldm % 4 != 0 || (out_tiled && (!is_bf16 || d % 32 != 0))) return hipErrorInvalidValue;
-#define FARD_NORM(VPT)                                                                                                 \
-  do {                                                                                                                 \
-    if (is_bf16)                                                                                                       \
-      norm_kernel<bf16, VPT><<<M, 256, 0, s>>>(h, d, M, m_dev, norm_type, eps, g, b, shift, scale, ldm, in_map, (bf16*)out, parts, n_parts, part_stride, h_wb, out_tiled);  \
-    else                                                                                                               \
-      norm_kernel<float, VPT><<<M, 256, 0, s>>>(h, d, M, m_dev, norm_type, eps, g, b, shift, scale, ldm, in_map, (float*)out, parts, n_parts, part_stride, h_wb, 0); \
+  if (d % 4 != 0 || d > NORM_MAX_D || ldm % 4 != 0 || (out_tiled && (!is_bf16 || d % 32 != 0))) return hipErrorInvalidValue;
+  const bool mod = scale != nullptr;
+  if (mod && (g != nullptr || b != nullptr || shift == nullptr)) return hipErrorInvalidValue;   // (one or the other: as every caller has it)
+  const float *ga = mod ? scale : g, *be = mod ? shift : b;
+  const int n4 = d >> 2;
+  // up to 512 threads with one piece each, then two
+  const int vpt = n4 <= 512 ? 1 : 2, threads = ((n4 + vpt - 1) / vpt + 63) / 64 * 64;
+  const int rms = norm_type != 0;
+#define FARD_NORM_L(TV, VPT, MODV, NPV)                                                                                        \
+  norm_kernel<TV, VPT, MODV, NPV><<<M, threads, 0, s>>>(h, ga, be, (TV*)out, d, ldm, M, m_dev, in_map, parts, n_parts, part_stride, \
+                                                        h_wb, rms, eps, out_tiled)
+#define FARD_NORM_P(TV, VPT)                                    \
+  do {                                                          \
+    if (mod && n_parts == 0) FARD_NORM_L(TV, VPT, true, 0);     \
+    else if (mod) FARD_NORM_L(TV, VPT, true, -1);               \
+    else if (n_parts == 0) FARD_NORM_L(TV, VPT, false, 0);      \
+    else if (n_parts == 4) FARD_NORM_L(TV, VPT, false, 4);      \
+    else if (n_parts == 5) FARD_NORM_L(TV, VPT, false, 5);      \
+    else FARD_NORM_L(TV, VPT, false, -1);                       \
   } while (0)
-  if (d <= 1024) FARD_NORM(1);
-  else if (d <= 2048) FARD_NORM(2);
-  else if (d <= 4096) FARD_NORM(4);
-  else FARD_NORM(8);
-#undef FARD_NORM
+  if (is_bf16) {
+    if (vpt == 1) FARD_NORM_P(bf16, 1); else FARD_NORM_P(bf16, 2);
+  } else {
+    if (vpt == 1) FARD_NORM_P(float, 1); else FARD_NORM_P(float, 2);
+  }
+#undef FARD_NORM_P
+#undef FARD_NORM_L
   return hipGetLastError();
 }
 
@@ -1480,23 +1426,32 @@ hipError_t launch_head_prep(hipStream_t s, int is_bf16, const float* xsrc, const
                             const void* w_in, const float* b_in, const float* cz, const float* temb, int S, float* hh,
                             void* sc, float* xt_out, int w, int n, const int* n_dev, unsigned* epoch) {
   if (n <= 0) return hipSuccess;
-  dim3 grid((w + 255) / 256, n);
+  if (w % 4 != 0 || D > 16) return hipErrorInvalidValue;
+  dim3 grid((w + 1023) / 1024, n);
   if (is_bf16)
-    head_prep_kernel<bf16><<<grid, 256, 0, s>>>(xsrc, xmap, xscale, D, (const bf16*)w_in, b_in, cz, temb, S, hh,
-                                                (bf16*)sc, xt_out, w, n, n_dev, epoch);
+    head_prep_kernel<bf16><<<grid, 256, 0, s>>>(cz, (const bf16*)w_in, b_in, temb, w, n, D, S, xsrc, xmap, xscale, hh, (bf16*)sc,
+                                                xt_out, n_dev, epoch);
   else
-    head_prep_kernel<float><<<grid, 256, 0, s>>>(xsrc, xmap, xscale, D, (const float*)w_in, b_in, cz, temb, S, hh,
-                                                 (float*)sc, xt_out, w, n, n_dev, epoch);
+    head_prep_kernel<float><<<grid, 256, 0, s>>>(cz, (const float*)w_in, b_in, temb, w, n, D, S, xsrc, xmap, xscale, hh, (float*)sc,
+                                                 xt_out, n_dev, epoch);
   return hipGetLastError();
 }
 
 hipError_t launch_head_out(hipStream_t s, int is_bf16, const HeadStepArgs& a) {
   if (a.n <= 0) return hipSuccess;
-  if (a.D > 16 || a.w % 4 != 0 || a.w > 256 * 4 * HO_VPT || a.ldm % 4 != 0) return hipErrorInvalidValue;
-  if (is_bf16)
-    head_out_kernel<bf16><<<a.n, 256, 0, s>>>(a);
-  else
-    head_out_kernel<float><<<a.n, 256, 0, s>>>(a);
+  if (a.D > 16 || a.w % 4 != 0 || a.w > 2048 || a.ldm % 4 != 0) return hipErrorInvalidValue;
+  const int threads = std::max(256, (a.w / 4 + 63) / 64 * 64);
+#define FARD_HO(TV, D16, LASTV)                                                                                            \
+  head_out_kernel<TV, D16, LASTV><<<a.n, threads, 0, s>>>(a.hh, a.scale, a.shift, a.w, a.ldm, a.D, a.n, (const TV*)a.w_out, \
+                                                          (const TV*)a.w_in, a)
+#define FARD_HO_T(TV)                                                              \
+  do {                                                                             \
+    if (a.D == 16) { if (a.last) FARD_HO(TV, true, true); else FARD_HO(TV, true, false); }    \
+    else { if (a.last) FARD_HO(TV, false, true); else FARD_HO(TV, false, false); } \
+  } while (0)
+  if (is_bf16) FARD_HO_T(bf16); else FARD_HO_T(float);
+#undef FARD_HO_T
+#undef FARD_HO
   return hipGetLastError();
 }
 
