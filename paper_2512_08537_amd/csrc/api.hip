@@ -182,6 +182,7 @@ struct Model {
   void *kc = nullptr, *vc = nullptr;       // [layer][B][Hkv][ctx_pad][dh]
   size_t layer_elems = 0;
   int ctx_pad = 0;
+  float* rope_tab = nullptr;               // bf16 with rotary positions: launch_rope_table over ctx_pad positions
   int *len = nullptr, *len_base = nullptr; // device [max_batch]
   int len_hi = 0;                          // host upper bound of any sample's length
   int written = 0;                         // rows per sample written since len_base was recorded
@@ -558,6 +559,10 @@ int load_model(fard_ctx* c, Loader& ld, int which) {
   const size_t bytes = m.layer_elems * t.n_layers * c->esz;
   if ((rc = dalloc_bytes(c, &m.kc, bytes))) return rc;
   if ((rc = dalloc_bytes(c, &m.vc, bytes))) return rc;
+  if (c->bf16 && t.pos == FARD_POS_ROPE) {
+    if ((rc = dalloc<float>(c, &m.rope_tab, (size_t)m.ctx_pad * t.d_head))) return rc;
+    HIPCHK(c, launch_rope_table(c->stream, m.rope_tab, m.ctx_pad, t.d_head, t.rope_theta));
+  }
   HIPCHK(c, hipMemsetAsync(m.kc, 0, bytes, c->stream));
   HIPCHK(c, hipMemsetAsync(m.vc, 0, bytes, c->stream));
   if ((rc = dalloc<int>(c, &m.len, c->cfg.max_batch))) return rc;
@@ -953,6 +958,13 @@ int flush_parts(fard_ctx* c, int d, int M, const int* m_dev) {
 // The bf16 activations that a narrow-tile GEMM reads (first-norm rows for QKV, attention output for the output
 // projection, second-norm rows and the MLP's hidden rows) are written in tile order (common.h: tile_offset) by their
 // producers; whether a buffer is tiled is a function of the consumer's route, i.e. of the shapes alone.
+// QKV of a few rows with rotary positions: as K-slice planes of the narrow kernel too, which the rotating kernel sums in fp32
+// (one rounding of q, k and v instead of two, and a product of K <= 1024 per workgroup).
+bool qkv_small_planes(const fard_ctx* c, const Model& m, int M) {
+  const int N = m.qkv_n(), K = m.c.d_model;
+  return c->bf16 && c->parts != nullptr && m.c.pos == FARD_POS_ROPE && plane_splits(c, M, N, K) == 0 && M <= 64 &&
+         routes_narrow(M, N, K, EPI_STORE) && (size_t)((K + 1023) / 1024) * M * N <= c->parts_cap;
+}
 bool qkv_reads_tiles(fard_ctx* c, const Model& m, int M) {
   const fard_tf_cfg& t = m.c;
   if (!c->bf16) return false;
@@ -986,14 +998,13 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
     KvGeom kg = kv_geom(c, m, l);
     // learned positions, bf16: the attention kernel stores the new K / V rows itself
     const bool fused_append = c->bf16 && t.pos != FARD_POS_ROPE;
-    if (!fused_append && c->bf16 && plane_splits(c, M, QN, d) > 0) {
+    if (!fused_append && c->bf16 && (plane_splits(c, M, QN, d) > 0 || qkv_small_planes(c, m, M))) {
       // the QKV product as K-slice planes, summed by the kernel that rotates q, k and appends k, v to the cache
       int n_pl = 0;
       size_t pl_stride = 0;
-      HIPCHK(c, gemm_planes(c, c->u, d, L.wqkv, L.bqkv, M, QN, d, m_dev, &n_pl, &pl_stride));
+      HIPCHK(c, gemm_planes(c, c->u, d, L.wqkv, L.bqkv, M, QN, d, m_dev, &n_pl, &pl_stride, u1_tiled));
       Bracket br(c, CLS_OTHER);
-      HIPCHK(c, launch_rope_append_planes(s, c->parts, n_pl, pl_stride, c->qkv, QN, t.n_heads, kg, t.pos == FARD_POS_ROPE,
-                                          t.rope_theta, c->maps.row_sample, c->maps.row_pos, M, m_dev));
+      HIPCHK(c, launch_rope_append_planes(s, c->parts, n_pl, pl_stride, c->qkv, QN, t.n_heads, kg, m.rope_tab, c->maps, M, m_dev));
     } else {
       if (u1_tiled) {
         GemmExtra ex;
@@ -1004,8 +1015,8 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
       }
       if (!fused_append) {
         Bracket br(c, CLS_OTHER);
-        HIPCHK(c, launch_rope_append(s, c->qkv, QN, t.n_heads, kg, t.pos == FARD_POS_ROPE, t.rope_theta, c->maps.row_sample,
-                                     c->maps.row_pos, M, m_dev));
+        HIPCHK(c, launch_rope_append(s, c->qkv, QN, t.n_heads, kg, t.pos == FARD_POS_ROPE, t.rope_theta, m.rope_tab, c->maps, B, nq_max,
+                                     M, m_dev));
       }
     }
     const bool fold2 = c->bf16 && L.w1f != nullptr && gelu && routes_narrow(M, d, HD, EPI_RESID) &&
@@ -1031,7 +1042,7 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
       const int n_pass = (nq_max + acap - 1) / acap;
       if (fused_append) {
         Bracket br(c, CLS_OTHER);
-        HIPCHK(c, launch_rope_append(s, c->qkv, QN, t.n_heads, kg, 0, t.rope_theta, c->maps.row_sample, c->maps.row_pos, M, m_dev));
+        HIPCHK(c, launch_rope_append(s, c->qkv, QN, t.n_heads, kg, 0, t.rope_theta, nullptr, c->maps, B, nq_max, M, m_dev));
       }
       Bracket br(c, CLS_ATTN);
       HIPCHK(c, launch_attention(s, c->qkv, QN, t.n_heads, kg, c->ap_len, c->ap_start, B, acap, c->ao, HD,

@@ -20,6 +20,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace fard {
 
@@ -30,64 +31,132 @@ namespace {
 #endif
 #define ATTN_MIN_WG(DH, NQB) (((DH) == 64 && (NQB) == 1) ? ATTN_OCC : 1)
 
-template <int DH, int NQB>
-__global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(const bf16* __restrict__ qkv, int ld, int n_heads, KvGeom kv,
-                                                        const int* __restrict__ cache_len,
+constexpr float LN2 = 0.6931471805599453f, LOG2E = 1.4426950408889634f;
+// exponents below this are zero and stay finite times zero (a masked score would be -inf)
+constexpr float T_MIN = -16384.f;
+
+// c / nq for column indexes (c < 64)
+__device__ __forceinline__ int col_head(int c, float inv_nq) { return (int)(((float)c + 0.5f) * inv_nq); }
+
+// Short contexts are bound by the launch's chain of dependent reads (lengths -> rows -> keys -> store and re-read of the new
+// rows -> merge; 8 us for 16 workgroups at 129 keys), long ones by the K / V stream.  So the wave's first block is requested
+// before the lengths are there; the new rows (APPEND) go into an LDS image of the tail blocks together with the cached
+// positions around them and from there into both the products and, whole 16-byte pieces, the cache; a block's K is requested
+// again as soon as its scores are out, its V as soon as they are summed.  Running maximum and exponentials are in base 2.
+template <int DH, int NQB, bool APPEND, bool SPLIT, bool ENT>
+__global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(const int* __restrict__ cache_len,
                                                         const int* __restrict__ row_start, const int* __restrict__ row_cnt,
+                                                        const bf16* __restrict__ qkv, void* kcache, void* vcache, int ctx_pad,
+                                                        int Hk, int ld, int n_heads,
                                                         bf16* __restrict__ out, int ldo, float* __restrict__ ent_heads,
-                                                        int append, int pass_stride, AttnSplit sp, int out_tiled) {
+                                                        int pass_stride, AttnSplit sp, int out_tiled) {
   constexpr int DC = DH / 16;      // k16 chunks of the head dim (QK^T)
   constexpr int DB = DH / 32;      // 32-dim row blocks of O^T
   constexpr int NCOL = 32 * NQB;
+  constexpr int PK = 4 * DH;       // 16-byte pieces of a 32-key block
   // merge area: one slab of partial O^T per wave (4 DH (NCOL + 1) floats of dynamic LDS: 17-133 KB), so that the
   // four waves meet behind one barrier; with one shared accumulator and a read-modify-write round per wave the merge was
-  // 5.3 us of a 15.8 us launch at DH = 128 with 64 columns
+  // 5.3 us of a 15.8 us launch at DH = 128 with 64 columns.  Before the merge it holds the tail blocks.
   constexpr int OLD = NCOL + 1;                            // padded row: conflict-free column-major reads
-  __shared__ float s_m[4][NCOL], s_l[4][NCOL], s_a[4][NCOL];
+  __shared__ float s_m[4][NCOL], s_l[4][NCOL], s_a[ENT ? 4 : 1][NCOL];
   extern __shared__ __attribute__((aligned(16))) float s_o[];
 
-  const int Hk = kv.n_kv_heads;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cl = lane & 31, g = lane >> 5;
+  const unsigned b = blockIdx.x / (unsigned)Hk, hk = blockIdx.x - b * (unsigned)Hk;
   const int G = n_heads / Hk;
-  const int b = blockIdx.x / Hk, hk = blockIdx.x - b * Hk;
   // several passes in one launch (blockIdx.y; the longest, i.e. last, pass is dispatched first): the per-sample
   // arrays of pass p start p * pass_stride entries in
-  const int pass_off = ((int)gridDim.y - 1 - (int)blockIdx.y) * pass_stride;
-  cache_len += pass_off;
-  row_start += pass_off;
-  if (row_cnt) row_cnt += pass_off;
-  const int r0 = row_start[b];
-  const int nq = row_cnt ? row_cnt[b] : row_start[b + 1] - r0;     // (row_cnt: a pass over part of the sample's rows)
-  if (nq <= 0) return;
-  const int p0 = cache_len[b];
-  const int ncols = nq * G;                       // column c <-> (query head hk*G + c / nq, row c % nq)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cl = lane & 31, g = lane >> 5;
-  const float scale = rsqrtf((float)DH);
+  const int at = ((int)gridDim.y - 1 - (int)blockIdx.y) * pass_stride + (int)b;
+  const int p0 = cache_len[at], r0 = row_start[at];
+  const int nq = row_cnt ? row_cnt[at] : row_start[at + 1] - r0;   // (row_cnt: a pass over part of the sample's rows)
 
-  // Q^T fragments: lane supplies column cl (+32*qb), dims 16*dc + 8*g .. +7
+  const size_t head_elems = (size_t)ctx_pad * DH;
+  bf16* Kb = (bf16*)kcache + ((size_t)b * Hk + hk) * head_elems;
+  bf16* Vb = (bf16*)vcache + ((size_t)b * Hk + hk) * head_elems;
+  bf16x8 kf[DC], vf[DB][2];
+  auto load_k = [&](int kb) {
+    const bf16x8* p = (const bf16x8*)(Kb + (size_t)kb * 32 * DH);
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) kf[dc] = p[dc * 64 + lane];
+  };
+  auto load_v = [&](int kb) {
+    const bf16x8* p = (const bf16x8*)(Vb + (size_t)kb * 32 * DH);
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) vf[db][hf] = p[(db * 2 + hf) * 64 + lane];
+  };
+  if constexpr (!SPLIT) {
+    const int kb = min(wave, (ctx_pad >> 5) - 1);
+    load_k(kb);
+    load_v(kb);
+  }
+  if (nq <= 0) return;
+  const int ncols = nq * G;                       // column c <-> (query head hk*G + c / nq, row c % nq)
+  const float inv_nq = 1.0f / (float)nq;
+
+  // Q^T fragments: lane supplies column cl (+32*qb), dims 16*dc + 8*g .. +7 (columns past the last repeat the first; they
+  // are computed and not written)
   bf16x8 qf[DC][NQB];
-  int jrow[NQB];
+  int lim[NQB];                                   // last visible position of the column
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
-    const int c = cl + 32 * qb;
-    const bool ok = c < ncols;
-    const int gq = ok ? c / nq : 0;
-    const int j = ok ? c - gq * nq : 0;
-    jrow[qb] = ok ? j : -1;
+    const int c = cl + 32 * qb < ncols ? cl + 32 * qb : 0;
+    const int gq = G == 1 ? 0 : col_head(c, inv_nq);
+    const int j = c - gq * nq;
+    lim[qb] = p0 + j;
     const bf16* qp = qkv + (size_t)(r0 + j) * ld + (size_t)(hk * G + gq) * DH + 8 * g;
 #pragma unroll
-    for (int dc = 0; dc < DC; ++dc) {
-      bf16x8 v;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = (bf16)0.f;
-      if (ok) v = *(const bf16x8*)(qp + 16 * dc);
-      qf[dc][qb] = v;
-    }
+    for (int dc = 0; dc < DC; ++dc) qf[dc][qb] = *(const bf16x8*)(qp + 16 * dc);
   }
 
-  const size_t head_elems = (size_t)kv.ctx_pad * DH;
-  bf16* Kb = (bf16*)kv.k + ((size_t)b * Hk + hk) * head_elems;
-  bf16* Vb = (bf16*)kv.v + ((size_t)b * Hk + hk) * head_elems;
+  const int n_keys = p0 + nq;
+  const int n_blocks = (n_keys + 31) >> 5;
+  // APPEND: blocks [0, p0 / 32) hold only cached positions, visible to every row; the workgroup owns this sample's kv head,
+  // assembles the blocks after them in LDS and stores the new rows' pieces of them to the cache
+  const int tail0 = APPEND ? (p0 >> 5) : n_blocks;
+  if constexpr (APPEND) {
+    const bf16* ksrc = qkv + (size_t)r0 * ld + (size_t)(n_heads + hk) * DH;
+    const bf16* vsrc = ksrc + (size_t)Hk * DH;
+    for (int kb = tail0; kb < n_blocks; ++kb) {
+      bf16x8* lk = (bf16x8*)s_o + (size_t)(kb - tail0) * 2 * PK;
+      bf16x8* kblk = (bf16x8*)(Kb + (size_t)kb * 32 * DH);
+      bf16x8* vblk = (bf16x8*)(Vb + (size_t)kb * 32 * DH);
+#pragma unroll
+      for (int i = 0; i < (PK + 255) / 256; ++i) {
+        const int pc = tid + 256 * i;
+        if (PK % 256 != 0 && pc >= PK) break;
+        const int ln = pc & 63;
+        // K: 8 dims of one key
+        const int jk = kb * 32 + (ln & 31) - p0;
+        const bool newk = (unsigned)jk < (unsigned)nq;
+        const bf16x8* kp = newk ? (const bf16x8*)(ksrc + (size_t)jk * ld + (pc >> 6) * 16 + (ln >> 5) * 8) : kblk + pc;
+        const bf16x8 kv8 = *kp;
+        // V: 8 keys of one dim, in the order of the score accumulators
+        bf16x8 vv = vblk[pc];
+        const int dim = (pc >> 7) * 32 + (ln & 31), key0 = kb * 32 + ((pc >> 6) & 1) * 16 + (ln >> 5) * 4 - p0;
+        bf16 ve[8];
+        bool newv = false;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int j = key0 + ((e >> 2) << 3) + (e & 3);
+          ve[e] = vsrc[(size_t)min(max(j, 0), nq - 1) * ld + dim];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int j = key0 + ((e >> 2) << 3) + (e & 3);
+          const bool in = (unsigned)j < (unsigned)nq;
+          newv = newv || in;
+          vv[e] = in ? ve[e] : vv[e];
+        }
+        lk[pc] = kv8;
+        lk[PK + pc] = vv;
+        if (newk) kblk[pc] = kv8;
+        if (newv) vblk[pc] = vv;
+      }
+    }
+  }
 
   float m_run[NQB], l_run[NQB], a_run[NQB];
   f32x16 o[DB][NQB];
@@ -101,106 +170,103 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[db][qb][e] = 0.f;
   }
-
-  const int n_keys = p0 + nq;
-  const int n_blocks = (n_keys + 31) >> 5;
-  // Blocks that hold only cached positions come first; with `append` the workgroup then stores the new rows'
-  // K and V into the cache (it owns this sample's kv head) and reads the blocks that contain them afterwards.
-  const int tail0 = append ? (p0 >> 5) : n_blocks;
-  for (int phase = 0; phase < 2; ++phase) {
-    if (phase == 1) {
-      if (!append) break;
-      const bf16* ksrc = qkv + (size_t)r0 * ld + (size_t)(n_heads + hk) * DH;
-      const bf16* vsrc = ksrc + (size_t)Hk * DH;
-      constexpr int D8 = DH / 8;
-      for (int idx = tid; idx < nq * D8; idx += 256) {       // K: 8 dims of a key are contiguous in the cache
-        const int j = idx / D8, d8 = idx - j * D8;
-        *(bf16x8*)(Kb + k_offset_bf16(p0 + j, d8 * 8, DH)) = *(const bf16x8*)(ksrc + (size_t)j * ld + d8 * 8);
-      }
-      for (int idx = tid; idx < nq * DH; idx += 256) {       // V: keys are contiguous, dims are not
-        const int j = idx / DH, d = idx - j * DH;
-        Vb[v_offset_bf16(p0 + j, d, DH)] = vsrc[(size_t)j * ld + d];
-      }
-      __threadfence_block();
-      __syncthreads();
-    }
-      int kb_lo = (phase == 0) ? 0 : tail0, kb_hi = (phase == 0) ? tail0 : n_blocks;
-    if (sp.n > 1) {                                        // this workgroup's share of the key blocks (append == 0)
-      kb_lo = (int)(((long)n_blocks * blockIdx.z) / sp.n);
-      kb_hi = (int)(((long)n_blocks * (blockIdx.z + 1)) / sp.n);
-    }
-  for (int kb = kb_lo + wave; kb < kb_hi; kb += 4) {
-    const bf16x8* kblk = (const bf16x8*)(Kb + (size_t)kb * 32 * DH);
-    const bf16x8* vblk = (const bf16x8*)(Vb + (size_t)kb * 32 * DH);
-    bf16x8 kf[DC];
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc) kf[dc] = kblk[dc * 64 + lane];
-    bf16x8 vf[DB][2];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) vf[db][hf] = vblk[(db * 2 + hf) * 64 + lane];
-
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-      f32x16 s;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) s[e] = 0.f;
-#pragma unroll
-      for (int dc = 0; dc < DC; ++dc) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[dc], qf[dc][qb], s, 0, 0, 0);
-      // register e holds key 32*kb + 8*(e/4) + 4*g + e%4 for query column cl
-      const int lim = (jrow[qb] >= 0) ? p0 + jrow[qb] : -1;     // last visible position
-      float bmax = -INFINITY;
+  const float sc2 = rsqrtf((float)DH) * LOG2E;
+  // scores of one block, running triple, probabilities as the next product's operand
+  auto softmax = [&](int kb, int qb, f32x16 s, bf16x8 (&pf)[2], auto masked) {
+    constexpr bool MASK = decltype(masked)::value;
+    // register e holds key 32*kb + 8*(e/4) + 4*g + e%4 for query column cl
+    float bmax = -INFINITY;
+    if constexpr (MASK) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int key = kb * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
-        s[e] = (key <= lim) ? s[e] * scale : -INFINITY;
-        bmax = fmaxf(bmax, s[e]);
+        s[e] = (key <= lim[qb]) ? s[e] : -INFINITY;
       }
-      bmax = xor32_max(bmax);
-      const float m_new = fmaxf(m_run[qb], bmax);
-      float psum = 0.f, asum = 0.f;
-      bf16x8 pf[2];
-      if (m_new == -INFINITY) {
+    }
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
+    for (int e = 0; e < 16; ++e) bmax = fmaxf(bmax, s[e]);
+    bmax = xor32_max(bmax);
+    const float m_new = fmaxf(m_run[qb], bmax * sc2);
+    const float m_ref = MASK ? (m_new == -INFINITY ? 0.f : m_new) : m_new;   // (no visible key so far)
+    float psum = 0.f, asum = 0.f;
 #pragma unroll
-          for (int i = 0; i < 8; ++i) pf[hf][i] = (bf16)0.f;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float t = s[e] - m_new;                       // -inf for masked keys
-          const float p = (s[e] == -INFINITY) ? 0.f : __expf(t);
-          psum += p;
-          asum += (s[e] == -INFINITY) ? 0.f : p * t;
-          pf[e >> 3][e & 7] = (bf16)p;
-        }
-        psum = xor32_sum(psum);
-        asum = xor32_sum(asum);
-        float corr = 1.f;
-        if (m_run[qb] != -INFINITY) {
-          const float dl = m_run[qb] - m_new;
-          corr = __expf(dl);
-          a_run[qb] = corr * (a_run[qb] + dl * l_run[qb]);
-          l_run[qb] = corr * l_run[qb];
-        }
-        a_run[qb] += asum;
-        l_run[qb] += psum;
-        m_run[qb] = m_new;
-        if (corr != 1.f) {
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) o[db][qb][e] *= corr;
-        }
-      }
+    for (int e = 0; e < 16; ++e) {
+      float t = fmaf(s[e], sc2, -m_ref);
+      if constexpr (MASK) t = fmaxf(t, T_MIN);
+      const float p = __builtin_amdgcn_exp2f(t);
+      psum += p;
+      if constexpr (ENT) asum = fmaf(p, t, asum);
+      pf[e >> 3][e & 7] = (bf16)p;
+    }
+    psum = xor32_sum(psum);
+    const float dl = fmaxf(m_run[qb] - m_ref, T_MIN), corr = __builtin_amdgcn_exp2f(dl);
+    if constexpr (ENT) a_run[qb] = fmaf(corr, fmaf(dl, l_run[qb], a_run[qb]), xor32_sum(asum));
+    l_run[qb] = fmaf(corr, l_run[qb], psum);
+    m_run[qb] = m_new;
+    if (__any(corr != 1.f)) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
-          o[db][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][hf], pf[hf], o[db][qb], 0, 0, 0);
+        for (int e = 0; e < 16; ++e) o[db][qb][e] *= corr;
+    }
+  };
+  auto score = [&](int qb) {
+    f32x16 s;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[dc], qf[dc][qb], s, 0, 0, 0);
+    return s;
+  };
+  auto product = [&](int qb, const bf16x8 (&pf)[2]) {
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+        o[db][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][hf], pf[hf], o[db][qb], 0, 0, 0);
+  };
+
+  int kb_lo = 0, kb_hi = tail0;
+  if constexpr (SPLIT) {                                   // this workgroup's share of the key blocks
+    kb_lo = (int)(((unsigned)n_blocks * blockIdx.z) / (unsigned)sp.n);
+    kb_hi = (int)(((unsigned)n_blocks * (blockIdx.z + 1)) / (unsigned)sp.n);
+    if (kb_lo + wave < kb_hi) {
+      load_k(kb_lo + wave);
+      load_v(kb_lo + wave);
     }
   }
+  for (int kb = kb_lo + wave; kb < kb_hi; kb += 4) {
+    const bool more = kb + 4 < kb_hi;
+    const bool whole = APPEND || kb * 32 + 31 <= p0;       // every row sees every key of the block
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      const f32x16 s = score(qb);
+      if (qb == NQB - 1 && more) load_k(kb + 4);
+      bf16x8 pf[2];
+      if (whole) softmax(kb, qb, s, pf, std::false_type{});
+      else softmax(kb, qb, s, pf, std::true_type{});
+      product(qb, pf);
+    }
+    if (more) load_v(kb + 4);
+  }
+  if constexpr (APPEND) {
+    __syncthreads();
+    for (int kb = tail0 + ((wave - tail0) & 3); kb < n_blocks; kb += 4) {
+      const bf16x8* lk = (const bf16x8*)s_o + (size_t)(kb - tail0) * 2 * PK;
+#pragma unroll
+      for (int dc = 0; dc < DC; ++dc) kf[dc] = lk[dc * 64 + lane];
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) vf[db][hf] = lk[PK + (db * 2 + hf) * 64 + lane];
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) {
+        const f32x16 s = score(qb);
+        bf16x8 pf[2];
+        softmax(kb, qb, s, pf, std::integral_constant<bool, true>{});
+        product(qb, pf);
+      }
+    }
   }
 
   // ---- merge the four waves
@@ -209,18 +275,17 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
     for (int qb = 0; qb < NQB; ++qb) {
       s_m[wave][cl + 32 * qb] = m_run[qb];
       s_l[wave][cl + 32 * qb] = l_run[qb];
-      s_a[wave][cl + 32 * qb] = a_run[qb];
+      if constexpr (ENT) s_a[wave][cl + 32 * qb] = a_run[qb];
     }
   }
   __syncthreads();
+  auto top = [&](int c) {                                  // largest reference of the column (0: no visible key at all)
+    const float m = fmaxf(fmaxf(s_m[0][c], s_m[1][c]), fmaxf(s_m[2][c], s_m[3][c]));
+    return m == -INFINITY ? 0.f : m;
+  };
   float f_me[NQB];
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    const int c = cl + 32 * qb;
-    float mstar = -INFINITY;
-    for (int w = 0; w < 4; ++w) mstar = fmaxf(mstar, s_m[w][c]);
-    f_me[qb] = (m_run[qb] == -INFINITY) ? 0.f : __expf(m_run[qb] - mstar);
-  }
+  for (int qb = 0; qb < NQB; ++qb) f_me[qb] = __builtin_amdgcn_exp2f(fmaxf(m_run[qb] - top(cl + 32 * qb), T_MIN));
   // every wave lays its rescaled partial O^T down in its own slab: one barrier, no read-modify-write rounds
   float* slab = s_o + (size_t)wave * DH * OLD;
 #pragma unroll
@@ -238,47 +303,41 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
   for (int idx = tid; idx < NCOL * D8; idx += 256) {
     const int c = idx / D8, d8 = idx - c * D8;
     if (c >= ncols) continue;
-    float mstar = -INFINITY;
-    for (int w = 0; w < 4; ++w) mstar = fmaxf(mstar, s_m[w][c]);
+    const float mstar = top(c);
     float lstar = 0.f, astar = 0.f;
+#pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float mw = s_m[w][c];
-      if (mw == -INFINITY) continue;
-      const float dl = mw - mstar, f = __expf(dl);
-      lstar += f * s_l[w][c];
-      astar += f * (s_a[w][c] + dl * s_l[w][c]);
+      const float dl = fmaxf(s_m[w][c] - mstar, T_MIN), f = __builtin_amdgcn_exp2f(dl);
+      lstar = fmaf(f, s_l[w][c], lstar);
+      if constexpr (ENT) astar = fmaf(f, fmaf(dl, s_l[w][c], s_a[w][c]), astar);
     }
-    const int gq = c / nq, j = c - gq * nq;
+    float acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      acc[i] = s_o[(d8 * 8 + i) * OLD + c];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) acc[i] += s_o[((size_t)w * DH + d8 * 8 + i) * OLD + c];
+    }
+    const int gq = G == 1 ? 0 : col_head(c, inv_nq), j = c - gq * nq;
     const int head = hk * G + gq;
-    if (sp.n > 1) {
+    if constexpr (SPLIT) {
       // keys split over workgroups: this one's running triple and unnormalised O row (relative to its own maximum)
       // go to the planes that attn_merge_kernel folds
       const size_t slot = ((size_t)blockIdx.z * sp.rows + (r0 + j)) * n_heads + head;
-      f32x4 lo, hi;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float acc = s_o[(d8 * 8 + i) * OLD + c];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) acc += s_o[((size_t)w * DH + d8 * 8 + i) * OLD + c];
-        if (i < 4) lo[i] = acc; else hi[i - 4] = acc;
-      }
-      *(f32x4*)(sp.o + slot * DH + d8 * 8) = lo;
-      *(f32x4*)(sp.o + slot * DH + d8 * 8 + 4) = hi;
+      *(f32x4*)(sp.o + slot * DH + d8 * 8) = f32x4{acc[0], acc[1], acc[2], acc[3]};
+      *(f32x4*)(sp.o + slot * DH + d8 * 8 + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
       if (d8 == 0) *(f32x4*)(sp.mla + slot * 4) = f32x4{mstar, lstar, astar, 0.f};
-      continue;
-    }
-    const float inv = 1.0f / lstar;
-    bf16x8 v;
+    } else {
+      const float inv = 1.0f / lstar;
+      bf16x8 v;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float acc = s_o[(d8 * 8 + i) * OLD + c];
-#pragma unroll
-      for (int w = 1; w < 4; ++w) acc += s_o[((size_t)w * DH + d8 * 8 + i) * OLD + c];
-      v[i] = (bf16)(acc * inv);
+      for (int i = 0; i < 8; ++i) v[i] = (bf16)(acc[i] * inv);
+      // (out_tiled: the rows in the tile order the output projection's narrow-tile GEMM reads; 8 dims are one piece)
+      *(bf16x8*)(out + (out_tiled ? tile_offset(r0 + j, head * DH + d8 * 8, ldo) : (size_t)(r0 + j) * ldo + (size_t)head * DH + d8 * 8)) = v;
+      if constexpr (ENT) {
+        if (d8 == 0) ent_heads[(size_t)(r0 + j) * n_heads + head] = logf(lstar) - LN2 * astar * inv;
+      }
     }
-    // (out_tiled: the rows in the tile order the output projection's narrow-tile GEMM reads; 8 dims are one piece)
-    *(bf16x8*)(out + (out_tiled ? tile_offset(r0 + j, head * DH + d8 * 8, ldo) : (size_t)(r0 + j) * ldo + (size_t)head * DH + d8 * 8)) = v;
-    if (ent_heads != nullptr && d8 == 0) ent_heads[(size_t)(r0 + j) * n_heads + head] = logf(lstar) - astar * inv;
   }
 }
 
@@ -303,18 +362,19 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnSplit sp, int n_hea
       lo[s] = *(const f32x4*)(sp.o + slot * dh + d8 * 8);
       hi[s] = *(const f32x4*)(sp.o + slot * dh + d8 * 8 + 4);
     }
+    // (a split that saw no visible key has sum 0 and whatever reference: its maximum does not count)
     float mstar = -INFINITY;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-      if (s < sp.n) mstar = fmaxf(mstar, t[s][0]);
+      if (s < sp.n && t[s][1] > 0.f) mstar = fmaxf(mstar, t[s][0]);
     float lstar = 0.f, astar = 0.f;
     float acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.f;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      if (s >= sp.n || t[s][0] == -INFINITY) continue;     // (a split that saw no visible key)
-      const float dl = t[s][0] - mstar, f = __expf(dl);
+      if (s >= sp.n || !(t[s][1] > 0.f)) continue;
+      const float dl = fmaxf(t[s][0] - mstar, T_MIN), f = __builtin_amdgcn_exp2f(dl);
       lstar += f * t[s][1];
       astar += f * (t[s][2] + dl * t[s][1]);
 #pragma unroll
@@ -326,7 +386,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnSplit sp, int n_hea
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = (bf16)(acc[i] * inv);
     *(bf16x8*)(out + (out_tiled ? tile_offset(row, head * dh + d8 * 8, ldo) : (size_t)row * ldo + (size_t)head * dh + d8 * 8)) = v;
-    if (ent_heads != nullptr && d8 == 0) ent_heads[rh] = logf(lstar) - astar * inv;
+    if (ent_heads != nullptr && d8 == 0) ent_heads[rh] = logf(lstar) - LN2 * astar * inv;
   }
 }
 
@@ -413,21 +473,33 @@ hipError_t launch_attention(hipStream_t s, const void* qkv, int ld, int n_heads,
   const int ps = B;
   const bf16* q = (const bf16*)qkv;
   bf16* o = (bf16*)out;
-  float* eh = sp.n > 1 ? nullptr : ent_heads;              // with split keys the merge writes the entropies
-#define FARD_ATT(DHV, NQBV)                                                                                          \
+  const bool want_a = ent_heads != nullptr;                // (with split keys the merge writes the entropies)
+#define FARD_ATT_L(DHV, NQBV, APPV, SPLV, ENTV)                                                                      \
   do {                                                                                                               \
-    constexpr int lds = 4 * DHV * (32 * NQBV + 1) * 4;     /* the four waves' slabs of partial O^T */                 \
+    constexpr int slabs = 4 * DHV * (32 * NQBV + 1) * 4;   /* the four waves' slabs of partial O^T */                 \
+    constexpr int tails = APPV ? 3 * 8 * DHV * 16 : 0;     /* or up to three tail blocks of K and V */                \
+    constexpr int lds = slabs > tails ? slabs : tails;                                                               \
     if constexpr (lds > 64 * 1024) {                                                                                 \
       static bool attr_set = false;                                                                                  \
       if (!attr_set) {                                                                                               \
-        hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_kernel<DHV, NQBV>,                                 \
+        hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_kernel<DHV, NQBV, APPV, SPLV, ENTV>,               \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);                         \
         if (e != hipSuccess) return e;                                                                               \
         attr_set = true;                                                                                             \
       }                                                                                                              \
     }                                                                                                                \
-    attn_bf16_kernel<DHV, NQBV><<<grid, 256, lds, s>>>(q, ld, n_heads, kv, cache_len, row_start, row_cnt, o, ldo, eh, \
-                                                       append, ps, sp, out_tiled);                                   \
+    attn_bf16_kernel<DHV, NQBV, APPV, SPLV, ENTV><<<grid, 256, lds, s>>>(cache_len, row_start, row_cnt, q, kv.k, kv.v, kv.ctx_pad, \
+                                                                         kv.n_kv_heads, ld, n_heads, o, ldo, ent_heads, ps, sp, out_tiled); \
+  } while (0)
+#define FARD_ATT_M(DHV, NQBV, ENTV)                                 \
+  do {                                                              \
+    if (sp.n > 1) FARD_ATT_L(DHV, NQBV, false, true, ENTV);         \
+    else if (append) FARD_ATT_L(DHV, NQBV, true, false, ENTV);      \
+    else FARD_ATT_L(DHV, NQBV, false, false, ENTV);                 \
+  } while (0)
+#define FARD_ATT(DHV, NQBV)                                                                    \
+  do {                                                                                         \
+    if (want_a) FARD_ATT_M(DHV, NQBV, true); else FARD_ATT_M(DHV, NQBV, false);                \
   } while (0)
   if (kv.d_head == 64) {
     if (cols <= 32) FARD_ATT(64, 1); else FARD_ATT(64, 2);
@@ -439,6 +511,8 @@ hipError_t launch_attention(hipStream_t s, const void* qkv, int ld, int n_heads,
     return hipErrorInvalidValue;
   }
 #undef FARD_ATT
+#undef FARD_ATT_M
+#undef FARD_ATT_L
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || sp.n <= 1) return e;
   const long total = (long)M * n_heads * (kv.d_head / 8);

@@ -77,18 +77,20 @@ __device__ __forceinline__ size_t v_offset_bf16(int pos, int d, int dh) {
   return (size_t)kb * 32 * dh + ((size_t)((db * 2 + hf) * 64 + lane) << 3) + i;
 }
 
+// Rotation angles: tab[pos][0][c] = cos, tab[pos][1][c] = sin of pos theta^(-2 c / dh), c < dh / 2, n_pos dh floats.
+hipError_t launch_rope_table(hipStream_t s, float* tab, int n_pos, int dh, float theta);
 // Splits qkv[M, (H+2Hkv) dh] rows: optional RoPE on q (in place) and k, then stores k, v at
-// position row_pos[r] of sample row_sample[r] in the cache.
+// position row_pos[r] of sample row_sample[r] in the cache.  The rows of a sample are consecutive positions, at most nq_max
+// of them, samples in order (maps.row_start).  bf16 with rope: angles from tab; fp32: from rope_theta.
 hipError_t launch_rope_append(hipStream_t s, void* qkv, int ld, int n_heads, KvGeom kv, int rope,
-                              float rope_theta, const int* row_sample, const int* row_pos, int M,
+                              float rope_theta, const float* tab, const RowMaps& maps, int B, int nq_max, int M,
                               const int* m_dev);
 
 // The same with the rows still in the K-slice planes of the QKV product (fp32 [n_parts][M, ld], plane p at
-// parts + p * part_stride): the planes are summed, q and k rotated in fp32; q goes to qkv as bf16 (the k and v columns of
-// qkv are not written), k and v to the cache.  bf16 caches only.
+// parts + p * part_stride): the planes are summed, q and k rotated in fp32 (tab; nullptr: no rotation); q goes to qkv as bf16
+// (the k and v columns of qkv are not written), k and v to the cache.  bf16 caches only.
 hipError_t launch_rope_append_planes(hipStream_t s, const float* parts, int n_parts, size_t part_stride, void* qkv, int ld,
-                                     int n_heads, KvGeom kv, int rope, float rope_theta, const int* row_sample,
-                                     const int* row_pos, int M, const int* m_dev);
+                                     int n_heads, KvGeom kv, const float* tab, const RowMaps& maps, int M, const int* m_dev);
 
 // Copies plain [B, Hkv, n, dh] tensors (storage type of the context) into the cache at positions 0..n-1.
 hipError_t launch_kv_load(hipStream_t s, KvGeom kv, const void* k, const void* v, int B, int n);

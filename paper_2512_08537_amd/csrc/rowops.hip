@@ -303,8 +303,7 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void norm_kernel(const float
 }
 
 // ================================================================== RoPE + KV append
-template <typename T>
-__global__ __launch_bounds__(256) void rope_append_kernel(T* __restrict__ qkv, int ld, int n_heads, KvGeom kv,
+__global__ __launch_bounds__(256) void rope_append_f32_kernel(float* __restrict__ qkv, int ld, int n_heads, KvGeom kv,
                                                           int rope, float theta, const int* __restrict__ row_sample,
                                                           const int* __restrict__ row_pos, int M, const int* m_dev) {
   const int Me = eff_rows(M, m_dev);
@@ -312,7 +311,7 @@ __global__ __launch_bounds__(256) void rope_append_kernel(T* __restrict__ qkv, i
   if (r >= Me) return;
   const int dh = kv.d_head, Hk = kv.n_kv_heads, half = dh >> 1;
   const int b = row_sample[r], pos = row_pos[r];
-  T* row = qkv + (size_t)r * ld;
+  float* row = qkv + (size_t)r * ld;
   const int n_rot_heads = n_heads + Hk;         // q heads then k heads are rotated
   if (rope) {
     // the angle depends on the row's position and on the pair index c only; a thread whose elements all share one c
@@ -329,74 +328,158 @@ __global__ __launch_bounds__(256) void rope_append_kernel(T* __restrict__ qkv, i
         const float inv = powf(theta, -2.0f * (float)c / (float)dh);
         sincosf((float)pos * inv, &sn, &cs);
       }
-      T* p = row + (size_t)hd * dh;
-      const float a = to_f32(p[c]), bb = to_f32(p[c + half]);
-      p[c] = from_f32<T>(a * cs - bb * sn);
-      p[c + half] = from_f32<T>(bb * cs + a * sn);
+      float* p = row + (size_t)hd * dh;
+      const float a = p[c], bb = p[c + half];
+      p[c] = a * cs - bb * sn;
+      p[c + half] = bb * cs + a * sn;
     }
     __syncthreads();
   }
-  const T* ksrc = row + (size_t)n_heads * dh;
-  const T* vsrc = ksrc + (size_t)Hk * dh;
+  const float* ksrc = row + (size_t)n_heads * dh;
+  const float* vsrc = ksrc + (size_t)Hk * dh;
   const size_t head_elems = (size_t)kv.ctx_pad * dh;
   for (int idx = threadIdx.x; idx < Hk * dh; idx += blockDim.x) {
     const int hk = idx / dh, d = idx - hk * dh;
     const size_t base = ((size_t)b * Hk + hk) * head_elems;
-    size_t ko, vo;
-    if (kv.is_bf16) {
-      ko = k_offset_bf16(pos, d, dh);
-      vo = v_offset_bf16(pos, d, dh);
-    } else {
-      ko = vo = (size_t)pos * dh + d;
+    ((float*)kv.k)[base + (size_t)pos * dh + d] = ksrc[idx];
+    ((float*)kv.v)[base + (size_t)pos * dh + d] = vsrc[idx];
+  }
+}
+
+// Rotation angles of every cache position: tab[pos][0][c] = cos, tab[pos][1][c] = sin of pos theta^(-2 c / d_head),
+// c < d_head / 2.  Made once: the library's sine with its range reduction was most of the instructions of the kernels that
+// rotate (7.9 us for 72 rows, cold).
+__global__ __launch_bounds__(64) void rope_table_kernel(float* __restrict__ tab, int n_pos, int dh, float theta) {
+  const int half = dh >> 1, pos = blockIdx.x;
+  for (int c = threadIdx.x; c < half; c += blockDim.x) {
+    float sn, cs;
+    const float inv = powf(theta, -2.0f * (float)c / (float)dh);
+    sincosf((float)pos * inv, &sn, &cs);
+    tab[(size_t)pos * dh + c] = cs;
+    tab[(size_t)pos * dh + half + c] = sn;
+  }
+}
+
+// The bf16 rows of a forward (qkv [M, ld]) into the cache, q and k rotated in place on the way (tab; nullptr: no rotation).
+// Workgroups [0, n_k) take q and k: a thread has 8 dims of a head, with rotation also their partners half a head on.  The
+// others take V, which the cache keeps as 16-byte pieces of 8 keys of one dim: a workgroup has 16 positions of a sample and
+// 128 dims, a thread one piece, whose 8 rows it reads 2 bytes at a time (neighbouring threads neighbouring dims).  Bound by
+// memory; V element by element cost partial writes of 2 bytes each: 3366 rows of 1024 took 16.4 us, 6144 rows of 7168 with
+// rotation 58 us.
+__global__ __launch_bounds__(256) void rope_append_bf16_kernel(bf16* __restrict__ qkv, int ld, int n_heads, KvGeom kv,
+                                                               const float* __restrict__ tab, const int* __restrict__ row_sample,
+                                                               const int* __restrict__ row_pos, const int* __restrict__ row_start,
+                                                               int M, const int* m_dev, int n_k, int chunks, int slabs) {
+  const int Me = eff_rows(M, m_dev);
+  const int dh = kv.d_head, Hk = kv.n_kv_heads, half = dh >> 1;
+  const size_t head_elems = (size_t)kv.ctx_pad * dh;
+  if ((int)blockIdx.x < n_k) {
+    const int per_head = tab ? half >> 3 : dh >> 3, heads = tab ? n_heads + Hk : Hk;
+    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+    const int per_row = per_head * heads;
+    const int r = (int)(idx / per_row);
+    if (r >= Me) return;
+    const int i = (int)(idx - (long)r * per_row);
+    const int hd = i / per_head, d = (i - hd * per_head) * 8;
+    bf16* src = qkv + (size_t)r * ld + (size_t)(tab ? hd : n_heads + hd) * dh + d;
+    const int hk = tab ? hd - n_heads : hd;                // kv head, < 0: a query head
+    bf16x8 lo = *(const bf16x8*)src, hi;
+    const int pos = row_pos[r], b = row_sample[r];
+    if (tab) {
+      hi = *(const bf16x8*)(src + half);
+      const float* t = tab + (size_t)pos * dh + d;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float cs = t[e], sn = t[half + e];
+        const float x = (float)lo[e], y = (float)hi[e];
+        lo[e] = (bf16)(x * cs - y * sn);
+        hi[e] = (bf16)(y * cs + x * sn);
+      }
+      if (hk < 0) {
+        *(bf16x8*)src = lo;
+        *(bf16x8*)(src + half) = hi;
+        return;
+      }
     }
-    ((T*)kv.k)[base + ko] = ksrc[idx];
-    ((T*)kv.v)[base + vo] = vsrc[idx];
+    bf16* kc = (bf16*)kv.k + ((size_t)b * Hk + hk) * head_elems;
+    *(bf16x8*)(kc + k_offset_bf16(pos, d, dh)) = lo;
+    if (tab) *(bf16x8*)(kc + k_offset_bf16(pos, d + half, dh)) = hi;
+    return;
+  }
+  const int v = blockIdx.x - n_k;
+  const int b = v / (chunks * slabs), cs = v - b * chunks * slabs, ch = cs / slabs, slab = cs - ch * slabs;
+  const int r0 = min(row_start[b], Me), nq = min(row_start[b + 1], Me) - r0;
+  if (nq <= 0) return;
+  const int pos0 = row_pos[r0];                            // the sample's rows are consecutive positions
+  const int p16 = ((pos0 >> 4) + ch) * 16;
+  if (p16 >= pos0 + nq) return;
+  const int dim = slab * 128 + (threadIdx.x & 127), g = threadIdx.x >> 7;
+  if (dim >= Hk * dh) return;
+  const int hk = dim / dh, d = dim - hk * dh;
+  const bf16* src = qkv + (size_t)r0 * ld + (size_t)(n_heads + Hk) * dh + dim;
+  bf16x8 piece;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int j = p16 + ((e >> 2) << 3) + 4 * g + (e & 3) - pos0;
+    piece[e] = src[(size_t)min(max(j, 0), nq - 1) * ld];
+  }
+  bf16* dst = (bf16*)kv.v + ((size_t)b * Hk + hk) * head_elems + v_offset_bf16(p16 + 4 * g, d, dh);
+  const int j0 = p16 + 4 * g - pos0;                       // keys j0 .. j0 + 3 and j0 + 8 .. j0 + 11
+  if (j0 >= 0 && j0 + 11 < nq) {
+    *(bf16x8*)dst = piece;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int j = j0 + ((e >> 2) << 3) + (e & 3);
+      if ((unsigned)j < (unsigned)nq) dst[e] = piece[e];
+    }
   }
 }
 
 // The same from the K-slice planes of the QKV product (fp32 [n_parts][M, ld], bias in plane 0): sums the planes, rotates
 // q and k in fp32, writes q as bf16 into qkv (what the attention kernel reads) and k, v into the cache.
 // Grid (rows, head groups): a thread owns 4 consecutive dims c .. c+3 of the first half of one head and their partners
-// c + d_head/2 ..; all its loads (2 x 16 bytes per plane, PMAX planes at most per batch) are requested before the first sum.
-template <int PMAX>
-__global__ __launch_bounds__(256) void rope_append_planes_kernel(const float* __restrict__ parts, int n_parts, size_t part_stride,
-                                                                 bf16* __restrict__ qkv, int ld, int n_heads, KvGeom kv, int rope,
-                                                                 float theta, const int* __restrict__ row_sample,
-                                                                 const int* __restrict__ row_pos, int M, const int* m_dev) {
-  const int Me = eff_rows(M, m_dev);
+// c + d_head/2 ..; all its loads (2 x 16 bytes per plane) are requested before the first sum.  NP: planes, -1: n_parts.
+template <int NP>
+__global__ __launch_bounds__(256) void rope_append_planes_kernel(const float* __restrict__ parts, const float* __restrict__ tab,
+                                                                 bf16* __restrict__ qkv, int n_parts, int ld, int n_heads, int M,
+                                                                 size_t part_stride, KvGeom kv, const int* __restrict__ row_sample,
+                                                                 const int* __restrict__ row_pos, const int* m_dev) {
   const int r = blockIdx.x;
-  if (r >= Me) return;
   const int dh = kv.d_head, Hk = kv.n_kv_heads, half = dh >> 1;
   const int tph = half >> 2;                               // threads per head
   const int hpw = 256 / tph;                               // heads per workgroup
   const int hd = blockIdx.y * hpw + threadIdx.x / tph;     // q heads, then k heads, then v heads
   if (hd >= n_heads + 2 * Hk) return;
   const int c = (threadIdx.x % tph) * 4;
-  const int b = row_sample[r], pos = row_pos[r];
   const float* p0 = parts + (size_t)r * ld + (size_t)hd * dh + c;
   f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-  for (int pb = 0; pb < n_parts; pb += PMAX) {
-    f32x4 tl[PMAX], th[PMAX];
+  if constexpr (NP > 0) {
+    f32x4 tl[NP], th[NP];
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p) {
-      const int pp = pb + p < n_parts ? pb + p : pb;       // (a re-read that is not added)
-      tl[p] = *(const f32x4*)(p0 + (size_t)pp * part_stride);
-      th[p] = *(const f32x4*)(p0 + (size_t)pp * part_stride + half);
+    for (int p = 0; p < NP; ++p) {
+      tl[p] = *(const f32x4*)(p0 + (size_t)p * part_stride);
+      th[p] = *(const f32x4*)(p0 + (size_t)p * part_stride + half);
     }
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p)
-      if (pb + p < n_parts) { lo += tl[p]; hi += th[p]; }
+    for (int p = 0; p < NP; ++p) { lo += tl[p]; hi += th[p]; }
+  } else {
+    for (int p = 0; p < n_parts; ++p) {
+      lo += *(const f32x4*)(p0 + (size_t)p * part_stride);
+      hi += *(const f32x4*)(p0 + (size_t)p * part_stride + half);
+    }
   }
+  const int Me = eff_rows(M, m_dev);
+  if (r >= Me) return;
+  const int b = row_sample[r], pos = row_pos[r];
   const bool is_v = hd >= n_heads + Hk;
-  if (rope && !is_v) {
+  if (tab != nullptr && !is_v) {
+    const f32x4 cs = *(const f32x4*)(tab + (size_t)pos * dh + c), sn = *(const f32x4*)(tab + (size_t)pos * dh + half + c);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float sn, cs;
-      const float inv = powf(theta, -2.0f * (float)(c + e) / (float)dh);
-      sincosf((float)pos * inv, &sn, &cs);
       const float a = lo[e], bb = hi[e];
-      lo[e] = a * cs - bb * sn;
-      hi[e] = bb * cs + a * sn;
+      lo[e] = a * cs[e] - bb * sn[e];
+      hi[e] = bb * cs[e] + a * sn[e];
     }
   }
   bf16x4 blo, bhi;
@@ -1333,19 +1416,33 @@ hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M,
   return hipGetLastError();
 }
 
-hipError_t launch_rope_append(hipStream_t s, void* qkv, int ld, int n_heads, KvGeom kv, int rope, float rope_theta,
-                              const int* row_sample, const int* row_pos, int M, const int* m_dev) {
+hipError_t launch_rope_table(hipStream_t s, float* tab, int n_pos, int dh, float theta) {
+  if (n_pos <= 0) return hipSuccess;
+  rope_table_kernel<<<n_pos, 64, 0, s>>>(tab, n_pos, dh, theta);
+  return hipGetLastError();
+}
+
+hipError_t launch_rope_append(hipStream_t s, void* qkv, int ld, int n_heads, KvGeom kv, int rope, float rope_theta, const float* tab,
+                              const RowMaps& maps, int B, int nq_max, int M, const int* m_dev) {
   if (M <= 0) return hipSuccess;
-  if (kv.is_bf16)
-    rope_append_kernel<bf16><<<M, 256, 0, s>>>((bf16*)qkv, ld, n_heads, kv, rope, rope_theta, row_sample, row_pos, M, m_dev);
-  else
-    rope_append_kernel<float><<<M, 256, 0, s>>>((float*)qkv, ld, n_heads, kv, rope, rope_theta, row_sample, row_pos, M, m_dev);
+  if (!kv.is_bf16) {
+    rope_append_f32_kernel<<<M, 256, 0, s>>>((float*)qkv, ld, n_heads, kv, rope, rope_theta, maps.row_sample, maps.row_pos, M, m_dev);
+    return hipGetLastError();
+  }
+  const int dh = kv.d_head, Hk = kv.n_kv_heads;
+  if ((rope && tab == nullptr) || dh % 16 != 0 || ld % 8 != 0 || (((uintptr_t)qkv) & 15) != 0 || B < 1 || nq_max < 1) return hipErrorInvalidValue;
+  const long per_row = rope ? (long)(n_heads + Hk) * (dh / 16) : (long)Hk * (dh / 8);
+  const long n_k = ((long)M * per_row + 255) / 256;
+  const int chunks = nq_max / 16 + 2, slabs = (Hk * dh + 127) / 128;   // (a run of nq positions touches at most nq / 16 + 2 groups of 16)
+  const long total = n_k + (long)B * chunks * slabs;
+  if (total >= (1L << 31)) return hipErrorInvalidValue;
+  rope_append_bf16_kernel<<<(unsigned)total, 256, 0, s>>>((bf16*)qkv, ld, n_heads, kv, rope ? tab : nullptr, maps.row_sample,
+                                                          maps.row_pos, maps.row_start, M, m_dev, (int)n_k, chunks, slabs);
   return hipGetLastError();
 }
 
 hipError_t launch_rope_append_planes(hipStream_t s, const float* parts, int n_parts, size_t part_stride, void* qkv, int ld,
-                                     int n_heads, KvGeom kv, int rope, float rope_theta, const int* row_sample,
-                                     const int* row_pos, int M, const int* m_dev) {
+                                     int n_heads, KvGeom kv, const float* tab, const RowMaps& maps, int M, const int* m_dev) {
   if (M <= 0) return hipSuccess;
   const int dh = kv.d_head;
   // a head's first half in groups of 4 dims; 16-byte loads of the planes, 8-byte stores of q and k
@@ -1354,8 +1451,14 @@ hipError_t launch_rope_append_planes(hipStream_t s, const float* parts, int n_pa
     return hipErrorInvalidValue;
   const int hpw = 256 / (dh / 8);
   const dim3 grid(M, (n_heads + 2 * kv.n_kv_heads + hpw - 1) / hpw);
-  rope_append_planes_kernel<8><<<grid, 256, 0, s>>>(parts, n_parts, part_stride, (bf16*)qkv, ld, n_heads, kv, rope, rope_theta,
-                                                    row_sample, row_pos, M, m_dev);
+#define FARD_RP(NPV)                                                                                                            \
+  rope_append_planes_kernel<NPV><<<grid, 256, 0, s>>>(parts, tab, (bf16*)qkv, n_parts, ld, n_heads, M, part_stride, kv, maps.row_sample, \
+                                                      maps.row_pos, m_dev)
+  if (n_parts == 2) FARD_RP(2);
+  else if (n_parts == 4) FARD_RP(4);
+  else if (n_parts == 5) FARD_RP(5);
+  else FARD_RP(-1);
+#undef FARD_RP
   return hipGetLastError();
 }
 
