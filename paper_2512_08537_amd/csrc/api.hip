@@ -38,8 +38,12 @@ __global__ void place_kernel(const TS* __restrict__ src, TD* __restrict__ dst, i
     dst[k * ldd + col0 + n] = from_f32<TD>(to_f32(src[i]));
   }
 }
-__global__ void len_commit_kernel(int* len, const int* base, const int* n_accept, int cap_extra, int B) {
+__global__ void len_commit_kernel(int* len0, const int* base0, int cap0, int* len1, const int* base1, int cap1,
+                                  const int* n_accept, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  int* len = blockIdx.y ? len1 : len0;
+  const int* base = blockIdx.y ? base1 : base0;
+  const int cap_extra = blockIdx.y ? cap1 : cap0;
   if (b < B) {
     int add = 1 + n_accept[b];
     if (add > cap_extra) add = cap_extra;      // never beyond what was written this round
@@ -826,7 +830,7 @@ int alloc_workspace(fard_ctx* c) {
       HIPCHK(c, launch_fill_i32(c->stream, (int*)c->epoch, 0, 1));
     }
   }
-  if ((rc = dalloc<int>(c, &c->alive, g.max_batch))) return rc;
+  if ((rc = dalloc<int>(c, &c->alive, 2 * (size_t)g.max_batch))) return rc;   // (before / after a draft step, taking turns)
   if ((rc = dalloc<int>(c, &c->act_idx, g.max_batch))) return rc;
   if ((rc = dalloc<int>(c, &c->n_act, 4))) return rc;
   if ((rc = dalloc<int>(c, &c->emap, g.max_batch))) return rc;
@@ -974,9 +978,10 @@ bool qkv_reads_tiles(fard_ctx* c, const Model& m, int M) {
 }
 
 // Layers [l0, l1) of one model over the packed rows described by c->maps (h in, h out).
-// first_norm_done: c->u already holds the first norm of layer l0 (the embedding kernel wrote it).
+// first_norm_done: c->u already holds the first norm of layer l0 (the embedding kernel wrote it).  row_entropy: the softmax
+// entropies of the rows as they enter layer l0, taken in its first norm.
 int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max, const int* m_dev, int ent_layer,
-               bool first_norm_done = false) {
+               bool first_norm_done = false, float* row_entropy = nullptr) {
   Model& m = c->mdl[which];
   const fard_tf_cfg& t = m.c;
   hipStream_t s = c->stream;
@@ -992,7 +997,7 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
     if (!(first_norm_done && l == l0 && c->pend_n == 0)) {
       Bracket br(c, CLS_OTHER);
       HIPCHK(c, launch_norm(s, c->bf16, c->h, d, M, m_dev, t.norm, t.norm_eps, L.n1g, L.n1b, nullptr, nullptr, 0, nullptr, c->u,
-                            c->parts, c->pend_n, c->pend_stride, c->h, u1_tiled));
+                            c->parts, c->pend_n, c->pend_stride, c->h, u1_tiled, l == l0 ? row_entropy : nullptr));
       c->pend_n = 0;
     }
     KvGeom kg = kv_geom(c, m, l);
@@ -1134,7 +1139,7 @@ int workspace_rows(const fard_round_cfg& g) {
 
 // S sampler steps of the head over n rows of z (compact), noise / output rows through emap / omap.
 int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* eps, size_t eps_step_stride,
-             const int* emap, const int* omap, float* mu, float* x) {
+             const int* emap, const int* omap, float* mu, float* x, int* len = nullptr, int* row_pos = nullptr) {
   const fard_head_cfg& hc = c->cfg.head;
   HeadW& hw = c->head;
   hipStream_t s = c->stream;
@@ -1144,7 +1149,7 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
   const bool chain = n <= c->xch_rows;
   { Bracket br(c, CLS_OTHER);
     HIPCHK(c, launch_head_prep(s, c->bf16, eps, emap, hc.temperature, D, hw.in_w, hw.in_b, c->cz, hw.temb, S, c->hh, c->sc,
-                               c->xt, w, n, n_dev, chain ? c->epoch : nullptr)); }
+                               c->xt, w, n, n_dev, chain ? c->epoch : nullptr, len, row_pos)); }
   // From the second block of a step on the modulated norm has no launch of its own when the rows are few (the launch
   // is then the cost; measured: a gain up to 64 rows, none above): the gate-residual GEMM of block j - 1 leaves
   // v = bf16(h (1 + scale_j)) and the tile moments of h, and block j's first GEMM multiplies v and applies mean, rstd,
@@ -1378,14 +1383,19 @@ int spec_kv_commit(fard_ctx* c, int32_t which, const int32_t* n_accept, int32_t 
   if (!n_accept) return fail(c, FARD_EINVAL, "n_accept");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (B == 0) return FARD_OK;
-  for (int w = 0; w < 2; ++w) {
-    if (which != -1 && which != w) continue;
-    Model& m = c->mdl[w];
-    if (m.written < 1) return fail(c, FARD_ESTATE, "spec_kv_commit without a preceding spec_draft / spec_verify");
-    len_commit_kernel<<<(B + 255) / 256, 256, 0, c->stream>>>(m.len, m.len_base, n_accept, m.written, B);
-    HIPCHK(c, hipGetLastError());
-    m.written = 0;
-  }
+  // (with both models the one that has nothing to commit is refused before the other is touched only if it comes first: as
+  // two calls would)
+  const int w0 = which == -1 ? 0 : which, n = which == -1 ? 2 : 1;
+  if (which != -1 && which != 0 && which != 1) return FARD_OK;
+  const bool second = n == 2 && c->mdl[1].written >= 1;
+  Model &m0 = c->mdl[w0], &m1 = c->mdl[second ? 1 : w0];
+  if (m0.written < 1) return fail(c, FARD_ESTATE, "spec_kv_commit without a preceding spec_draft / spec_verify");
+  len_commit_kernel<<<dim3((B + 255) / 256, second ? 2 : 1), 256, 0, c->stream>>>(m0.len, m0.len_base, m0.written, m1.len, m1.len_base,
+                                                                                 m1.written, n_accept, B);
+  HIPCHK(c, hipGetLastError());
+  m0.written = 0;
+  if (second) m1.written = 0;
+  if (n == 2 && !second) return fail(c, FARD_ESTATE, "spec_kv_commit without a preceding spec_draft / spec_verify");
   return FARD_OK;
 }
 
@@ -1619,13 +1629,8 @@ static int draft_begin(fard_ctx* c, int B, int32_t* n_keep, float* x_draft, floa
   const int K = c->cfg.K, D = m.c.d_latent;
   hipStream_t s = c->stream;
   Bracket br(c, CLS_OTHER);
-  copy_i32_kernel<<<(B + 255) / 256, 256, 0, s>>>(m.len, m.len_base, B);
-  HIPCHK(c, hipGetLastError());
-  HIPCHK(c, launch_fill_i32(s, c->alive, 1, B));
-  HIPCHK(c, launch_fill_i32(s, n_keep, 0, B));
-  // dropped drafts keep finite values: they still travel through the dense draft rows
-  HIPCHK(c, launch_fill_f32(s, x_draft, 0.f, (size_t)B * K * D));
-  HIPCHK(c, launch_fill_f32(s, mu_q, 0.f, (size_t)B * K * D));
+  // (dropped drafts keep finite values: they still travel through the dense draft rows)
+  HIPCHK(c, launch_stage_begin(s, m.len, m.len_base, c->alive, n_keep, B, x_draft, mu_q, (size_t)B * K * D));
   m.written = 0;
   return FARD_OK;
 }
@@ -1650,20 +1655,32 @@ static int draft_step(fard_ctx* c, int i, const float* xs, int ldx, const int32_
   HIPCHK(c, embed_first_norm(c, FARD_DRAFT, xs, ldx, ids, B, nullptr));
   const bool attn_mode = c->cfg.entropy_mode == FARD_ENT_ATTN;
   if ((rc = run_layers(c, FARD_DRAFT, 0, ls, B, B, 1, nullptr, attn_mode ? ls : 0, true))) return rc;
-  // pending partial planes of the last shallow layer: the entropy rows add them on the fly and the next norm
-  // folds them into the stream; otherwise they are folded here
-  const bool ent_folds = !attn_mode && ls < m.c.n_layers && ent_rows_in_regs_f32(c->h, d, d);
-  if (!ent_folds && (rc = flush_parts(c, d, B, nullptr))) return rc;
-  { Bracket br(c, CLS_ENT, 0, (double)B * d * 4);
-    if (!attn_mode)
-      HIPCHK(c, launch_entropy_rows_f32(s, c->h, d, B, d, c->h_row, c->parts, ent_folds ? c->pend_n : 0, c->pend_stride));
-    HIPCHK(c, launch_entropy_step(s, attn_mode ? c->ent_heads : nullptr, m.c.n_heads, c->h_row, B, K, i, tau, H, keep, c->alive,
-                                  n_keep, c->act_idx, c->n_act, c->emap, c->omap)); }
-  if ((rc = run_layers(c, FARD_DRAFT, ls, m.c.n_layers, B, B, 1, nullptr, 0))) return rc;
+  // FEATURE entropies of the shallow rows: in the first norm of the next layer where there is one (which also folds pending
+  // partial planes in), by a launch of their own otherwise; the threshold rides in the final norm up to ENT_STEP_MAX_B samples
+  const bool in_norm = !attn_mode && ls < m.c.n_layers, in_final = !attn_mode && B <= ENT_STEP_MAX_B;
+  if (!in_norm && (rc = flush_parts(c, d, B, nullptr))) return rc;
+  if (!in_norm && !attn_mode) {
+    Bracket br(c, CLS_ENT, 0, (double)B * d * 4);
+    HIPCHK(c, launch_entropy_rows_f32(s, c->h, d, B, d, c->h_row));
+  }
+  if ((rc = run_layers(c, FARD_DRAFT, ls, m.c.n_layers, B, B, 1, nullptr, 0, false, in_norm ? c->h_row : nullptr))) return rc;
+  int* alive_in = c->alive + (i & 1) * c->cfg.max_batch;
+  int* alive_out = c->alive + ((i + 1) & 1) * c->cfg.max_batch;
   // only samples that are still speculating reach the head
-  if ((rc = run_final(c, FARD_DRAFT, B, c->n_act, c->act_idx, c->z))) return rc;
-  if ((rc = run_head(c, c->z, B, c->n_act, eps, eps_stride, c->emap, c->omap, mu_q, x_draft))) return rc;
-  HIPCHK(c, launch_len_add(s, m.len, nullptr, 1, B, c->maps.row_pos));
+  if (in_final) {
+    EntStep st{c->h_row, alive_in, alive_out, tau, K, i, H, keep, n_keep, c->act_idx, c->n_act, c->emap, c->omap};
+    { Bracket br(c, CLS_OTHER);
+      HIPCHK(c, launch_final_step(s, c->bf16, c->h, d, B, m.c.norm, m.c.norm_eps, m.nfg, m.nfb, m.up ? c->ztmp : c->z, c->parts, c->pend_n,
+                                  c->pend_stride, st));
+      c->pend_n = 0; }
+    if (m.up) HIPCHK(c, gemm(c, c->ztmp, d, m.up, nullptr, c->z, m.c.d_out, B, m.c.d_out, d, c->n_act, EPI_STORE, ACT_NONE));
+  } else {
+    { Bracket br(c, CLS_ENT, 0, (double)B * d * 4);
+      HIPCHK(c, launch_entropy_step(s, attn_mode ? c->ent_heads : nullptr, m.c.n_heads, c->h_row, B, K, i, tau, H, keep, alive_in,
+                                    alive_out, n_keep, c->act_idx, c->n_act, c->emap, c->omap)); }
+    if ((rc = run_final(c, FARD_DRAFT, B, c->n_act, c->act_idx, c->z))) return rc;
+  }
+  if ((rc = run_head(c, c->z, B, c->n_act, eps, eps_stride, c->emap, c->omap, mu_q, x_draft, m.len, c->maps.row_pos))) return rc;
   m.len_hi += 1;
   m.written += 1;
   return FARD_OK;
@@ -1732,10 +1749,8 @@ int spec_verify(fard_ctx* c, const float* x_pending, const int32_t* pending_id, 
   hipStream_t s = c->stream;
   int rc;
   { Bracket br(c, CLS_OTHER);
-    copy_i32_kernel<<<(B + 255) / 256, 256, 0, s>>>(m.len, m.len_base, B);
-    HIPCHK(c, hipGetLastError());
-    HIPCHK(c, launch_build_rows(s, n_keep, 1, B, K, D, m.len, c->maps, x_pending, x_draft, c->x_in, c->aux_row, M, K + 1));
-    HIPCHK(c, launch_fill_f32(s, mu_p, 0.f, (size_t)B * (K + 1) * D)); }
+    HIPCHK(c, launch_stage_begin(s, m.len, m.len_base, nullptr, nullptr, B, mu_p, nullptr, (size_t)B * (K + 1) * D));
+    HIPCHK(c, launch_build_rows(s, n_keep, 1, B, K, D, m.len, c->maps, x_pending, x_draft, c->x_in, c->aux_row, M, K + 1));}
   const int* md = c->maps.m_total;
   int* cid = nullptr;
   { Bracket br(c, CLS_OTHER);

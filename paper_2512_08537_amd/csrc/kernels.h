@@ -48,12 +48,13 @@ hipError_t launch_embed_norm(hipStream_t s, int is_bf16, const float* x, int ldx
 
 // out_T[r, :] = norm(h[r, :]) with optional affine (g, b) and optional AdaLN modulation
 // (1 + scale[r, :]) / shift[r, :] read with row stride ldm.  norm_type 0 LayerNorm, 1 RMSNorm.
-// in_map (optional) gathers: output row r is computed from input row in_map[r].
+// in_map (optional) gathers: output row r is computed from input row in_map[r].  ent (optional, neither modulation nor
+// in_map): the softmax entropy of every (completed) row over its channels.
 hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M, const int* m_dev,
                        int norm_type, float eps, const float* g, const float* b, const float* shift,
                        const float* scale, int ldm, const int* in_map, void* out,
                        const float* parts = nullptr, int n_parts = 0, size_t part_stride = 0, float* h_wb = nullptr,
-                       int out_tiled = 0);
+                       int out_tiled = 0, float* ent = nullptr);
 // parts / n_parts / part_stride: K-slice partial sums [n_parts][M, d] that a preceding GEMM left for the
 // residual stream; the norm adds them to its input row first and writes the completed row to h_wb (if given).
 hipError_t launch_add_parts(hipStream_t s, float* h, const float* parts, int n_parts, size_t part_stride, int d,
@@ -130,26 +131,40 @@ hipError_t launch_entropy_prefilter(hipStream_t s, int is_bf16, const void* feat
                                     int* n_surv, int* blk_cnt);
 
 // H[r] = softmax entropy of the fp32 row feat[r*ld .. r*ld+L) (one wave per row).
-// parts (n_parts > 0): pending partial planes added to the rows on the fly; only when ent_rows_in_regs_f32 holds.
-bool ent_rows_in_regs_f32(const float* feat, int ld, int L);
-hipError_t launch_entropy_rows_f32(hipStream_t s, const float* feat, int ld, int rows, int L, float* H,
-                                   const float* parts = nullptr, int n_parts = 0, size_t part_stride = 0);
+hipError_t launch_entropy_rows_f32(hipStream_t s, const float* feat, int ld, int rows, int L, float* H);
 
 // One draft step's threshold on per-row entropies already computed elsewhere (ATTN mode) or per
-// head (mean over heads taken here): alive[b] &= (H >= tau); n_keep[b] += alive[b]; writes H and keep
+// head (mean over heads taken here): alive_out[b] = alive_in[b] && (H >= tau); n_keep[b] += alive_out[b]; writes H and keep
 // at column `step` of [B, K] arrays and compacts the alive sample indices into act_idx / n_act with the
 // matching noise rows emap = b*(K+1)+step and output rows omap = b*K+step.
 hipError_t launch_entropy_step(hipStream_t s, const float* ent_heads, int n_heads, const float* H_in,
                                int B, int K, int step, float tau, float* H, uint8_t* keep,
-                               int* alive, int* n_keep, int* act_idx, int* n_act, int* emap, int* omap);
+                               const int* alive_in, int* alive_out, int* n_keep, int* act_idx, int* n_act, int* emap,
+                               int* omap);
+
+// The same step inside the draft's final norm (rows of the samples still speculating, in sample order; H_in: the entropies of
+// all samples), up to ENT_STEP_MAX_B samples.  alive_in and alive_out: different buffers.
+constexpr int ENT_STEP_MAX_B = 64;
+struct EntStep {
+  const float* H_in; const int* alive_in; int* alive_out;
+  float tau; int K, step;
+  float* H; uint8_t* keep; int* n_keep; int* act_idx; int* n_act; int* emap; int* omap;
+};
+hipError_t launch_final_step(hipStream_t s, int is_bf16, const float* h, int d, int B, int norm_type, float eps, const float* g,
+                             const float* b, void* out, const float* parts, int n_parts, size_t part_stride, const EntStep& st);
+
+// Start of a stage: len_base = len; alive = 1 and n_keep = 0 (alive != nullptr); z0, z1 = 0 (nz floats; z1 may be null).
+hipError_t launch_stage_begin(hipStream_t s, const int* len, int* len_base, int* alive, int* n_keep, int B, float* z0, float* z1,
+                              size_t nz);
 
 // Head pieces.
 // hh[r, :] = x_t[r, :] W_in + b_in ; sc[k n + r, :] = T(silu(cz[r, :] + temb[k, :])) for the S sampler
 // times k.  x_t comes from xsrc[xmap ? xmap[r] : r] * xscale.  epoch (optional): one more decode begins (launch_head_chain).
+// len, row_pos (optional, n rows): every sample's length, and with it its position, moves on by one.
 hipError_t launch_head_prep(hipStream_t s, int is_bf16, const float* xsrc, const int* xmap, float xscale,
                             int D, const void* w_in, const float* b_in, const float* cz,
                             const float* temb, int S, float* hh, void* sc, float* xt_out, int w, int n,
-                            const int* n_dev, unsigned* epoch = nullptr);
+                            const int* n_dev, unsigned* epoch = nullptr, int* len = nullptr, int* row_pos = nullptr);
 
 struct HeadStepArgs {
   const float* hh; int w;            // residual stream of the head [n, w]
@@ -209,8 +224,7 @@ hipError_t launch_catchup_pack(hipStream_t s, const int* n_accept, const float* 
                                int* nq, float* x_pack);
 
 // cache_len[b] += base + (n ? n[b] : 0)
-// row_pos (optional, one row per sample): row b's position is refreshed to the new length
-hipError_t launch_len_add(hipStream_t s, int* cache_len, const int* n, int base, int B, int* row_pos = nullptr);
+hipError_t launch_len_add(hipStream_t s, int* cache_len, const int* n, int base, int B);
 hipError_t launch_fill_i32(hipStream_t s, int* p, int v, int n);
 hipError_t launch_fill_f32(hipStream_t s, float* p, float v, size_t n);
 // copy rows: dst[dmap ? dmap[r] : r, :] = src[r, :] for r < n (fp32 or storage type by elem_size)

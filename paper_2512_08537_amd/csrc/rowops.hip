@@ -185,6 +185,7 @@ __device__ __forceinline__ f32x4 load4f<bf16>(const bf16* p) {
 }
 
 constexpr int NORM_MAX_D = 8192;
+constexpr float ENT_LOG2E = 1.4426950408889634f, ENT_LN2 = 0.6931471805599453f;
 template <typename T>
 __device__ __forceinline__ void store4(T* p, float a, float b, float c, float d);
 template <>
@@ -223,7 +224,8 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void norm_kernel(const float
                                                                      const float* __restrict__ be, T* __restrict__ out, int d,
                                                                      int ldm, int M, const int* m_dev, const int* __restrict__ in_map,
                                                                      const float* __restrict__ parts, int n_parts, size_t part_stride,
-                                                                     float* h_wb, int rms, float eps, int out_tiled) {
+                                                                     float* h_wb, int rms, float eps, int out_tiled,
+                                                                     float* __restrict__ ent) {
   __shared__ __attribute__((aligned(8))) float red[32];
   const int r = blockIdx.x;
   // (rows past the device-side count are read, not written: the buffers hold M rows, and a stale index is clamped to them)
@@ -287,6 +289,35 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void norm_kernel(const float
   // RMS norm: E[x^2] = E[(x-p)^2] + 2 p E[x-p] + p^2
   const float var = rms ? fmaxf(m2 + 2.f * pivot * m1 + pivot * pivot, 0.f) : fmaxf(m2 - m1 * m1, 0.f);
   const float rstd = 1.0f / sqrtf(var + eps);
+  if (!MOD && ent != nullptr) {
+    // softmax entropy over the channels of the row (the shallow-feature indicator), in base-2 units as in ent_row_regs
+    __shared__ float red_m[16];
+    __shared__ __attribute__((aligned(8))) float red_e[32];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      if ((int)(threadIdx.x + i * blockDim.x) < n4) mx = fmaxf(mx, fmaxf(fmaxf(x[i][0], x[i][1]), fmaxf(x[i][2], x[i][3])));
+    }
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) red_m[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) mx = fmaxf(mx, red_m[i]);
+    const float m2x = mx * ENT_LOG2E;
+    float l = 0.f, a = 0.f;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      if ((int)(threadIdx.x + i * blockDim.x) < n4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float t = fmaf(x[i][e], ENT_LOG2E, -m2x), w = __builtin_amdgcn_exp2f(t);
+          l += w;
+          a = fmaf(w, t, a);
+        }
+      }
+    }
+    block_sum2(l, a, red_e);
+    if (threadIdx.x == 0) ent[r] = __logf(l) - ENT_LN2 * a / l;
+  }
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
     const int c4 = threadIdx.x + i * blockDim.x;
@@ -299,6 +330,112 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void norm_kernel(const float
     if (ga != nullptr) y = MOD ? y * (1.0f + gv[i]) : y * gv[i];
     if (be != nullptr) y += bv[i];
     store4<T>(out + (out_tiled ? tile_offset(r, c4 * 4, d) : (size_t)r * d + c4 * 4), y[0], y[1], y[2], y[3]);
+  }
+}
+
+// The draft's final norm together with the step's threshold (entropy_step_kernel), up to 64 samples: every workgroup finds
+// the samples still speculating from the entropies and the flags before the step (one ballot), workgroup r normalises the
+// row of the r-th of them, and workgroup 0 leaves the step's results for the kernels that follow.  The flags alternate
+// between two buffers, so that no workgroup reads what another writes.
+template <typename T, int VPT>
+__global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void final_step_kernel(const float* __restrict__ h, const float* __restrict__ ga,
+                                                                           const float* __restrict__ be, T* __restrict__ out, int d,
+                                                                           int B, const float* __restrict__ parts, int n_parts,
+                                                                           size_t part_stride, int rms, float eps, EntStep st) {
+  __shared__ __attribute__((aligned(8))) float red[32];
+  const int r = blockIdx.x, lane = threadIdx.x & 63;
+  const int bb = lane < B ? lane : 0;
+  const float hv = st.H_in[bb];
+  const int was = st.alive_in[bb];
+  const int now = lane < B && was && !(hv < st.tau);
+  const unsigned long long mask = __ballot(now);
+  const int rank = __popcll(mask & ((1ull << lane) - 1)), n_act = __popcll(mask);
+  if (r == 0 && threadIdx.x < 64 && lane < B) {
+    st.H[(size_t)lane * st.K + st.step] = was ? hv : 0.f;
+    st.keep[(size_t)lane * st.K + st.step] = (uint8_t)now;
+    st.alive_out[lane] = now;
+    st.n_keep[lane] += now;
+    if (now) {
+      st.act_idx[rank] = lane;
+      st.emap[rank] = lane * (st.K + 1) + st.step;
+      st.omap[rank] = lane * st.K + st.step;
+    }
+    if (lane == 0) *st.n_act = n_act;
+  }
+  if (r >= n_act) return;
+  const int src = __ffsll((unsigned long long)__ballot(now && rank == r)) - 1;
+  const size_t ro = (size_t)src * d;
+  const int n4 = d >> 2;
+  const float pivot = h[ro];
+  const float* bp = be != nullptr ? be : ga;
+  f32x4 x[VPT], gv[VPT], bv[VPT];
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) {
+    const int c4 = threadIdx.x + i * blockDim.x;
+    const int cc = (c4 < n4 ? c4 : 0) * 4;
+    x[i] = *(const f32x4*)(h + ro + cc);
+    gv[i] = *(const f32x4*)(ga + cc);
+    bv[i] = *(const f32x4*)(bp + cc);
+  }
+  for (int p0 = 0; p0 < n_parts; p0 += 4) {
+    f32x4 t[4][VPT];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < VPT; ++i) {
+        const int c4 = threadIdx.x + i * blockDim.x;
+        t[q][i] = *(const f32x4*)(parts + (size_t)(p0 + q < n_parts ? p0 + q : p0) * part_stride + ro + (c4 < n4 ? c4 : 0) * 4);
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (p0 + q < n_parts) {
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) x[i] += t[q][i];
+      }
+    }
+  }
+  float s = 0.f, q = 0.f;
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) {
+    if ((int)(threadIdx.x + i * blockDim.x) < n4) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { const float t = x[i][e] - pivot; s += t; q = fmaf(t, t, q); }
+    }
+  }
+  block_sum2(s, q, red);
+  const float m1 = s / (float)d, m2 = q / (float)d;
+  const float mean = rms ? 0.f : pivot + m1;
+  const float var = rms ? fmaxf(m2 + 2.f * pivot * m1 + pivot * pivot, 0.f) : fmaxf(m2 - m1 * m1, 0.f);
+  const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) {
+    const int c4 = threadIdx.x + i * blockDim.x;
+    if (c4 >= n4) continue;
+    f32x4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = (x[i][e] - mean) * rstd * gv[i][e];
+    if (be != nullptr) y += bv[i];
+    store4<T>(out + (size_t)r * d + c4 * 4, y[0], y[1], y[2], y[3]);
+  }
+}
+
+// Start of a stage of a round: the lengths to roll back to, and (alive != nullptr) every sample alive with nothing kept;
+// z0 and z1 (nz floats each; z1 may be null) cleared: dropped drafts keep finite values, they still travel through the
+// dense draft rows.
+__global__ __launch_bounds__(256) void stage_begin_kernel(const int* __restrict__ len, int* __restrict__ len_base,
+                                                          int* __restrict__ alive, int* __restrict__ n_keep, int B,
+                                                          float* __restrict__ z0, float* __restrict__ z1, size_t nz) {
+  const size_t i0 = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)gridDim.x * 256;
+  for (size_t i = i0; i < (size_t)B; i += step) {
+    len_base[i] = len[i];
+    if (alive != nullptr) {
+      alive[i] = 1;
+      n_keep[i] = 0;
+    }
+  }
+  for (size_t i = i0; i < nz; i += step) {
+    z0[i] = 0.f;
+    if (z1 != nullptr) z1[i] = 0.f;
   }
 }
 
@@ -533,8 +670,7 @@ __global__ __launch_bounds__(256) void kv_load_kernel(KvGeom kv, const T* __rest
 // (m, l, a) kept in base-2 units: m = log2(e) * (reference value), l = sum 2^t, a = sum 2^t * t with
 // t = log2(e) * x - m.  The reference cancels in H = ln l - ln(2) * a / l, so any m that avoids overflow is
 // valid; lanes are merged through a wave maximum and two wave sums.
-constexpr float LOG2E = 1.4426950408889634f;
-constexpr float LN2 = 0.6931471805599453f;
+constexpr float LOG2E = ENT_LOG2E, LN2 = ENT_LN2;
 struct Mla { float m, l, a; };
 // Move the reference of s up to the element value mx (no-op when it is not larger).
 __device__ __forceinline__ void mla_raise(Mla& s, float mx) {
@@ -723,13 +859,9 @@ __device__ __forceinline__ int block_excl_scan(int v, int* s_scan, int* total) {
 }
 
 // H[r] = entropy of row r (one wave per row, rows `ld` elements apart).
-// With n_parts > 0 (fp32 rows held in registers only; the host checks ent_rows_in_regs) the row is
-// feat[r] + sum_p parts[p * part_stride + r * L + .]: pending partial planes of a K-sliced GEMM, added in
-// plane order.
 template <typename T>
 __global__ __launch_bounds__(256) void entropy_rows_kernel(const T* __restrict__ feat, int ld, int rows, int L,
-                                                           float* __restrict__ H, const float* __restrict__ parts = nullptr,
-                                                           int n_parts = 0, size_t part_stride = 0) {
+                                                           float* __restrict__ H) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = blockIdx.x * 4 + wave;
   if (r >= rows) return;
@@ -739,14 +871,6 @@ __global__ __launch_bounds__(256) void entropy_rows_kernel(const T* __restrict__
   if ((((uintptr_t)row) & 15) == 0 && L % VE == 0 && L >= VE && L / VE <= ENT_NCH * WAVE) {
     typename EntVec<T>::type v[ENT_NCH];
     ent_fetch<T>(row, 0, L / VE, lane, v);
-    if constexpr (sizeof(T) == 4) {
-      for (int p = 0; p < n_parts; ++p) {
-        f32x4 w[ENT_NCH];
-        ent_fetch<float>(parts + p * part_stride + (size_t)r * L, 0, L / VE, lane, w);
-#pragma unroll
-        for (int j = 0; j < ENT_NCH; ++j) v[j] += w[j];
-      }
-    }
     h = ent_row_regs<T>(v, L / VE, lane);
   } else {
     h = row_entropy_wave(row, L, lane);
@@ -887,7 +1011,8 @@ __global__ __launch_bounds__(256) void entropy_compact_kernel(const int* __restr
 
 __global__ __launch_bounds__(256) void entropy_step_kernel(const float* __restrict__ ent_heads, int n_heads,
                                                            const float* __restrict__ H_in, int B, int K, int step,
-                                                           float tau, float* __restrict__ H, uint8_t* keep, int* alive,
+                                                           float tau, float* __restrict__ H, uint8_t* keep,
+                                                           const int* __restrict__ alive_in, int* __restrict__ alive_out,
                                                            int* n_keep, int* act_idx, int* n_act, int* emap,
                                                            int* omap) {
   __shared__ int s_scan[256];
@@ -907,11 +1032,11 @@ __global__ __launch_bounds__(256) void entropy_step_kernel(const float* __restri
       } else {
         h = H_in[b];
       }
-      const int was = alive[b];
+      const int was = alive_in[b];
       now = (was && !(h < tau)) ? 1 : 0;
       H[(size_t)b * K + step] = was ? h : 0.f;
       keep[(size_t)b * K + step] = (uint8_t)now;
-      alive[b] = now;
+      alive_out[b] = now;
       n_keep[b] += now;
     }
     s_scan[tid] = now;
@@ -1014,8 +1139,10 @@ __global__ __launch_bounds__(256) void head_prep_kernel(const float* __restrict_
                                                         int n, int D, int S, const float* __restrict__ xsrc,
                                                         const int* __restrict__ xmap, float xscale, float* __restrict__ hh,
                                                         T* __restrict__ sc, float* __restrict__ xt_out, const int* n_dev,
-                                                        unsigned* __restrict__ epoch) {
+                                                        unsigned* __restrict__ epoch, int* __restrict__ len,
+                                                        int* __restrict__ row_pos) {
   if (epoch != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *epoch += 1;
+  if (len != nullptr && (blockIdx.x | threadIdx.x) == 0) row_pos[blockIdx.y] = ++len[blockIdx.y];
   const int r = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * 4, cc = c < w ? c : 0;
   const f32x4 czv = *(const f32x4*)(cz + (size_t)r * w + cc);
   f32x4 wv[16], v = *(const f32x4*)(b_in + cc);
@@ -1206,13 +1333,9 @@ __global__ __launch_bounds__(64) void accept_kernel(const float* __restrict__ x,
   }
 }
 
-__global__ void len_add_kernel(int* cache_len, const int* n, int base, int B, int* row_pos) {
+__global__ void len_add_kernel(int* cache_len, const int* n, int base, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) {
-    const int v = cache_len[b] + base + (n ? n[b] : 0);
-    cache_len[b] = v;
-    if (row_pos) row_pos[b] = v;             // one row per sample: row b's next position
-  }
+  if (b < B) cache_len[b] += base + (n ? n[b] : 0);
 }
 __global__ void fill_i32_kernel(int* p, int v, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1384,8 +1507,9 @@ hipError_t launch_add_parts(hipStream_t s, float* h, const float* parts, int n_p
 hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M, const int* m_dev, int norm_type,
                        float eps, const float* g, const float* b, const float* shift, const float* scale, int ldm,
                        const int* in_map, void* out, const float* parts, int n_parts, size_t part_stride, float* h_wb,
-                       int out_tiled) {
+                       int out_tiled, float* ent) {
   if (M <= 0) return hipSuccess;
+  if (ent != nullptr && (scale != nullptr || in_map != nullptr)) return hipErrorInvalidValue;
   if (d % 4 != 0 || d > NORM_MAX_D || ldm % 4 != 0 || (out_tiled && (!is_bf16 || d % 32 != 0))) return hipErrorInvalidValue;
   const bool mod = scale != nullptr;
   if (mod && (g != nullptr || b != nullptr || shift == nullptr)) return hipErrorInvalidValue;   // (one or the other: as every caller has it)
@@ -1396,7 +1520,7 @@ hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M,
   const int rms = norm_type != 0;
 #define FARD_NORM_L(TV, VPT, MODV, NPV)                                                                                        \
   norm_kernel<TV, VPT, MODV, NPV><<<M, threads, 0, s>>>(h, ga, be, (TV*)out, d, ldm, M, m_dev, in_map, parts, n_parts, part_stride, \
-                                                        h_wb, rms, eps, out_tiled)
+                                                        h_wb, rms, eps, out_tiled, ent)
 #define FARD_NORM_P(TV, VPT)                                    \
   do {                                                          \
     if (mod && n_parts == 0) FARD_NORM_L(TV, VPT, true, 0);     \
@@ -1413,6 +1537,30 @@ hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M,
   }
 #undef FARD_NORM_P
 #undef FARD_NORM_L
+  return hipGetLastError();
+}
+
+hipError_t launch_final_step(hipStream_t s, int is_bf16, const float* h, int d, int B, int norm_type, float eps, const float* g,
+                             const float* b, void* out, const float* parts, int n_parts, size_t part_stride, const EntStep& st) {
+  if (B <= 0) return hipSuccess;
+  if (B > ENT_STEP_MAX_B || d % 4 != 0 || d > NORM_MAX_D || g == nullptr) return hipErrorInvalidValue;
+  const int n4 = d >> 2, vpt = n4 <= 512 ? 1 : 2, threads = ((n4 + vpt - 1) / vpt + 63) / 64 * 64, rms = norm_type != 0;
+#define FARD_FS(TV, VPT) \
+  final_step_kernel<TV, VPT><<<B, threads, 0, s>>>(h, g, b, (TV*)out, d, B, parts, n_parts, part_stride, rms, eps, st)
+  if (is_bf16) {
+    if (vpt == 1) FARD_FS(bf16, 1); else FARD_FS(bf16, 2);
+  } else {
+    if (vpt == 1) FARD_FS(float, 1); else FARD_FS(float, 2);
+  }
+#undef FARD_FS
+  return hipGetLastError();
+}
+
+hipError_t launch_stage_begin(hipStream_t s, const int* len, int* len_base, int* alive, int* n_keep, int B, float* z0, float* z1,
+                              size_t nz) {
+  const unsigned blocks = (unsigned)std::min<size_t>((std::max<size_t>(nz, (size_t)B) + 255) / 256, 2048);
+  if (blocks == 0) return hipSuccess;
+  stage_begin_kernel<<<blocks, 256, 0, s>>>(len, len_base, alive, n_keep, B, z0, z1, nz);
   return hipGetLastError();
 }
 
@@ -1504,39 +1652,32 @@ hipError_t launch_entropy_prefilter(hipStream_t s, int is_bf16, const void* feat
   return hipGetLastError();
 }
 
-bool ent_rows_in_regs_f32(const float* feat, int ld, int L) {
-  return (((uintptr_t)feat) & 15) == 0 && ld % 4 == 0 && L % 4 == 0 && L >= 4 && L / 4 <= ENT_NCH * WAVE;
-}
-
-hipError_t launch_entropy_rows_f32(hipStream_t s, const float* feat, int ld, int rows, int L, float* H, const float* parts,
-                                   int n_parts, size_t part_stride) {
+hipError_t launch_entropy_rows_f32(hipStream_t s, const float* feat, int ld, int rows, int L, float* H) {
   if (rows <= 0) return hipSuccess;
-  if (n_parts > 0 && (!ent_rows_in_regs_f32(feat, ld, L) || (((uintptr_t)parts) & 15) != 0 || part_stride % 4 != 0))
-    return hipErrorInvalidValue;
-  entropy_rows_kernel<float><<<(rows + 3) / 4, 256, 0, s>>>(feat, ld, rows, L, H, parts, n_parts, part_stride);
+  entropy_rows_kernel<float><<<(rows + 3) / 4, 256, 0, s>>>(feat, ld, rows, L, H);
   return hipGetLastError();
 }
 
 hipError_t launch_entropy_step(hipStream_t s, const float* ent_heads, int n_heads, const float* H_in, int B, int K,
-                               int step, float tau, float* H, uint8_t* keep, int* alive, int* n_keep, int* act_idx,
-                               int* n_act, int* emap, int* omap) {
-  entropy_step_kernel<<<1, 256, 0, s>>>(ent_heads, n_heads, H_in, B, K, step, tau, H, keep, alive, n_keep, act_idx,
-                                        n_act, emap, omap);
+                               int step, float tau, float* H, uint8_t* keep, const int* alive_in, int* alive_out, int* n_keep,
+                               int* act_idx, int* n_act, int* emap, int* omap) {
+  entropy_step_kernel<<<1, 256, 0, s>>>(ent_heads, n_heads, H_in, B, K, step, tau, H, keep, alive_in, alive_out, n_keep,
+                                        act_idx, n_act, emap, omap);
   return hipGetLastError();
 }
 
 hipError_t launch_head_prep(hipStream_t s, int is_bf16, const float* xsrc, const int* xmap, float xscale, int D,
                             const void* w_in, const float* b_in, const float* cz, const float* temb, int S, float* hh,
-                            void* sc, float* xt_out, int w, int n, const int* n_dev, unsigned* epoch) {
+                            void* sc, float* xt_out, int w, int n, const int* n_dev, unsigned* epoch, int* len, int* row_pos) {
   if (n <= 0) return hipSuccess;
   if (w % 4 != 0 || D > 16) return hipErrorInvalidValue;
   dim3 grid((w + 1023) / 1024, n);
   if (is_bf16)
     head_prep_kernel<bf16><<<grid, 256, 0, s>>>(cz, (const bf16*)w_in, b_in, temb, w, n, D, S, xsrc, xmap, xscale, hh, (bf16*)sc,
-                                                xt_out, n_dev, epoch);
+                                                xt_out, n_dev, epoch, len, row_pos);
   else
     head_prep_kernel<float><<<grid, 256, 0, s>>>(cz, (const float*)w_in, b_in, temb, w, n, D, S, xsrc, xmap, xscale, hh, (float*)sc,
-                                                 xt_out, n_dev, epoch);
+                                                 xt_out, n_dev, epoch, len, row_pos);
   return hipGetLastError();
 }
 
@@ -1593,8 +1734,9 @@ hipError_t launch_accept(hipStream_t s, const float* x, const float* mu_p, const
   return hipGetLastError();
 }
 
-hipError_t launch_len_add(hipStream_t s, int* cache_len, const int* n, int base, int B, int* row_pos) {
-  len_add_kernel<<<(B + 255) / 256, 256, 0, s>>>(cache_len, n, base, B, row_pos);
+hipError_t launch_len_add(hipStream_t s, int* cache_len, const int* n, int base, int B) {
+  if (B <= 0) return hipSuccess;
+  len_add_kernel<<<(B + 255) / 256, 256, 0, s>>>(cache_len, n, base, B);
   return hipGetLastError();
 }
 hipError_t launch_fill_i32(hipStream_t s, int* p, int v, int n) {
