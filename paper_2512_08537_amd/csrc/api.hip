@@ -631,6 +631,17 @@ hipError_t gemm(fard_ctx* c, const void* A, int lda, const void* W, const float*
   return launch_gemm_bf16(c->stream, a);
 }
 
+// fp32: the product of the rows' norm (ga, be; norm_ld > 0: modulation rows) without a launch for the norm.
+hipError_t gemm_normed(fard_ctx* c, const float* rows, const void* W, const float* bias, void* out, int M, int N, int K, const int* m_dev,
+                       int act, const float* ga, const float* be, int norm_ld, int rms, float eps) {
+  GemmArgs a;
+  a.A = rows; a.lda = K; a.W = W; a.bias = bias; a.out = out; a.ldo = N; a.gate = nullptr; a.ldg = 0;
+  a.M = M; a.N = N; a.K = K; a.m_dev = m_dev; a.act = act; a.epi = EPI_STORE;
+  a.norm_ga = ga; a.norm_be = be; a.norm_ld = norm_ld; a.norm_rms = rms; a.norm_eps = eps;
+  Bracket br(c, CLS_GEMM, 2.0 * M * (double)N * K, (double)K * N * 4 + (double)M * K * 4 + (double)M * N * 4);
+  return launch_gemm_f32(c->stream, a);
+}
+
 int load_head(fard_ctx* c, Loader& ld) {
   const fard_head_cfg& hc = c->cfg.head;
   HeadW& hw = c->head;
@@ -994,15 +1005,19 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
   const bool ff_tiled = up_narrow && down_narrow;
   for (int l = l0; l < l1; ++l) {
     const LayerW& L = m.L[l];
-    if (!(first_norm_done && l == l0 && c->pend_n == 0)) {
+    const bool normed = first_norm_done && l == l0 && c->pend_n == 0;
+    // fp32, few rows: the norms ride in the products behind them
+    const bool ride1 = !c->bf16 && !normed && !(l == l0 && row_entropy) && gemm_f32_norm_fits(M, QN, d, EPI_STORE);
+    const bool ride2 = !c->bf16 && gelu && gemm_f32_norm_fits(M, F, d, EPI_STORE);
+    if (!normed && !ride1) {
       Bracket br(c, CLS_OTHER);
       HIPCHK(c, launch_norm(s, c->bf16, c->h, d, M, m_dev, t.norm, t.norm_eps, L.n1g, L.n1b, nullptr, nullptr, 0, nullptr, c->u,
                             c->parts, c->pend_n, c->pend_stride, c->h, u1_tiled, l == l0 ? row_entropy : nullptr));
       c->pend_n = 0;
     }
     KvGeom kg = kv_geom(c, m, l);
-    // learned positions, bf16: the attention kernel stores the new K / V rows itself
-    const bool fused_append = c->bf16 && t.pos != FARD_POS_ROPE;
+    // learned positions: the attention kernel stores the new K / V rows itself
+    const bool fused_append = (c->bf16 || attn_f32_wide(kg, t.n_heads, QN)) && t.pos != FARD_POS_ROPE;
     if (!fused_append && c->bf16 && (plane_splits(c, M, QN, d) > 0 || qkv_small_planes(c, m, M))) {
       // the QKV product as K-slice planes, summed by the kernel that rotates q, k and appends k, v to the cache
       int n_pl = 0;
@@ -1015,6 +1030,8 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
         GemmExtra ex;
         ex.a_tiled = 1;
         HIPCHK(c, gemm(c, c->u, d, L.wqkv, L.bqkv, c->qkv, QN, M, QN, d, m_dev, EPI_STORE, ACT_NONE, nullptr, 0, &ex));
+      } else if (ride1) {
+        HIPCHK(c, gemm_normed(c, c->h, L.wqkv, L.bqkv, c->qkv, M, QN, d, m_dev, ACT_NONE, L.n1g, L.n1b, 0, t.norm != FARD_NORM_LAYER, t.norm_eps));
       } else {
         HIPCHK(c, gemm(c, c->u, d, L.wqkv, L.bqkv, c->qkv, QN, M, QN, d, m_dev, EPI_STORE, ACT_NONE));
       }
@@ -1075,7 +1092,8 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
       } else {
         HIPCHK(c, gemm(c, c->ao, HD, L.wo, L.bo, c->h, d, M, d, HD, m_dev, EPI_RESID, ACT_NONE));
       }
-      { Bracket br(c, CLS_OTHER);
+      if (!ride2) {
+        Bracket br(c, CLS_OTHER);
         HIPCHK(c, launch_norm(s, c->bf16, c->h, d, M, m_dev, t.norm, t.norm_eps, L.n2g, L.n2b, nullptr, nullptr, 0, nullptr, c->u,
                               c->parts, c->pend_n, c->pend_stride, c->h, up_narrow));
         c->pend_n = 0; }
@@ -1083,6 +1101,8 @@ int run_layers(fard_ctx* c, int which, int l0, int l1, int B, int M, int nq_max,
         GemmExtra ex;
         ex.a_tiled = 1; ex.out_tiled = ff_tiled;
         HIPCHK(c, gemm(c, c->u, d, L.w1, L.b1, c->ff, F, M, F, d, m_dev, EPI_STORE, ACT_GELU, nullptr, 0, &ex));
+      } else if (ride2) {
+        HIPCHK(c, gemm_normed(c, c->h, L.w1, L.b1, c->ff, M, F, d, m_dev, ACT_GELU, L.n2g, L.n2b, 0, t.norm != FARD_NORM_LAYER, t.norm_eps));
       } else if (gelu) {
         HIPCHK(c, gemm(c, c->u, d, L.w1, L.b1, c->ff, F, M, F, d, m_dev, EPI_STORE, ACT_GELU));
       } else {
@@ -1179,7 +1199,9 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
     for (int j = 0; j < Nb && !chain; ++j) {
       const float* mj = modk + (size_t)3 * w * j;
       const bool folded = fold && j > 0;
-      if (!folded) {
+      if (!c->bf16 && gemm_f32_norm_fits(n, w, w, EPI_STORE)) {
+        HIPCHK(c, gemm_normed(c, c->hh, hw.B[j].w1, hw.B[j].b1, c->a2, n, w, w, n_dev, ACT_SILU, mj + w, mj, hw.mod_n, 0, 1e-6f));
+      } else if (!folded) {
         { Bracket br(c, CLS_OTHER);
           HIPCHK(c, launch_norm(s, c->bf16, c->hh, w, n, n_dev, 0, 1e-6f, nullptr, nullptr, mj, mj + w, hw.mod_n, nullptr, c->a1,
                                 nullptr, 0, 0, nullptr, g1_narrow)); }

@@ -390,7 +390,95 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnSplit sp, int n_hea
   }
 }
 
-// fp32 path: one wave per (row, head).
+// fp32 path, head dims 32 / 64 / 128: one workgroup per (head, row, sample).  Every score is one chain of fused multiply-adds
+// over the dims, every output one over the keys, and the sums of the exponentials go by lanes of one wave, all as in the
+// kernel for any head dim below: the same bits.  A thread has a key for the scores (all its loads at once), the values go
+// through LDS a tile of keys at a time, the first tile asked for before the scores.  append: the new rows' keys and values
+// are read from qkv and stored to the cache by the first query head of their kv head.  (One wave, a key a lane and the
+// values one after the other from memory: 16-17 us at 69 keys.)
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_wide_kernel(const int* __restrict__ cache_len, const int* __restrict__ row_start,
+                                                            const int* __restrict__ row_cnt, const float* __restrict__ qkv, int ld,
+                                                            int n_heads, KvGeom kv, int B, float* __restrict__ out, int ldo,
+                                                            float* __restrict__ ent_heads, int pass_stride, int append) {
+  extern __shared__ __attribute__((aligned(16))) float s_p[];   // [ctx_pad] scores / probabilities
+  __shared__ float s_la[2];
+  constexpr int TV = DH / 4, KT = 8192 / DH, NV = KT * TV / 256;   // threads a key of a tile, keys of a tile (32 KB), pieces a thread
+  __shared__ __attribute__((aligned(16))) float s_v[KT * DH];
+  const int head = blockIdx.x, j = blockIdx.y, z = blockIdx.z;
+  const int b = z % B, pass_off = (z / B) * pass_stride;   // passes of one launch: blockIdx.z = pass * B + b
+  const int p0 = cache_len[pass_off + b], r0 = row_start[pass_off + b];
+  const int nq = row_cnt ? row_cnt[pass_off + b] : row_start[pass_off + b + 1] - r0;
+  if (j >= nq) return;
+  const int Hk = kv.n_kv_heads, G = n_heads / Hk, hk = head / G;
+  const int tid = threadIdx.x;
+  const int vis = p0 + j + 1, n_old = append ? p0 : vis;
+  const float* q = qkv + (size_t)(r0 + j) * ld + (size_t)head * DH;
+  const float* kn = qkv + (size_t)r0 * ld + (size_t)(n_heads + hk) * DH;   // new rows' keys; their values Hk heads on
+  const float* vn = kn + (size_t)Hk * DH;
+  float* Kc = (float*)kv.k + ((size_t)b * Hk + hk) * (size_t)kv.ctx_pad * DH;
+  float* Vc = (float*)kv.v + ((size_t)b * Hk + hk) * (size_t)kv.ctx_pad * DH;
+  f32x4 vv[NV];
+  auto load_v = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = tid + 256 * i, c = min(c0 + e / TV, vis - 1), d = (e % TV) * 4;
+      vv[i] = *(const f32x4*)((c < n_old ? Vc + (size_t)c * DH : vn + (size_t)(c - p0) * ld) + d);
+    }
+  };
+  load_v(0);
+  if (append && head == hk * G && tid < DH) {
+    Kc[(size_t)(p0 + j) * DH + tid] = kn[(size_t)j * ld + tid];
+    Vc[(size_t)(p0 + j) * DH + tid] = vn[(size_t)j * ld + tid];
+  }
+  const float scale = 1.0f / sqrtf((float)DH);
+  for (int c = tid; c < vis; c += 256) {
+    const float* kp = c < n_old ? Kc + (size_t)c * DH : kn + (size_t)(c - p0) * ld;
+    f32x4 k4[DH / 4];
+#pragma unroll
+    for (int i = 0; i < DH / 4; ++i) k4[i] = *(const f32x4*)(kp + 4 * i);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < DH / 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = fmaf(q[4 * i + e], k4[i][e], s);
+    s_p[c] = s * scale;
+  }
+  __syncthreads();
+  if (tid < WAVE) {
+    float mx = -INFINITY;
+    for (int c = tid; c < vis; c += WAVE) mx = fmaxf(mx, s_p[c]);
+    mx = wave_max(mx);
+    float l = 0.f, a = 0.f;
+    for (int c = tid; c < vis; c += WAVE) {
+      const float t = s_p[c] - mx, e = expf(t);
+      s_p[c] = e;
+      l += e;
+      a = fmaf(e, t, a);
+    }
+    l = wave_sum(l);
+    a = wave_sum(a);
+    if (tid == 0) { s_la[0] = l; s_la[1] = a; }
+  }
+  float acc = 0.f;
+  for (int c0 = 0; c0 < vis; c0 += KT) {
+    if (c0 > 0) __syncthreads();                           // the previous tile is read
+#pragma unroll
+    for (int i = 0; i < NV; ++i) *(f32x4*)&s_v[(tid + 256 * i) * 4] = vv[i];
+    __syncthreads();
+    if (c0 + KT < vis) load_v(c0 + KT);
+    if (tid < DH) {
+      const int n = min(KT, vis - c0);
+#pragma unroll 8
+      for (int c = 0; c < n; ++c) acc = fmaf(s_p[c0 + c], s_v[c * DH + tid], acc);
+    }
+  }
+  const float l = s_la[0], inv = 1.0f / l;
+  if (tid < DH) out[(size_t)(r0 + j) * ldo + (size_t)head * DH + tid] = acc * inv;
+  if (ent_heads != nullptr && tid == 0) ent_heads[(size_t)(r0 + j) * n_heads + head] = logf(l) - s_la[1] * inv;
+}
+
+// fp32 path, any head dim: one wave per (row, head).
 __global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ qkv, int ld, int n_heads, KvGeom kv,
                                                       const int* __restrict__ cache_len,
                                                       const int* __restrict__ row_start, const int* __restrict__ row_cnt,
@@ -443,6 +531,12 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ 
 
 }  // namespace
 
+bool attn_f32_wide(const KvGeom& kv, int n_heads, int ld) {
+  const int dh = kv.d_head;
+  return !kv.is_bf16 && (dh == 32 || dh == 64 || dh == 128) && ld % 4 == 0 && kv.n_kv_heads > 0 && n_heads % kv.n_kv_heads == 0 &&
+         kv.ctx_pad <= 7936;                               // (scores and a tile of values in 64 KB of LDS)
+}
+
 hipError_t launch_attention(hipStream_t s, const void* qkv, int ld, int n_heads, KvGeom kv, const int* cache_len,
                             const int* row_start, int B, int nq_max, void* out, int ldo, float* ent_heads, int append,
                             const int* row_cnt, int n_pass, const AttnSplit* split, int M, const int* m_dev, int out_tiled) {
@@ -451,8 +545,19 @@ hipError_t launch_attention(hipStream_t s, const void* qkv, int ld, int n_heads,
   if (n_pass > 1 && (append || row_cnt == nullptr || n_pass > 65535 || (long)B * n_pass > 65535)) return hipErrorInvalidValue;
   if (out_tiled && (!kv.is_bf16 || ldo % 32 != 0)) return hipErrorInvalidValue;
   if (!kv.is_bf16) {
-    if (append) return hipErrorInvalidValue;
     dim3 grid(n_heads, nq_max, B * n_pass);
+    if (attn_f32_wide(kv, n_heads, ld)) {
+      const size_t smem = (size_t)kv.ctx_pad * sizeof(float);
+      auto go = [&](auto dh) {
+        attn_f32_wide_kernel<decltype(dh)::value><<<grid, 256, smem, s>>>(cache_len, row_start, row_cnt, (const float*)qkv, ld, n_heads,
+                                                                         kv, B, (float*)out, ldo, ent_heads, B, append);
+      };
+      if (kv.d_head == 32) go(std::integral_constant<int, 32>{});
+      else if (kv.d_head == 64) go(std::integral_constant<int, 64>{});
+      else go(std::integral_constant<int, 128>{});
+      return hipGetLastError();
+    }
+    if (append) return hipErrorInvalidValue;
     const size_t smem = (size_t)kv.ctx_pad * sizeof(float);
     if (smem > 64 * 1024) return hipErrorInvalidValue;
     attn_f32_kernel<<<grid, 64, smem, s>>>((const float*)qkv, ld, n_heads, kv, cache_len, row_start, row_cnt, B, (float*)out,

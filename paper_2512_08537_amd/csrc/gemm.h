@@ -62,6 +62,12 @@ struct GemmArgs {
   // reads 1 KiB of consecutive memory (lanes whose pieces lie a row apart are served one by one: measured 0.4 us of
   // a 3.9 us launch at 8-16 rows, 0.8 us at 32).  Whole 16-row tiles must be allocated.
   int a_tiled = 0, out_tiled = 0;
+  // fp32 path only (gemm_f32_norm_fits): A holds raw rows, their norm is taken by every workgroup of the product:
+  //   (x - mean) rstd ga[k] + be[k], or with norm_ld > 0 (x - mean) rstd (1 + ga[m, k]) + be[m, k]; be may be null
+  const float* norm_ga = nullptr;
+  const float* norm_be = nullptr;
+  int norm_ld = 0, norm_rms = 0;
+  float norm_eps = 0.f;
 };
 
 // Packed bf16 weight size in elements for a [K, N] matrix (K % 16 == 0, N % 32 == 0).
@@ -70,6 +76,7 @@ inline size_t packed_elems(int K, int N) { return (size_t)K * (size_t)N; }
 // Returns hipSuccess or the launch error.  K % 64 == 0 and N % 32 == 0 are required (bf16 path).
 hipError_t launch_gemm_bf16(hipStream_t s, const GemmArgs& a);
 hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a);
+bool gemm_f32_norm_fits(int M, int N, int K, int epi);
 
 // Tiles with both operands through LDS (gemm_tile.hip): the variant that its rule finds ahead (hundreds of rows and more), -1 for none.
 int gemm_tile_variant(const GemmArgs& a);

@@ -731,7 +731,9 @@ hipError_t launch_wm(hipStream_t s, const GemmArgs& a) {
 // rows x 256 x 256 take 3.0-3.3 us, 9 x 256 x 1024 (k) 7.3 (16 x 16 tiles that step through K 16 at a time, two barriers and a
 // round trip a step: 10.4 and 35.6); 8192 x 4096 x 1024 2.04 ms (4.25).  K split over the lanes is ahead of the chain by
 // 0.5 us for up to 4 rows, and gives other results.
-template <int RM, bool SWIGLU>
+// NORM (RM = 4): the rows' norm in front of the product, a wave a row (K <= 256: one chunk); a launch of its own for it cost
+// 2.3-3.6 us.  The roundings are those of the norm kernel.
+template <int RM, bool SWIGLU, bool NORM>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
   constexpr int KC = 256, LA = KC + 4;                       // (rows of 260 floats: sixteen of them start in different banks)
   constexpr int NC = SWIGLU ? 2 : 1;
@@ -772,10 +774,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
 #pragma unroll
       for (int n = 0; n < NC; ++n) w[n][i] = W[(size_t)kk * a.N + n * ncols];
     }
+    if constexpr (!NORM) {
 #pragma unroll
-    for (int r = 0; r < RM; ++r) {
-      const int k = k0 + tid, gr = m0 + r < M ? m0 + r : M - 1;
-      av[r] = k < a.K ? A[(size_t)gr * a.lda + k] : 0.f;
+      for (int r = 0; r < RM; ++r) {
+        const int k = k0 + tid, gr = m0 + r < M ? m0 + r : M - 1;
+        av[r] = k < a.K ? A[(size_t)gr * a.lda + k] : 0.f;
+      }
     }
   };
   float acc[NC][RT];
@@ -805,6 +809,39 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
           for (int r = 0; r < RT; ++r) acc[n][r] = fmaf(xv[i][r][g][e], wv[i][n][g][e], acc[n][r]);
   };
   load(0);
+  if constexpr (NORM) {
+    // wave r takes row r, four columns a lane: the sums and roundings of the norm kernel
+    const int wr = tid >> 6, lane = tid & 63, gr = m0 + wr < M ? m0 + wr : M - 1;
+    const bool on = lane * 4 < a.K;
+    const int cc = on ? lane * 4 : 0;
+    const f32x4 x = *(const f32x4*)(A + (size_t)gr * a.lda + cc);
+    const f32x4 ga = *(const f32x4*)(a.norm_ga + (size_t)gr * a.norm_ld + cc);
+    const f32x4 be = *(const f32x4*)((a.norm_be != nullptr ? a.norm_be : a.norm_ga) + (size_t)gr * a.norm_ld + cc);
+    const float pivot = A[(size_t)gr * a.lda];
+    float s = 0.f, q = 0.f;
+    if (on) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { const float t = x[e] - pivot; s += t; q = fmaf(t, t, q); }
+    }
+    s = wave_sum(s);
+    q = wave_sum(q);
+    const float m1 = s / (float)a.K, m2 = q / (float)a.K;
+    const float mean = a.norm_rms ? 0.f : pivot + m1;
+    const float var = a.norm_rms ? fmaxf(m2 + 2.f * pivot * m1 + pivot * pivot, 0.f) : fmaxf(m2 - m1 * m1, 0.f);
+    const float rstd = 1.0f / sqrtf(var + a.norm_eps);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma clang fp contract(off)
+      float y = (x[e] - mean) * rstd;
+      if (a.norm_ld > 0) {
+        y = fmaf(y, 1.0f + ga[e], be[e]);
+      } else {
+        y = y * ga[e];
+        if (a.norm_be != nullptr) y = y + be[e];
+      }
+      As[wr * LA + lane * 4 + e] = on ? y : 0.f;
+    }
+  }
   for (int k0 = 0; k0 < a.K; k0 += KC) {
     if (k0 > 0) __syncthreads();                             // the previous chunk is consumed
     if (a.K - k0 < KC) {
@@ -814,8 +851,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
         for (int i = 0; i < 16; ++i)
           if (k0 + ks * 16 + i >= a.K) w[n][i] = 0.f;
     }
+    if constexpr (!NORM) {
 #pragma unroll
-    for (int r = 0; r < RM; ++r) As[r * LA + tid] = av[r];
+      for (int r = 0; r < RM; ++r) As[r * LA + tid] = av[r];
+    }
 #pragma unroll
     for (int n = 0; n < NC; ++n)
 #pragma unroll
@@ -927,6 +966,11 @@ hipError_t launch_gemm_bf16_planes(hipStream_t s, const GemmArgs& a) {
   return hipErrorInvalidValue;
 }
 
+// Few enough rows that workgroups of four are one round of the chip, whole rows in one chunk.
+bool gemm_f32_norm_fits(int M, int N, int K, int epi) {
+  return epi != EPI_SWIGLU && K <= 256 && K % 4 == 0 && (long)((N + 15) / 16) * ((M + 3) / 4) <= 256;
+}
+
 hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a) {
   if (a.M <= 0) return hipSuccess;
   const int ncols = a.epi == EPI_SWIGLU ? a.N / 2 : a.N;
@@ -939,9 +983,14 @@ hipError_t launch_gemm_f32(hipStream_t s, const GemmArgs& a) {
 #define FARD_F32(RM)                                                                          \
   do {                                                                                        \
     const dim3 grid(cols, (unsigned)((a.M + (RM) - 1) / (RM)));                               \
-    if (a.epi == EPI_SWIGLU) gemm_f32_kernel<RM, true><<<grid, 256, 0, s>>>(a);               \
-    else gemm_f32_kernel<RM, false><<<grid, 256, 0, s>>>(a);                                  \
+    if (a.epi == EPI_SWIGLU) gemm_f32_kernel<RM, true, false><<<grid, 256, 0, s>>>(a);        \
+    else gemm_f32_kernel<RM, false, false><<<grid, 256, 0, s>>>(a);                           \
   } while (0)
+  if (a.norm_ga != nullptr) {
+    if (!gemm_f32_norm_fits(a.M, a.N, a.K, a.epi)) return hipErrorInvalidValue;
+    gemm_f32_kernel<4, false, true><<<dim3(cols, (unsigned)((a.M + 3) / 4)), 256, 0, s>>>(a);
+    return hipGetLastError();
+  }
   if (groups(4) <= 256) FARD_F32(4);
   else if (groups(8) <= 512) FARD_F32(8);
   else if (groups(16) <= 640) FARD_F32(16);

@@ -114,6 +114,8 @@ struct AttnSplit {
   float* o;           // [n][rows][n_heads][d_head] unnormalised outputs, relative to the split's own maximum
   float* mla;         // [n][rows][n_heads][4] running maximum, sum, entropy accumulator
 };
+// fp32 caches: whether launch_attention takes them through the kernel that also appends (append is refused otherwise).
+bool attn_f32_wide(const KvGeom& kv, int n_heads, int ld);
 hipError_t launch_attention(hipStream_t s, const void* qkv, int ld, int n_heads, KvGeom kv,
                             const int* cache_len, const int* row_start, int B, int nq_max,
                             void* out, int ldo, float* ent_heads, int append, const int* row_cnt = nullptr,

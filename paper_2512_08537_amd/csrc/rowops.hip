@@ -324,11 +324,21 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void norm_kernel(const float
     if (c4 >= n4) continue;
     // the completed row goes back only here: every thread has the pivot (element 0 of the old row) since the barrier
     if (NP != 0 && h_wb != nullptr) *(f32x4*)(h_wb + ro + c4 * 4) = x[i];
+    // (fp32 results do not depend on which kernel takes a norm: gain and bias are rounded one by one, the modulation is fused)
     f32x4 y;
+    {
+#pragma clang fp contract(off)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = (x[i][e] - mean) * rstd;
-    if (ga != nullptr) y = MOD ? y * (1.0f + gv[i]) : y * gv[i];
-    if (be != nullptr) y += bv[i];
+      for (int e = 0; e < 4; ++e) {
+        y[e] = (x[i][e] - mean) * rstd;
+        if (MOD) {
+          y[e] = fmaf(y[e], 1.0f + gv[i][e], bv[i][e]);
+        } else {
+          if (ga != nullptr) y[e] = y[e] * gv[i][e];
+          if (be != nullptr) y[e] = y[e] + bv[i][e];
+        }
+      }
+    }
     store4<T>(out + (out_tiled ? tile_offset(r, c4 * 4, d) : (size_t)r * d + c4 * 4), y[0], y[1], y[2], y[3]);
   }
 }
@@ -412,9 +422,14 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void final_step_kernel(const
     const int c4 = threadIdx.x + i * blockDim.x;
     if (c4 >= n4) continue;
     f32x4 y;
+    {
+#pragma clang fp contract(off)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = (x[i][e] - mean) * rstd * gv[i][e];
-    if (be != nullptr) y += bv[i];
+      for (int e = 0; e < 4; ++e) {
+        y[e] = (x[i][e] - mean) * rstd * gv[i][e];
+        if (be != nullptr) y[e] = y[e] + bv[i][e];
+      }
+    }
     store4<T>(out + (size_t)r * d + c4 * 4, y[0], y[1], y[2], y[3]);
   }
 }
@@ -1279,7 +1294,11 @@ __global__ __launch_bounds__(512) void head_out_kernel(const float* hh, const fl
     __syncthreads();
     // input projection of the next step
 #pragma unroll
-    for (int j = 0; j < 16; ++j) bi += (j < D) ? wi[j] * xs[j < D ? j : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 16; ++j) {
+      const float xj = xs[j < D ? j : 0];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bi[e] = j < D ? fmaf(wi[j][e], xj, bi[e]) : bi[e];
+    }
     if (on) *(f32x4*)(a.hh_next + (size_t)r * w + c) = bi;
   }
 }
@@ -1439,7 +1458,9 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void embed_norm_kernel(const
       if (b_in == nullptr) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (pos_table) v[i] += load4f<T>(pos_table + (size_t)pos0 * d + cc);
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[i] += (k < D) ? w[i][k] * xr[k] : f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int k = 0; k < 16; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i][e] = k < D ? fmaf(w[i][k][e], xr[k], v[i][e]) : v[i][e];
     }
     if (c4 < n4) {
       *(f32x4*)(h + (size_t)r * d + cc) = v[i];
@@ -1469,10 +1490,15 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void embed_norm_kernel(const
     const int c4 = threadIdx.x + i * blockDim.x;
     if (c4 >= n4) continue;
     f32x4 y;
+    {
+#pragma clang fp contract(off)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = (v[i][e] - mean) * rstd;
-    if (g) y *= gv[i];
-    if (b) y += bv[i];
+      for (int e = 0; e < 4; ++e) {
+        y[e] = (v[i][e] - mean) * rstd;
+        if (g) y[e] = y[e] * gv[i][e];
+        if (b) y[e] = y[e] + bv[i][e];
+      }
+    }
     store4<T>(u + (u_tiled ? tile_offset(r, c4 * 4, d) : (size_t)r * d + c4 * 4), y[0], y[1], y[2], y[3]);
   }
 }

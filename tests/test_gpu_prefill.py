@@ -105,6 +105,34 @@ def test_prefill_f32_swiglu_layers():
     ctx.close()
 
 
+@pytest.mark.parametrize("d,heads,kv_heads", [(256, 8, 8), (256, 4, 2), (256, 2, 1), (288, 3, 3), (128, 8, 8)])
+def test_f32_attention_and_norms_of_few_rows(d, heads, kv_heads):
+    """Head dims 32, 64 and 128 (a workgroup per row and head, which appends the new rows) and 96 and 16 (a wave); contexts around
+    a tile of values and a pass over the keys; then one row per sample, whose norms are taken inside the products (d <= 256)."""
+    from oracle import transformer as tf
+    from synth.configs import RoundCfg, TfCfg, HeadCfg
+    t = TfCfg(n_layers=2, d_model=d, n_heads=heads, n_kv_heads=kv_heads, d_head=d // heads, d_ff=256, max_pos=264)
+    n = np.array([259, 1, 63, 64, 65, 128, 255, 256, 257, 33], np.int32)
+    rc = RoundCfg(name="f32-heads", target=t, draft=t, head=HeadCfg(2, 128, d), K=4, max_batch=len(n), max_ctx=264, entropy_layer=1,
+                  dtype=DT_F32, batch=len(n), n_ctx=8)
+    case = build_case(rc, seed=46, peaky=True)
+    ctx = make_ctx(case)
+    rng = np.random.default_rng(12)
+    x = rng.normal(size=(len(n), 259, t.d_latent)).astype(np.float32)
+    ctx.spec_kv_reset(0, None)
+    z_last = ctx.spec_prefill(0, ctx.dev_f32(x), n)
+    cache, zo = _oracle_prefill(case, 0, x, None, n)
+    assert rel_inf(z_last.float().cpu().numpy(), np.stack([zo[b] for b in range(len(n))])) < TOL[DT_F32]
+    nq = np.ones(len(n), np.int32)
+    nq[1] = 2
+    xs = [rng.normal(size=(q, t.d_latent)).astype(np.float32) for q in nq]
+    z2, _, _ = ctx.spec_forward(0, ctx.dev_f32(np.concatenate(xs)), nq, commit=False)
+    ctx.sync()
+    z2o, _, _ = tf.forward(t, case.W, "target", cache, xs, commit=False)
+    assert rel_inf(z2.float().cpu().numpy(), np.concatenate(z2o)) < TOL[DT_F32]
+    ctx.close()
+
+
 def test_prefill_appends_to_an_existing_cache_and_checks_capacity():
     from paper_2512_08537_amd.binding import FardError
     from oracle import transformer as tf
