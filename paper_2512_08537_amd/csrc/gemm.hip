@@ -41,7 +41,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x16 (&acc)[WM][WN
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int row = m0 + 32 * i + 8 * (e >> 2) + rhalf + (e & 3);
-          if (FULL || row < M) out[(size_t)row * a.ldo + col] = (bf16)(silu(acc[i][0][e]) * acc[i][1][e]);
+          if (FULL || row < M) out[(size_t)row * a.ldo + col] = (bf16)(silu<true>(acc[i][0][e]) * acc[i][1][e]);
         }
     }
     return;
@@ -60,7 +60,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, f32x16 (&acc)[WM][WN
           float v = acc[i][j][e] + bv;
           const size_t o = (size_t)row * a.ldo + col;
           if constexpr (KIND == EPI_STORE) {
-            ((bf16*)a.out)[o] = (bf16)apply_act(v, a.act);
+            ((bf16*)a.out)[o] = (bf16)apply_act<true>(v, a.act);
           } else if constexpr (KIND == EPI_STORE_F32) {
             ((float*)a.out)[o] = apply_act(v, a.act);
           } else if constexpr (KIND == EPI_PARTIAL) {
@@ -121,7 +121,7 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, f32x16 (&acc)
         const f32x4 g = *(const f32x4*)(&lds[row * LDT + pc]), u = *(const f32x4*)(&lds[row * LDT + pc + 32]);
         bf16x4 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (bf16)(silu(g[e]) * u[e]);
+        for (int e = 0; e < 4; ++e) o[e] = (bf16)(silu<true>(g[e]) * u[e]);
         *(bf16x4*)(out + (size_t)gr * a.ldo + (n0 >> 1) + oc) = o;
       }
       continue;
@@ -149,7 +149,7 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, f32x16 (&acc)
       if (epi == EPI_STORE) {
         bf16x4 t;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) t[e] = (bf16)apply_act(v[e], a.act);
+        for (int e = 0; e < 4; ++e) t[e] = (bf16)apply_act<true>(v[e], a.act);
         *(bf16x4*)((bf16*)a.out + o) = t;
       } else if (epi == EPI_STORE_F32) {
 #pragma unroll
@@ -463,7 +463,7 @@ __device__ __forceinline__ void lds_epilogue(const GemmArgs& a, f32x16 (&acc)[WM
       }
       bf16x4 o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = (bf16)(silu(g[e]) * u[e]);
+      for (int e = 0; e < 4; ++e) o[e] = (bf16)(silu<true>(g[e]) * u[e]);
       *(bf16x4*)(out + (size_t)gr * a.ldo + (n0 >> 1) + oc) = o;
     }
     return;
@@ -479,7 +479,7 @@ __device__ __forceinline__ void lds_epilogue(const GemmArgs& a, f32x16 (&acc)[WM
     if (a.epi == EPI_STORE) {
       bf16x4 t;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) t[e] = (bf16)apply_act(v[e], a.act);
+      for (int e = 0; e < 4; ++e) t[e] = (bf16)apply_act<true>(v[e], a.act);
       *(bf16x4*)((bf16*)a.out + o) = t;
     } else if (a.epi == EPI_STORE_F32) {
 #pragma unroll

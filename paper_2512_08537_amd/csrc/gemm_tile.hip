@@ -62,7 +62,7 @@ __device__ __forceinline__ void half_out(const GemmArgs& a, const float* half, i
       for (int h = 0; h < 2; ++h) {
         const f32x4 g = half_read(half, row, c + 4 * h), u = half_read(half, row, 32 + c + 4 * h);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[4 * h + e] = (bf16)(silu(g[e]) * u[e]);
+        for (int e = 0; e < 4; ++e) o[4 * h + e] = (bf16)(silu<true>(g[e]) * u[e]);
       }
       *(bf16x8*)(out + (size_t)(mb + row) * a.ldo) = o;
     }
@@ -76,10 +76,10 @@ __device__ __forceinline__ void half_out(const GemmArgs& a, const float* half, i
       f32x4 v0 = half_read(half, row, c) + b0, v1 = half_read(half, row, c + 4) + b1;
       if (a.act == ACT_GELU) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { v0[e] = gelu_erf(v0[e]); v1[e] = gelu_erf(v1[e]); }
+        for (int e = 0; e < 4; ++e) { v0[e] = gelu_erf<true>(v0[e]); v1[e] = gelu_erf<true>(v1[e]); }
       } else if (a.act == ACT_SILU) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { v0[e] = silu(v0[e]); v1[e] = silu(v1[e]); }
+        for (int e = 0; e < 4; ++e) { v0[e] = silu<true>(v0[e]); v1[e] = silu<true>(v1[e]); }
       }
       bf16x8 o;
 #pragma unroll

@@ -283,7 +283,7 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
       }
       v += b1;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = silu(v[e]);
+      for (int e = 0; e < 4; ++e) v[e] = silu<true>(v[e]);
       if (mine) put4(XB, v, tag + 1);
       __builtin_amdgcn_sched_barrier(0);
       load_w(blk.w2, wt);

@@ -168,7 +168,7 @@ struct NarrowEpi {
       if (a.epi == EPI_STORE) {
         bf16x4 t;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) t[e] = (bf16)apply_act(v[e], a.act);
+        for (int e = 0; e < 4; ++e) t[e] = (bf16)apply_act<true>(v[e], a.act);
         *(bf16x4*)((bf16*)a.out + (a.out_tiled ? ot : o)) = t;
       } else if (a.epi == EPI_STORE_F32) {
 #pragma unroll

@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256, (MT == 2 && NT == 4) ? 2 : 1) void gemm_narrow
     if constexpr (OUT16) {
       bf16x4 b;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) b[e] = (bf16)apply_act(v[e], ACT);
+      for (int e = 0; e < 4; ++e) b[e] = (bf16)apply_act<true>(v[e], ACT);
       const unsigned gc = n0 + ec;
       const unsigned o = (row_tile + (row >> 4)) * t.o_hi + (row & 15u) * t.o_lo + (gc >> 5) * t.o_c32 + ((gc >> 3) & 3u) * t.o_c8 + (gc & 7u);
       *(bf16x4*)((bf16*)t.out + o) = b;

@@ -1175,7 +1175,7 @@ __global__ __launch_bounds__(256) void head_prep_kernel(const float* __restrict_
     *(f32x4*)(hh + (size_t)r * w + c) = v;
     for (int k = 0; k < S; ++k) {
       const f32x4 t = czv + *(const f32x4*)(temb + (size_t)k * w + c);
-      store4<T>(sc + ((size_t)k * n + r) * w + c, silu(t[0]), silu(t[1]), silu(t[2]), silu(t[3]));
+      store4<T>(sc + ((size_t)k * n + r) * w + c, silu<sizeof(T) == 2>(t[0]), silu<sizeof(T) == 2>(t[1]), silu<sizeof(T) == 2>(t[2]), silu<sizeof(T) == 2>(t[3]));
     }
   }
   if (xt_out && blockIdx.x == 0 && (int)threadIdx.x < D) xt_out[(size_t)r * D + threadIdx.x] = xr[threadIdx.x] * xscale;
