@@ -122,18 +122,17 @@ def make_cfg(rc) -> RoundCfg:
 def _ptr(t):
     if t is None:
         return None
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()              # (the argument types make a pointer of it)
 
 
 def entropy_prefilter_static(feat, tau, out, stream=None):
     """feat: device tensor [B, K, L], float32 or bfloat16; out: dict of preallocated device tensors H [B,K] f32,
     keep [B,K] u8, n_keep [B] i32, surv_idx [B*K] i32, n_surv [1] i32.  Allocates nothing."""
-    import torch
     B, K, L = feat.shape
     dt = FARD_BF16 if feat.dtype == torch.bfloat16 else FARD_F32
     code = lib.entropy_prefilter_static(_ptr(feat), dt, B, K, L, float(tau), _ptr(out["H"]), _ptr(out["keep"]),
                                         _ptr(out["n_keep"]), _ptr(out["surv_idx"]), _ptr(out["n_surv"]),
-                                        None if stream is None else C.c_void_p(stream.cuda_stream))
+                                        None if stream is None else stream.cuda_stream)
     if code != 0:
         raise FardError(code, "entropy_prefilter_static")
     return out
