@@ -210,6 +210,49 @@ def test_gemm_narrow_matches_fp64(ctx_bf16, M, K, N, epi):
     assert err < 1e-2, err
 
 
+@pytest.mark.parametrize("K", [1024, 1280, 1536, 2048])
+@pytest.mark.parametrize("N", [32, 64, 160, 2048, 2080])
+@pytest.mark.parametrize("M", [1, 15, 16, 17, 33, 64, 65, 95, 97])
+def test_gemm_narrow_whole_wave_shares(ctx_bf16, M, K, N):
+    """K a whole number of steps per wave, where row tiles of 16 and 32, columns of 16, 32 and 64 meet their edges: every
+    epilogue with and without bias, the rows behind M untouched.  fp32 results: sums of K products, below K / 4 x 2^-24 of
+    sum |a w| (64 levels at most in a lane's chain of 32-k steps): bar 1e-5; bf16 results half an ulp on top."""
+    import torch
+    ctx, _ = ctx_bf16
+    tag = f"x{M}.{K}.{N}"
+    A = gen.normal(18, "A" + tag, (M, K), 1.0, DT_BF16)
+    W = gen.normal(18, "W" + tag, (K, N), 0.05, DT_BF16)
+    b = gen.normal(18, "b" + tag, (N,), 0.1, DT_F32)
+    gate = gen.normal(18, "g" + tag, (M, N), 1.0, DT_F32)
+    base = gen.normal(18, "o" + tag, (M + 1, N), 1.0, DT_F32)
+    dA, dW, db, dg = ctx.dev_store(A), ctx.dev_store(W), ctx.dev_f32(b), ctx.dev_f32(gate)
+    prod = A.astype(np.float64) @ W.astype(np.float64)
+    mag = np.abs(A).astype(np.float64) @ np.abs(W).astype(np.float64)
+    for epi, act, bias in [(0, 0, True), (0, 1, True), (0, 2, False), (1, 0, True), (1, 0, False), (2, 0, False), (2, 0, True),
+                           (3, 0, True)]:
+        out = ctx.dev_f32(base)
+        if epi == 0:
+            out = out.to(torch.bfloat16)
+        torch.cuda.synchronize()
+        ctx.spec_gemm_narrow(dA, dW, out, bias=db if bias else None, gate=dg if epi == 3 else None, epi=epi, act=act)
+        ctx.sync()
+        got = out.float().cpu().numpy().astype(np.float64)
+        v = prod + (b if bias else 0.0)
+        if act:
+            from oracle import transformer as otf
+            v = {1: otf.gelu_erf, 2: otf.silu}[act](v)
+        if epi == 3:
+            v = v * gate
+        if epi >= 2:
+            v = v + base[:M]
+        bar = 1e-5 * (mag * (np.abs(gate) if epi == 3 else 1.0) + 1.0) * (1.2 if act else 1.0)
+        if epi == 0:
+            bar = bar + 2.0 ** -8 * np.abs(v)
+        assert (np.abs(got[:M] - v) <= bar).all(), (epi, act, bias, np.max(np.abs(got[:M] - v) / bar))
+        ref_tail = torch.from_numpy(base[M]).to(torch.bfloat16).float().numpy() if epi == 0 else base[M]
+        assert np.array_equal(got[M].astype(np.float32), ref_tail)
+
+
 @pytest.mark.parametrize("M,K,N,epi", [(32, 1024, 1024, 2), (288, 1024, 1024, 2), (45, 512, 96, 3), (130, 1280, 2048, 3)])
 def test_gemm_narrow_bf16_copy_of_a_residual_update(ctx_bf16, M, K, N, epi):
     import torch
