@@ -832,7 +832,7 @@ int alloc_workspace(fard_ctx* c) {
     HIPCHK(c, hipDeviceGetAttribute(&c->compute_units, hipDeviceAttributeMultiprocessorCount, dev));
     if (const char* q = getenv("GPU_MAX_HW_QUEUES")) c->queues = std::max(c->queues, atoi(q));
     c->xch_rows = M;
-    while (c->xch_rows > 0 && !head_chain_fits(c->xch_rows, w, g.head.n_blocks, g.head.n_steps, c->compute_units, c->queues)) c->xch_rows -= 1;
+    while (c->xch_rows > 0 && head_chain_tiles(c->xch_rows, w, g.head.n_blocks, g.head.n_steps, c->compute_units, c->queues) == 0) c->xch_rows -= 1;
     if (c->xch_rows > 0) {
       const size_t words = head_chain_bytes(c->xch_rows, w) / 4;
       if ((rc = dalloc_bytes(c, &c->xch, words * 4))) return rc;
@@ -1194,7 +1194,7 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
       a.xch = c->xch; a.epoch = c->epoch; a.tag_base = 1 + 2 * Nb * k;
       a.n = n; a.n_dev = n_dev;
       Bracket br(c, CLS_GEMM_NARROW, 4.0 * Nb * n * (double)w * w, 2.0 * Nb * ((double)w * w * 2 + (double)n * w * 2));
-      HIPCHK(c, launch_head_chain(s, a, w));
+      HIPCHK(c, launch_head_chain(s, a, w, head_chain_tiles(n, w, Nb, S, c->compute_units, c->queues)));
     }
     for (int j = 0; j < Nb && !chain; ++j) {
       const float* mj = modk + (size_t)3 * w * j;

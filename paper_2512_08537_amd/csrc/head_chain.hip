@@ -2,7 +2,7 @@
 //
 // As separate launches a block is two dependent products of a few rows with 2-5 MB of weights, each a launch that costs
 // 1.6 us of dispatch (2.5 when another queue waits on this one) and 1.5-2 us of cold start for well under a microsecond
-// of work.  Here one workgroup per 16 columns and 16 rows stays for all blocks: its slice of the fp32 residual rows lives
+// of work.  Here one workgroup per 16 or 32 columns and 16 rows stays for all blocks: its slice of the fp32 residual rows lives
 // in registers, the weights of the next product are requested while the current one runs, and the bf16 rows that every
 // product needs whole pass between the workgroups through memory.
 //
@@ -44,7 +44,8 @@ constexpr int SPIN_LIMIT = 16000000;                       // reads of one excha
 // R: rows that a launch reads per 16-row group (4, 8 or 16).  What bounds a read of an exchange is the compute unit's 64
 // bytes a clock from the vector cache: rows that are not there are not read, and up to 8 rows go through LDS (a wave stores
 // its own share of k and reads it back as operands) instead of every lane reading its row's copy.
-template <int NS, int R>                                   // w = 128 NS
+// CT: 16-column tiles of a workgroup; wave j < CT holds tile j's slice of the rows and writes for it.
+template <int NS, int R, int CT>                           // w = 128 NS
 __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
   constexpr int W_COLS = 128 * NS;
   constexpr bool STAGE = R < 16;
@@ -52,13 +53,13 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
   constexpr int TPR = 256 / R;                             // threads that share a row's tile moments: lanes of one wave
   constexpr int NM = (8 * NS + TPR - 1) / TPR;             // moments a thread reads
   constexpr int LDT = 20;
-  __shared__ __attribute__((aligned(16))) float red[2][4 * 16 * LDT];
+  __shared__ __attribute__((aligned(16))) float red[2][CT][4 * 16 * LDT];
   __shared__ __attribute__((aligned(16))) char stage[STAGE ? 4 * NS * 64 * R : 16];
   __shared__ float rowstat[32];
 
   const unsigned tid = threadIdx.x, lane = tid & 63u, kw = __builtin_amdgcn_readfirstlane(tid >> 6);
   const unsigned kg = lane >> 4, l16 = lane & 15u;
-  const unsigned m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  const unsigned m0 = blockIdx.y * 16, n0 = blockIdx.x * (16 * CT);
   const int n = eff_rows(a.n, a.n_dev);
   if ((int)m0 >= n) return;                                // (uniform over the workgroups of a row group)
   const unsigned rows = (unsigned)n - m0 < (unsigned)R ? (unsigned)n - m0 : (unsigned)R;
@@ -86,22 +87,28 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
     const unsigned t = mt + TPR * i;
     rdm[i] = XM + ((mr < rows ? mr : rows - 1) * (8 * NS) + (t < 8 * NS ? t : 0)) * 16;
   }
-  // writers (wave 0): 4 columns of a row
-  const unsigned er = lane >> 2, ec = (lane & 3u) * 4, col = n0 + ec;
-  const bool out_wave = kw == 0, mine = out_wave && er < rows;
+  // writers: 4 columns of a row
+  const bool out_wave = kw < CT;
+  const unsigned er = lane >> 2, ec = (lane & 3u) * 4, own = out_wave ? kw : 0, col = n0 + 16 * own + ec;
+  const bool mine = out_wave && er < rows;
   const unsigned wr = (((col >> 5) * 8 + ((col >> 2) & 1u) * 4 + ((col >> 3) & 3u)) * R + er) * 16;
-  const unsigned wrm = XM + (er * (8 * NS) + blockIdx.x) * 16;
+  const unsigned wrm = XM + (er * (8 * NS) + blockIdx.x * CT + own) * 16;
   const unsigned gr = m0 + (er < rows ? er : rows - 1);
 
   // weights: packed fragments of this 16-column tile, step s
   const unsigned wl = (lane >> 5) * 1024 + (kg & 1u) * 512 + l16 * 16;
-  const size_t wtile = (size_t)(blockIdx.x >> 1) * (W_COLS / 16) * 1024 + (blockIdx.x & 1u) * 256 + kw * 2048;
-  auto load_w = [&](const void* Wm, bf16x8 (&b)[NS]) {
+  const unsigned t0 = blockIdx.x * CT;
+  const size_t wtile = (size_t)(t0 >> 1) * (W_COLS / 16) * 1024 + (t0 & 1u) * 256 + kw * 2048;
+  auto load_w = [&](const void* Wm, bf16x8 (&b)[CT][NS]) {
     const char* p = (const char*)Wm + wtile;
     unsigned step = 8192;
     asm("" : "+s"(step));
 #pragma unroll
-    for (int i = 0; i < NS; ++i) { b[i] = *(const bf16x8*)(p + wl); p += step; }
+    for (int i = 0; i < NS; ++i) {
+#pragma unroll
+      for (int j = 0; j < CT; ++j) b[j][i] = *(const bf16x8*)(p + wl + j * 256);
+      p += step;
+    }
   };
   // An exchange's words, read until all are there.  The waves that do not write wait 64 x 20-24 cycles first: the words
   // cannot be there sooner, and their reads would stand in the way of the writers' stores (w = 1536, 8 rows, a block: 5.7 us
@@ -136,9 +143,10 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
       if (it >= SPIN_LIMIT) { dead = true; break; }
     }
   };
-  f32x4 acc;
-  auto product = [&](const bf16x8 (&b)[NS]) {
-    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[CT];
+  auto product = [&](const bf16x8 (&b)[CT][NS]) {
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     if constexpr (STAGE) {
       typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
       char* st = stage + kw * (NS * 64 * R);
@@ -151,25 +159,32 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
 #pragma unroll
       for (int p = 0; p < NS; ++p) {
         const bf16x8 f = *(const bf16x8*)(st + ((p * 4 + kg) * R + (l16 % R)) * 16);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, b[p], acc, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, b[j][p], acc[j], 0, 0, 0);
       }
     } else {
 #pragma unroll
       for (int p = 0; p < NS; ++p) {
         const u32x4 f = {x[2 * p][0], x[2 * p][2], x[2 * p + 1][0], x[2 * p + 1][2]};
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f), b[p], acc, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f), b[j][p], acc[j], 0, 0, 0);
       }
     }
-    if (dead) acc = f32x4{1.f, 1.f, 1.f, 1.f} * __builtin_nanf("");
-  };
-  auto to_lds = [&](float* r) {
+    if (dead) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) r[(kw * 16 + 4 * kg + e) * LDT + l16] = acc[e];
+      for (int j = 0; j < CT; ++j) acc[j] = f32x4{1.f, 1.f, 1.f, 1.f} * __builtin_nanf("");
+    }
   };
-  auto from_lds = [&](const float* r) {
+  auto to_lds = [&](float (&r)[CT][4 * 16 * LDT]) {
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[j][(kw * 16 + 4 * kg + e) * LDT + l16] = acc[j][e];
+  };
+  auto from_lds = [&](const float (&r)[CT][4 * 16 * LDT]) {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v += *(const f32x4*)(r + (k * 16 + er) * LDT + ec);
+    for (int k = 0; k < 4; ++k) v += *(const f32x4*)(r[own] + (k * 16 + er) * LDT + ec);
     return v;
   };
   auto put4 = [&](unsigned base, f32x4 v, unsigned tag) {
@@ -198,7 +213,7 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
   const float* mrow = a.mod + ((size_t)gr * a.ldm + col);  // this thread's row and columns of the step's modulations
   f32x4 h = {0.f, 0.f, 0.f, 0.f}, b1, c1, c0, b2, gate, scn;
   float centre = 0.f;
-  bf16x8 wt[NS];
+  bf16x8 wt[CT][NS];
   HeadBlockW blk = a.blocks[0];
   load_w(blk.w1, wt);
   if (out_wave) {
@@ -325,22 +340,34 @@ int head_chain_rows(int n) { return n <= 4 ? 4 : (n <= 8 ? 8 : 16); }
 size_t head_chain_bytes(int rows, int w) { return (size_t)((rows + 15) / 16) * 16 * 9 * w; }
 
 // Every workgroup has to be resident while any of them waits: two fit a compute unit (registers), and as many launches as
-// there are hardware queues may be on the chip side by side.
-bool head_chain_fits(int n, int w, int n_blocks, int n_steps, int compute_units, int queues) {
-  if (w != 1024 && w != 1280 && w != 1536) return false;
-  if (n < 1 || n_blocks < 1 || n_steps < 1 || (long)2 * n_blocks * n_steps >= 4095) return false;
-  return (long)(w / 16) * ((n + 15) / 16) * queues <= 2L * compute_units;
+// there are hardware queues may be on the chip side by side.  Workgroups of one 16-column tile while that holds, else of
+// two, which read as much of the exchange for twice the columns (a decode of 2 steps, launch per product -> resident: 33 rows of
+// 6 x 1024 140 -> 103 us, 64 rows 144 -> 105; 17 rows of 8 x 1280 183 -> 138, 48 rows 196 -> 151; one tile at 32 and 16 rows of
+// these 97 and 128).  At a width of 1536 two tiles do not fit the registers.
+int head_chain_tiles(int n, int w, int n_blocks, int n_steps, int compute_units, int queues) {
+  if (w != 1024 && w != 1280 && w != 1536) return 0;
+  if (n < 1 || n_blocks < 1 || n_steps < 1 || (long)2 * n_blocks * n_steps >= 4095) return 0;
+  const long one = (long)(w / 16) * ((n + 15) / 16) * queues;
+  if (one <= 2L * compute_units) return 1;
+  return w <= 1280 && one <= 4L * compute_units ? 2 : 0;
 }
 
-hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w) {
+hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w, int tiles) {
   if (a.n < 1 || a.n_blocks < 1 || a.tag_base < 1 || a.tag_base + 2 * a.n_blocks > 4096) return hipErrorInvalidValue;
-  const dim3 grid(w / 16, (a.n + 15) / 16);
+  if (tiles != 1 && (tiles != 2 || w > 1280)) return hipErrorInvalidValue;
+  const dim3 grid(w / (16 * tiles), (a.n + 15) / 16);
   const int R = head_chain_rows(a.n);
-#define FARD_HC(NSV)                                                              \
-  case 128 * NSV:                                                                 \
-    if (R == 4) head_chain_kernel<NSV, 4><<<grid, 256, 0, s>>>(a);                \
-    else if (R == 8) head_chain_kernel<NSV, 8><<<grid, 256, 0, s>>>(a);           \
-    else head_chain_kernel<NSV, 16><<<grid, 256, 0, s>>>(a);                      \
+#define FARD_HC(NSV)                                                                \
+  case 128 * NSV:                                                                   \
+    if (tiles == 2) {                                                               \
+      if constexpr (NSV <= 10) head_chain_kernel<NSV, 16, 2><<<grid, 256, 0, s>>>(a); \
+    } else if (R == 4) {                                                            \
+      head_chain_kernel<NSV, 4, 1><<<grid, 256, 0, s>>>(a);                         \
+    } else if (R == 8) {                                                            \
+      head_chain_kernel<NSV, 8, 1><<<grid, 256, 0, s>>>(a);                         \
+    } else {                                                                        \
+      head_chain_kernel<NSV, 16, 1><<<grid, 256, 0, s>>>(a);                        \
+    }                                                                               \
     break
   switch (w) {
     FARD_HC(8);

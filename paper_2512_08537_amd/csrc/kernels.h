@@ -202,8 +202,9 @@ struct HeadChainArgs {
   int n; const int* n_dev;
 };
 size_t head_chain_bytes(int rows, int w);
-bool head_chain_fits(int n, int w, int n_blocks, int n_steps, int compute_units, int queues);
-hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w);
+// 16-column tiles of a workgroup with which a launch of n rows may wait for itself, 0 for none
+int head_chain_tiles(int n, int w, int n_blocks, int n_steps, int compute_units, int queues);
+hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w, int tiles);
 
 // out[n] = act(sum_k in[k] W[k, n] + b[n]) for one fp32 vector (time embedding at init).
 hipError_t launch_matvec(hipStream_t s, int is_bf16, const float* in, const void* W, const float* b,

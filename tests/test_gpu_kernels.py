@@ -616,6 +616,34 @@ def test_diffhead_decode_with_resident_blocks(w, n, live):
     ctx.close()
 
 
+@pytest.mark.parametrize("w,n,live", [(1024, 33, 33), (1024, 48, 47), (1024, 49, 49), (1024, 64, 64), (1024, 65, 65), (1280, 17, 16),
+                                      (1280, 32, 32), (1280, 33, 33), (1280, 48, 31), (1280, 48, 48), (1280, 49, 49), (1536, 17, 1),
+                                      (1536, 31, 31), (1536, 32, 32), (1536, 33, 33)])
+def test_diffhead_decode_with_resident_blocks_of_two_tiles(w, n, live):
+    """More rows: workgroups of 32 columns, up to the row count from which a step goes back to a launch per product."""
+    from oracle import head as ohd
+    from synth.configs import RoundCfg, TfCfg, HeadCfg
+    tf = TfCfg(n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, d_head=64, d_ff=256, max_pos=32)
+    rc = RoundCfg(name="head-chain-2", target=tf, draft=tf, head=HeadCfg(3, w, 128, n_steps=2), K=8, max_batch=16, max_ctx=32,
+                  entropy_layer=1, batch=4, n_ctx=8)
+    case = build_case(rc, seed=10)
+    ctx = make_ctx(case)
+    D, S = rc.head.d_latent, rc.head.n_steps
+    z = gen.normal(19, f"z{w}.{n}", (n, rc.head.d_cond), 1.0, rc.dtype)
+    eps = gen.noise(19, f"e{w}.{n}", (S + 1, n, D))
+    cnt = ctx.dev_i32(np.array([live], np.int32))
+    mu, x = (t.clone() for t in ctx.diffhead_decode(ctx.dev_store(z), ctx.dev_f32(eps), n_rows=cnt))
+    ctx.diffhead_decode(ctx.dev_store(-z), ctx.dev_f32(eps))
+    mu2, x2 = ctx.diffhead_decode(ctx.dev_store(z), ctx.dev_f32(eps), n_rows=cnt)
+    ctx.sync()
+    assert np.array_equal(mu.cpu().numpy()[:live], mu2.cpu().numpy()[:live])
+    assert np.array_equal(x.cpu().numpy()[:live], x2.cpu().numpy()[:live])
+    mu_o, x_o = ohd.decode(rc.head, case.W, z[:live], eps[:, :live])
+    assert rel_inf(mu.cpu().numpy()[:live], mu_o) < 2e-2
+    assert rel_inf(x.cpu().numpy()[:live], x_o) < 2e-2
+    ctx.close()
+
+
 def test_head_closed_form_zero_weights():
     """All head weights zero except the output bias: mu = temperature*eps0 - b_out (1 step)."""
     case = build_case("ln-gelu-bf16", seed=1)
