@@ -85,6 +85,25 @@ def test_round_with_entropy_early_stop(kind):
     _compare_round(case, g, o, tau)
 
 
+@pytest.mark.parametrize("kind", ["ln-gelu-bf16", "ln-gelu-f32"])
+@pytest.mark.parametrize("B", [1, 63, 64, 65])
+def test_entropy_early_stop_around_one_ballot_of_samples(kind, B):
+    """Up to 64 samples a step's threshold and compaction ride in the final norm's launch, above in one of their own."""
+    from synth import configs
+    rc = configs.reduced(kind)
+    rc.max_batch = rc.batch = B
+    case = build_case(rc, seed=33, std_overrides={"in.w": 0.5})
+    o_all = run_oracle_round(case, tau=-1.0)
+    Hs = np.sort(o_all["H"].reshape(-1))
+    lo, hi = len(Hs) // 4, len(Hs) - len(Hs) // 4
+    j = lo + int(np.argmax(np.diff(Hs[lo:hi])))
+    tau = float(0.5 * (Hs[j] + Hs[j + 1]))
+    o = run_oracle_round(case, tau=tau)
+    g = run_gpu_round(case, tau=tau)
+    assert B == 1 or 0 < o["n_keep"].sum() < case.B * rc.K
+    _compare_round(case, g, o, tau)
+
+
 def test_draft_equal_to_target_accepts_everything():
     case = build_case("ln-gelu-bf16", seed=33, same_draft=True)
     g = run_gpu_round(case, tau=-1.0)
