@@ -32,7 +32,8 @@ namespace {
 #define ATTN_MIN_WG(DH, NQB) (((DH) == 64 && (NQB) == 1) ? ATTN_OCC : 1)
 
 constexpr float LN2 = 0.6931471805599453f, LOG2E = 1.4426950408889634f;
-// exponents below this are zero and stay finite times zero (a masked score would be -inf)
+// exponents below this are zero and stay finite times zero: the logarithm in a term p ln p and the distance of two references
+// are held to it (an invisible score is -inf).  Never an exponent itself: the maximum would turn a NaN score into probability 0.
 constexpr float T_MIN = -16384.f;
 
 // c / nq for column indexes (c < 64)
@@ -191,11 +192,10 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
     float psum = 0.f, asum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      float t = fmaf(s[e], sc2, -m_ref);
-      if constexpr (MASK) t = fmaxf(t, T_MIN);
+      const float t = fmaf(s[e], sc2, -m_ref);
       const float p = __builtin_amdgcn_exp2f(t);
       psum += p;
-      if constexpr (ENT) asum = fmaf(p, t, asum);
+      if constexpr (ENT) asum = fmaf(p, MASK ? fmaxf(t, T_MIN) : t, asum);
       pf[e >> 3][e & 7] = (bf16)p;
     }
     psum = xor32_sum(psum);
@@ -362,18 +362,18 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnSplit sp, int n_hea
       lo[s] = *(const f32x4*)(sp.o + slot * dh + d8 * 8);
       hi[s] = *(const f32x4*)(sp.o + slot * dh + d8 * 8 + 4);
     }
-    // (a split that saw no visible key has sum 0 and whatever reference: its maximum does not count)
+    // (a split that saw no visible key has sum 0 and whatever reference: its maximum does not count; a NaN sum does)
     float mstar = -INFINITY;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-      if (s < sp.n && t[s][1] > 0.f) mstar = fmaxf(mstar, t[s][0]);
+      if (s < sp.n && t[s][1] != 0.f) mstar = fmaxf(mstar, t[s][0]);
     float lstar = 0.f, astar = 0.f;
     float acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.f;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      if (s >= sp.n || !(t[s][1] > 0.f)) continue;
+      if (s >= sp.n || t[s][1] == 0.f) continue;
       const float dl = fmaxf(t[s][0] - mstar, T_MIN), f = __builtin_amdgcn_exp2f(dl);
       lstar += f * t[s][1];
       astar += f * (t[s][2] + dl * t[s][1]);
