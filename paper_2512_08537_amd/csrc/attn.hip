@@ -33,7 +33,8 @@ namespace {
 
 constexpr float LN2 = 0.6931471805599453f, LOG2E = 1.4426950408889634f;
 // exponents below this are zero and stay finite times zero: the logarithm in a term p ln p and the distance of two references
-// are held to it (an invisible score is -inf).  Never an exponent itself: the maximum would turn a NaN score into probability 0.
+// are held to it (an invisible or infinitely low score is -inf).  Never an exponent itself: the maximum would turn a NaN score into
+// probability 0.
 constexpr float T_MIN = -16384.f;
 
 // c / nq for column indexes (c < 64)
@@ -43,7 +44,8 @@ __device__ __forceinline__ int col_head(int c, float inv_nq) { return (int)(((fl
 // rows -> merge; 8 us for 16 workgroups at 129 keys), long ones by the K / V stream.  So the wave's first block is requested
 // before the lengths are there; the new rows (APPEND) go into an LDS image of the tail blocks together with the cached
 // positions around them and from there into both the products and, whole 16-byte pieces, the cache; a block's K is requested
-// again as soon as its scores are out, its V as soon as they are summed.  Running maximum and exponentials are in base 2.
+// again as soon as its scores are out, its V as soon as they are summed.  The running maximum is that of the raw
+// scores, exponents and the accumulator a are in base 2.
 template <int DH, int NQB, bool APPEND, bool SPLIT, bool ENT>
 __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(const int* __restrict__ cache_len,
                                                         const int* __restrict__ row_start, const int* __restrict__ row_cnt,
@@ -187,19 +189,20 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
 #pragma unroll
     for (int e = 0; e < 16; ++e) bmax = fmaxf(bmax, s[e]);
     bmax = xor32_max(bmax);
-    const float m_new = fmaxf(m_run[qb], bmax * sc2);
-    const float m_ref = MASK ? (m_new == -INFINITY ? 0.f : m_new) : m_new;   // (no visible key so far)
+    const float m_new = fmaxf(m_run[qb], bmax);
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // (no key with a score above -inf so far)
     float psum = 0.f, asum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const float t = fmaf(s[e], sc2, -m_ref);
+      // (not one fused s sc2 - m_ref sc2: the rounding of the second product is no power of two's worth for scores of millions)
+      const float t = (s[e] - m_ref) * sc2;
       const float p = __builtin_amdgcn_exp2f(t);
       psum += p;
-      if constexpr (ENT) asum = fmaf(p, MASK ? fmaxf(t, T_MIN) : t, asum);
+      if constexpr (ENT) asum = fmaf(p, fmaxf(t, T_MIN), asum);
       pf[e >> 3][e & 7] = (bf16)p;
     }
     psum = xor32_sum(psum);
-    const float dl = fmaxf(m_run[qb] - m_ref, T_MIN), corr = __builtin_amdgcn_exp2f(dl);
+    const float dl = fmaxf((m_run[qb] - m_ref) * sc2, T_MIN), corr = __builtin_amdgcn_exp2f(dl);
     if constexpr (ENT) a_run[qb] = fmaf(corr, fmaf(dl, l_run[qb], a_run[qb]), xor32_sum(asum));
     l_run[qb] = fmaf(corr, l_run[qb], psum);
     m_run[qb] = m_new;
@@ -285,7 +288,7 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
   };
   float f_me[NQB];
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) f_me[qb] = __builtin_amdgcn_exp2f(fmaxf(m_run[qb] - top(cl + 32 * qb), T_MIN));
+  for (int qb = 0; qb < NQB; ++qb) f_me[qb] = __builtin_amdgcn_exp2f(fmaxf((m_run[qb] - top(cl + 32 * qb)) * sc2, T_MIN));
   // every wave lays its rescaled partial O^T down in its own slab: one barrier, no read-modify-write rounds
   float* slab = s_o + (size_t)wave * DH * OLD;
 #pragma unroll
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
     float lstar = 0.f, astar = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float dl = fmaxf(s_m[w][c] - mstar, T_MIN), f = __builtin_amdgcn_exp2f(dl);
+      const float dl = fmaxf((s_m[w][c] - mstar) * sc2, T_MIN), f = __builtin_amdgcn_exp2f(dl);
       lstar = fmaf(f, s_l[w][c], lstar);
       if constexpr (ENT) astar = fmaf(f, fmaf(dl, s_l[w][c], s_a[w][c]), astar);
     }
@@ -347,6 +350,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnSplit sp, int n_hea
                                                          int out_tiled) {
   const int Me = eff_rows(M, m_dev);
   const int d8n = dh >> 3;
+  const float sc2 = rsqrtf((float)dh) * LOG2E;
   const long total = (long)Me * n_heads * d8n;
   for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
     const int d8 = (int)(idx % d8n);
@@ -374,7 +378,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnSplit sp, int n_hea
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (s >= sp.n || t[s][1] == 0.f) continue;
-      const float dl = fmaxf(t[s][0] - mstar, T_MIN), f = __builtin_amdgcn_exp2f(dl);
+      const float dl = fmaxf((t[s][0] - mstar) * sc2, T_MIN), f = __builtin_amdgcn_exp2f(dl);
       lstar += f * t[s][1];
       astar += f * (t[s][2] + dl * t[s][1]);
 #pragma unroll

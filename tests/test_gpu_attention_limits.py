@@ -1,6 +1,6 @@
-"""NaN scores in the cached attention: a NaN key shows in every row that sees it and in no other sample.  Over the forms of the
-bf16 kernel (appending, without append, keys split over workgroups, passes of rows) and the fp32 one, with the key in a block
-that every row sees whole and in the masked one."""
+"""NaN and infinite scores in the cached attention: a NaN key shows in every row that sees it, a key whose score is -inf has no
+weight, and neither touches another sample.  Over the forms of the bf16 kernel (appending, without append, keys split over
+workgroups, passes of rows) and the fp32 one, with the key in a block that every row sees whole and in the masked one."""
 import numpy as np
 import pytest
 
@@ -54,3 +54,28 @@ def test_nan_key_shows_in_every_row_that_sees_it(form, tail):
     assert np.isnan(z[:n0]).all()
     assert rel_inf(z[n0:], z0[n0:]) < 1e-2                 # (many rows: residual products of several K slices meet by atomics)
     assert np.isfinite(ha[n0:]).all()
+
+
+@pytest.mark.parametrize("form", ["append", "append-64-wide", "passes"])
+@pytest.mark.parametrize("keys", [slice(5, 6), slice(0, 32), slice(33, 36)])
+def test_key_of_score_minus_infinity_has_no_weight(form, keys):
+    """Queries of ones (zero weights, unit bias) against keys of -3e38, whose products sum to -inf in fp32: rows and row
+    entropies of the first layer are those of a finite score far below every other one.  (Scores of 1e31 are also where a
+    reference and a score that are rounded apart would be powers of two apart.)"""
+    make, n0 = FORMS[form]
+    out = []
+    for low in (-3e38, -1e30):
+        case = build_case(make(), seed=32)
+        t = case.rc.target
+        q = t.n_heads * t.d_head
+        case.W["target.L0.wqkv"][:, :q] = 0.0
+        case.W["target.L0.bqkv"][:q] = 1.0
+        k, v = case.cache_t[0]
+        k = k.copy()
+        k[0, :, keys, :] = low
+        case.cache_t[0] = (k, v)
+        out.append(_forward(case, n0))
+    (z, ha), (zf, haf) = out
+    assert np.isfinite(zf).all() and np.isfinite(haf).all()
+    assert rel_inf(z, zf) < 1e-2
+    assert np.abs(ha - haf).max() < 1e-4
