@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
     float psum = 0.f, asum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      // (not one fused s sc2 - m_ref sc2: the rounding of the second product is no power of two's worth for scores of millions)
+      // (not one fused s sc2 - m_ref sc2: the second product is rounded, for scores of 1e9 and more by whole powers of two)
       const float t = (s[e] - m_ref) * sc2;
       const float p = __builtin_amdgcn_exp2f(t);
       psum += p;
@@ -238,19 +238,26 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
       load_v(kb_lo + wave);
     }
   }
-  for (int kb = kb_lo + wave; kb < kb_hi; kb += 4) {
+  // first the blocks of which every row sees every key, then the masked ones: with both softmaxes in one loop behind a branch
+  // the next block's K and V did not fit beside them (36-168 bytes of scratch a lane).  Forward of 256 rows at 768 keys, 8 rotary
+  // layers of 16 heads of 64: 2.84 -> 1.65 ms; prefill of 8 x 768 rows, 40 layers of 40 heads of 128: 136.3 -> 133.9 ms.
+  auto block = [&](int kb, auto masked) {
     const bool more = kb + 4 < kb_hi;
-    const bool whole = APPEND || kb * 32 + 31 <= p0;       // every row sees every key of the block
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       const f32x16 s = score(qb);
       if (qb == NQB - 1 && more) load_k(kb + 4);
       bf16x8 pf[2];
-      if (whole) softmax(kb, qb, s, pf, std::false_type{});
-      else softmax(kb, qb, s, pf, std::true_type{});
+      softmax(kb, qb, s, pf, masked);
       product(qb, pf);
     }
     if (more) load_v(kb + 4);
+  };
+  const int kb_whole = APPEND ? kb_hi : min(kb_hi, (p0 + 1) >> 5);
+  int kb = kb_lo + wave;
+  for (; kb < kb_whole; kb += 4) block(kb, std::false_type{});
+  if constexpr (!APPEND) {
+    for (; kb < kb_hi; kb += 4) block(kb, std::true_type{});
   }
   if constexpr (APPEND) {
     __syncthreads();
