@@ -1427,20 +1427,24 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void embed_norm_kernel(const
   const int r = blockIdx.x;
   const int n4 = d >> 2, nw = blockDim.x >> 6;
   // (everything but the position row and an id's row is requested before the first wait; an absent vector is a re-read of
-  // the row's place in h, which holds d floats whatever they are)
+  // the row's place in h, which holds d floats whatever they are; fp32 weights of two pieces a thread, 128 registers, are
+  // requested piece by piece: they do not fit beside the rest)
+  constexpr bool EARLY = sizeof(T) == 2 || VPT == 1;
   const float* xz = h + (size_t)r * d;
   const int id0 = cond_id ? cond_id[r] : -1;
   const int pos0 = pos_table ? row_pos[r] : 0;
   float xr[16];                                            // D <= 16 (checked on the host)
 #pragma unroll
   for (int k = 0; k < 16; ++k) xr[k] = x[(size_t)r * ldx + (k < D ? k : 0)];
-  f32x4 v[VPT], gv[VPT], bv[VPT], w[VPT][16];
+  f32x4 v[VPT], gv[VPT], bv[VPT], w[EARLY ? VPT : 1][16];
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
     const int c4 = threadIdx.x + i * blockDim.x;
     const int cc = (c4 < n4 ? c4 : 0) * 4;
+    if constexpr (EARLY) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) w[i][k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * d + cc);
+      for (int k = 0; k < 16; ++k) w[i][k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * d + cc);
+    }
     v[i] = *(const f32x4*)((b_in ? b_in : xz) + cc);
     gv[i] = *(const f32x4*)((g ? g : xz) + cc);
     bv[i] = *(const f32x4*)((b ? b : xz) + cc);
@@ -1455,12 +1459,16 @@ __global__ __launch_bounds__(VPT == 1 ? 512 : 1024) void embed_norm_kernel(const
     if (id0 >= 0) {
       v[i] = load4f<T>(cond_table + (size_t)id0 * d + cc);
     } else {
+      if constexpr (!EARLY) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) w[0][k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * d + cc);
+      }
       if (b_in == nullptr) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (pos_table) v[i] += load4f<T>(pos_table + (size_t)pos0 * d + cc);
 #pragma unroll
       for (int k = 0; k < 16; ++k)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[i][e] = k < D ? fmaf(w[i][k][e], xr[k], v[i][e]) : v[i][e];
+        for (int e = 0; e < 4; ++e) v[i][e] = k < D ? fmaf(w[EARLY ? i : 0][k][e], xr[k], v[i][e]) : v[i][e];
     }
     if (c4 < n4) {
       *(f32x4*)(h + (size_t)r * d + cc) = v[i];

@@ -36,9 +36,11 @@ def kernels(lib):
     return _kernels(lib.LIB_PATH)
 
 
-@pytest.mark.parametrize("name,least", [("attn_bf16_kernel", 36), ("attn_merge_kernel", 1), ("attn_f32_wide_kernel", 3)])
-def test_attention_keeps_its_blocks_in_registers(kernels, name, least):
-    """Every instance: the next block's K and V are in flight through the softmax, and fit beside it."""
+@pytest.mark.parametrize("name,least", [("attn_bf16_kernel", 36), ("attn_merge_kernel", 1), ("attn_f32_wide_kernel", 3),
+                                        ("embed_norm_kernel", 4), ("", 300)])
+def test_kernels_keep_what_is_in_flight_in_registers(kernels, name, least):
+    """Every instance: what a kernel requests ahead (attention: the next block's K and V through the softmax) fits beside what it
+    works on."""
     of = {k: v for k, v in kernels.items() if name in k}
     assert len(of) >= least
     assert {k: v[".private_segment_fixed_size"] for k, v in of.items() if v[".private_segment_fixed_size"]} == {}
