@@ -114,6 +114,23 @@ int spec_round_init(const fard_round_cfg* cfg, const fard_tensor* weights, int32
                     void* hip_stream, fard_ctx** out);
 int spec_round_destroy(fard_ctx* ctx);
 
+/* Resident launches: a head decode of few rows (bf16; widths 1024, 1280 and 1536, up to 64, 48 and 16 rows) takes all blocks of
+ * a sampler step in one launch whose workgroups wait for one another, so all of them have to be on the GPU at once.  The row
+ * limits leave room for `launches` such launches side by side: 4 by default, or GPU_MAX_HW_QUEUES if that is more, which is
+ * what the streams of one process can have in flight.  A context whose stream has a compute-unit mask or a priority of its
+ * own never uses them.  What a context cannot see is other PROCESSES that decode on the same GPU: give it 4 times their
+ * number here, or 0 to use a launch per product (the same results up to rounding).
+ * Where the count is wrong all the same, a launch gives up after give_up_s (10 s by default): its rows are NaN, and the next
+ * call on the context, or the spec_kv_lengths that waits for it, returns FARD_EHIP once; the context goes on with a launch per
+ * product.  Caches and tokens written since then hold NaN: restart those samples.
+ *   launches >= 0: the new count (more rows than init reserved are never taken); < 0: as it is
+ *   give_up_s > 0: the new limit, at most 20 s; 0 (tests): 1 ms, and launches lack a workgroup, so that they give up;
+ *   < 0: as it is
+ * Drops the graphs of spec_graph_enable, which record themselves again. */
+int spec_resident(fard_ctx* ctx, int32_t launches, float give_up_s);
+/* How a head decode of n rows runs: 16-column tiles (1 or 2) of a resident launch's workgroup, 0: a launch per product. */
+int spec_resident_tiles(fard_ctx* ctx, int32_t n);
+
 /* Sets the cached length of every sample of model `which` (FARD_TARGET / FARD_DRAFT).
  * cache_len: HOST int32 [B] or NULL (all 0).  Does not touch cache contents. */
 int spec_kv_reset(fard_ctx* ctx, int32_t which, const int32_t* cache_len, int32_t B);

@@ -53,6 +53,8 @@ _vp, _i32, _f32 = C.c_void_p, C.c_int32, C.c_float
 _SIGS = {
     "spec_round_init": [C.POINTER(RoundCfg), C.POINTER(Tensor), _i32, _vp, C.POINTER(_vp)],
     "spec_round_destroy": [_vp],
+    "spec_resident": [_vp, _i32, _f32],
+    "spec_resident_tiles": [_vp, _i32],
     "spec_kv_reset": [_vp, _i32, _vp, _i32],
     "spec_kv_restore": [_vp, _i32, _vp, _i32, _i32],
     "spec_kv_load": [_vp, _i32, _i32, _vp, _vp, _i32, _i32],
@@ -216,6 +218,16 @@ class Context:
         self.torch.cuda.synchronize(self.dev)
 
     # ------------------------------------------------------------------ C ABI, one method per entry point
+    def spec_resident(self, launches=-1, give_up_s=-1.0):
+        """Resident launches that may be on the GPU at once, over all processes (0: a launch per product); seconds a launch waits."""
+        self._chk(lib.spec_resident(self.h, int(launches), float(give_up_s)))
+
+    def spec_resident_tiles(self, n):
+        tiles = lib.spec_resident_tiles(self.h, int(n))
+        if tiles < 0:
+            self._chk(tiles)
+        return tiles
+
     def spec_kv_reset(self, which, cache_len=None, B=None):
         if cache_len is None:
             self._chk(lib.spec_kv_reset(self.h, which, None, self.rc.max_batch if B is None else B))

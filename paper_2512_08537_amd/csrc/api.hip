@@ -258,10 +258,16 @@ struct fard_ctx {
   // workspace
   float *h = nullptr, *x_in = nullptr, *ent_heads = nullptr, *h_row = nullptr;
   void* hv = nullptr;            // head: bf16 rows h (1 + scale of the next block), written by a block's second GEMM
-  void* xch = nullptr;           // head_chain.hip: exchange words of up to xch_rows rows, and the decode count in their tags
-  int xch_rows = 0;
-  unsigned* epoch = nullptr;
-  int compute_units = 0, queues = 4;
+  // head_chain.hip: exchange words of up to xch_rows rows (0: the path is not for this context), of which chain_rows are in use;
+  // the decode count in their tags and the give-up word (device), the latter also in host memory
+  void* xch = nullptr;
+  int xch_rows = 0, chain_rows = 0;
+  HeadChainState* chain_state = nullptr;
+  int* chain_gave_up = nullptr;
+  int compute_units = 0, launches = 4;
+  bool chain_short = false;                // (tests of the give-up)
+  unsigned chain_limit = 0;
+  unsigned clock_khz = 100000;             // of the counter that the waits are measured with
   float* hmom = nullptr;         // head: [rows][w / 16] (mean, centred squares) of h per 16-column tile
   void *u = nullptr, *qkv = nullptr, *ao = nullptr, *ff = nullptr, *z = nullptr, *ztmp = nullptr;
   RowMaps maps{};
@@ -782,6 +788,30 @@ constexpr int ATTN_MAX_SPLIT = 8;        // attention workgroups per (sample, kv
 
 int cap_nq(const fard_ctx* c, int which);
 
+constexpr unsigned CHAIN_GIVE_UP_S = 10;
+
+// The most rows, up to `most`, that a sampler step of the head takes in one resident launch.
+int chain_rows_of(const fard_ctx* c, int most) {
+  const fard_head_cfg& h = c->cfg.head;
+  while (most > 0 && head_chain_tiles(most, h.width, h.n_blocks, h.n_steps, c->compute_units, c->launches) == 0) most -= 1;
+  return most;
+}
+
+// Whether the resident launches' count of workgroups and queues holds on a stream: it may use every compute unit, and its
+// launches come through the process's ordinary hardware queues (a stream with a mask or of another priority has one beside them).
+bool stream_has_whole_chip(hipStream_t s, int compute_units) {
+  int priority = 0;
+  uint32_t mask[32] = {};
+  if (hipStreamGetPriority(s, &priority) != hipSuccess || priority != 0 ||
+      hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int units = 0;
+  for (uint32_t m : mask) units += __builtin_popcount(m);
+  return units >= compute_units;
+}
+
 int alloc_workspace(fard_ctx* c) {
   const fard_round_cfg& g = c->cfg;
   const int M = c->m_max, MR = c->m_rows;
@@ -827,18 +857,25 @@ int alloc_workspace(fard_ctx* c) {
   if ((rc = dalloc_bytes(c, &c->hv, (size_t)((M + 15) / 16 * 16) * w * c->esz))) return rc;
   if ((rc = dalloc<float>(c, &c->hmom, (size_t)(w / 16 + 1) * M * 2))) return rc;
   if (c->head.table != nullptr) {
-    int dev = 0;
+    int dev = 0, khz = 0;
     HIPCHK(c, hipGetDevice(&dev));
     HIPCHK(c, hipDeviceGetAttribute(&c->compute_units, hipDeviceAttributeMultiprocessorCount, dev));
-    if (const char* q = getenv("GPU_MAX_HW_QUEUES")) c->queues = std::max(c->queues, atoi(q));
-    c->xch_rows = M;
-    while (c->xch_rows > 0 && head_chain_tiles(c->xch_rows, w, g.head.n_blocks, g.head.n_steps, c->compute_units, c->queues) == 0) c->xch_rows -= 1;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0) c->clock_khz = (unsigned)khz;
+    if (const char* q = getenv("GPU_MAX_HW_QUEUES")) c->launches = std::max(c->launches, atoi(q));
+    c->xch_rows = stream_has_whole_chip(c->stream, c->compute_units) ? chain_rows_of(c, M) : 0;
+    c->chain_rows = c->xch_rows;
+    c->chain_limit = CHAIN_GIVE_UP_S * 1000u * c->clock_khz;
     if (c->xch_rows > 0) {
       const size_t words = head_chain_bytes(c->xch_rows, w) / 4;
       if ((rc = dalloc_bytes(c, &c->xch, words * 4))) return rc;
-      if ((rc = dalloc<unsigned>(c, &c->epoch, 1))) return rc;
+      if ((rc = dalloc<HeadChainState>(c, &c->chain_state, 1))) return rc;
       HIPCHK(c, launch_fill_f32(c->stream, (float*)c->xch, 0.f, words));
-      HIPCHK(c, launch_fill_i32(c->stream, (int*)c->epoch, 0, 1));
+      HIPCHK(c, hipHostMalloc((void**)&c->chain_gave_up, sizeof(int), hipHostMallocMapped));
+      *c->chain_gave_up = 0;
+      HeadChainState st{};
+      HIPCHK(c, hipHostGetDevicePointer((void**)&st.host_gave_up, c->chain_gave_up, 0));
+      HIPCHK(c, hipMemcpyAsync(c->chain_state, &st, sizeof(st), hipMemcpyHostToDevice, c->stream));
+      HIPCHK(c, hipStreamSynchronize(c->stream));          // (the host struct goes away)
     }
   }
   if ((rc = dalloc<int>(c, &c->alive, 2 * (size_t)g.max_batch))) return rc;   // (before / after a draft step, taking turns)
@@ -1166,10 +1203,10 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
   const int w = hc.width, D = hc.d_latent, Nb = hc.n_blocks, S = hc.n_steps;
   HIPCHK(c, gemm(c, z, hc.d_cond, hw.c_w, hw.c_b, c->cz, w, n, w, hc.d_cond, n_dev, EPI_STORE_F32, ACT_NONE));
   // few rows: all blocks of a sampler step in one launch, the modulated norms folded around every block's first product
-  const bool chain = n <= c->xch_rows;
+  const bool chain = n <= c->chain_rows;
   { Bracket br(c, CLS_OTHER);
     HIPCHK(c, launch_head_prep(s, c->bf16, eps, emap, hc.temperature, D, hw.in_w, hw.in_b, c->cz, hw.temb, S, c->hh, c->sc,
-                               c->xt, w, n, n_dev, chain ? c->epoch : nullptr, len, row_pos)); }
+                               c->xt, w, n, n_dev, chain ? &c->chain_state->decodes : nullptr, len, row_pos)); }
   // From the second block of a step on the modulated norm has no launch of its own when the rows are few (the launch
   // is then the cost; measured: a gain up to 64 rows, none above): the gate-residual GEMM of block j - 1 leaves
   // v = bf16(h (1 + scale_j)) and the tile moments of h, and block j's first GEMM multiplies v and applies mean, rstd,
@@ -1191,10 +1228,11 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
       a.hh = c->hh;
       a.blocks = hw.table; a.n_blocks = Nb;
       a.mod = modk; a.ldm = hw.mod_n; a.fold_base = hw.fold_base;
-      a.xch = c->xch; a.epoch = c->epoch; a.tag_base = 1 + 2 * Nb * k;
+      a.xch = c->xch; a.tag_base = 1 + 2 * Nb * k;
+      a.state = c->chain_state; a.limit = c->chain_limit;
       a.n = n; a.n_dev = n_dev;
       Bracket br(c, CLS_GEMM_NARROW, 4.0 * Nb * n * (double)w * w, 2.0 * Nb * ((double)w * w * 2 + (double)n * w * 2));
-      HIPCHK(c, launch_head_chain(s, a, w, head_chain_tiles(n, w, Nb, S, c->compute_units, c->queues)));
+      HIPCHK(c, launch_head_chain(s, a, w, head_chain_tiles(n, w, Nb, S, c->compute_units, c->launches), c->chain_short));
     }
     for (int j = 0; j < Nb && !chain; ++j) {
       const float* mj = modk + (size_t)3 * w * j;
@@ -1254,7 +1292,27 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
   return FARD_OK;
 }
 
-int check_ctx(fard_ctx* c) { return c ? FARD_OK : FARD_EINVAL; }
+// A resident head launch has given up (head_chain.hip): the rows of every decode since then are NaN.  Reported once; the
+// context goes on with a launch per product.
+int chain_gave_up(fard_ctx* c) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (c->stream != nullptr) (void)hipStreamIsCapturing(c->stream, &cap);   // (the default stream cannot be captured)
+  if (cap == hipStreamCaptureStatusNone) {
+    HIPCHK(c, hipStreamSynchronize(c->stream));            // (launches behind it mark the word again)
+    HIPCHK(c, launch_fill_i32(c->stream, (int*)&c->chain_state->gave_up, 0, 1));
+  }
+  __atomic_store_n(c->chain_gave_up, 0, __ATOMIC_RELAXED);
+  c->chain_rows = 0;
+  c->rgraph.drop();
+  c->ggraph.drop();
+  return fail(c, FARD_EHIP, "a head decode waited too long for its own workgroups (is the GPU shared by other processes? see "
+                            "spec_resident): its rows and all that was computed from them are NaN; later decodes use a launch per product");
+}
+int enter(fard_ctx* c) {
+  if (!c) return FARD_EINVAL;
+  if (c->chain_gave_up != nullptr && __atomic_load_n(c->chain_gave_up, __ATOMIC_RELAXED) != 0) return chain_gave_up(c);
+  return FARD_OK;
+}
 
 }  // namespace
 
@@ -1274,6 +1332,7 @@ int spec_round_init(const fard_round_cfg* cfg, const fard_tensor* weights, int32
     // keep the message reachable: the caller gets no context on failure, so print it
     fprintf(stderr, "spec_round_init: %s\n", c->err.c_str());
     for (void* p : c->allocs) (void)hipFree(p);
+    if (c->chain_gave_up) (void)hipHostFree(c->chain_gave_up);
     delete c;
     return code;
   };
@@ -1326,8 +1385,30 @@ int spec_round_destroy(fard_ctx* c) {
   if (c->gemm_tmp) (void)hipFree(c->gemm_tmp);
   if (c->loss_tmp) (void)hipFree(c->loss_tmp);
   for (void* p : c->allocs) (void)hipFree(p);
+  if (c->chain_gave_up) (void)hipHostFree(c->chain_gave_up);
   delete c;
   return FARD_OK;
+}
+
+int spec_resident(fard_ctx* c, int32_t launches, float give_up_s) {
+  if (int e = enter(c)) return e;
+  if (!(give_up_s <= 20.f)) return fail(c, FARD_EINVAL, "give_up_s beyond 20");
+  if (launches >= 0) c->launches = launches;
+  c->chain_rows = chain_rows_of(c, c->xch_rows);
+  if (give_up_s >= 0.f) {
+    c->chain_short = give_up_s == 0.f;
+    c->chain_limit = (unsigned)((c->chain_short ? 1e-3 : (double)give_up_s) * 1000.0 * c->clock_khz);
+  }
+  c->rgraph.drop();                                        // (they hold the launches of before)
+  c->ggraph.drop();
+  return FARD_OK;
+}
+
+int spec_resident_tiles(fard_ctx* c, int32_t n) {
+  if (int e = enter(c)) return e;
+  if (n < 1 || n > c->chain_rows) return 0;
+  const fard_head_cfg& h = c->cfg.head;
+  return head_chain_tiles(n, h.width, h.n_blocks, h.n_steps, c->compute_units, c->launches);
 }
 
 const char* spec_last_error(const fard_ctx* c) { return c ? c->err.c_str() : "null context"; }
@@ -1335,7 +1416,7 @@ const char* spec_last_error(const fard_ctx* c) { return c ? c->err.c_str() : "nu
 float entropy_threshold(float mean_H, float std_H) { return 0.3f * mean_H - 0.1f * std_H; }
 
 int spec_kv_reset(fard_ctx* c, int32_t which, const int32_t* cache_len, int32_t B) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (which != FARD_TARGET && which != FARD_DRAFT) return fail(c, FARD_EINVAL, "which");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   Model& m = c->mdl[which];
@@ -1356,7 +1437,7 @@ int spec_kv_reset(fard_ctx* c, int32_t which, const int32_t* cache_len, int32_t 
 }
 
 int spec_kv_restore(fard_ctx* c, int32_t which, const int32_t* cache_len_dev, int32_t B, int32_t len_hi) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (which != FARD_TARGET && which != FARD_DRAFT) return fail(c, FARD_EINVAL, "which");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (len_hi < 0 || len_hi > c->cfg.max_ctx) return fail(c, FARD_ECAPACITY, "len_hi outside [0, max_ctx]");
@@ -1372,7 +1453,7 @@ int spec_kv_restore(fard_ctx* c, int32_t which, const int32_t* cache_len_dev, in
 }
 
 int spec_kv_load(fard_ctx* c, int32_t which, int32_t layer, const void* k, const void* v, int32_t B, int32_t n) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (which != FARD_TARGET && which != FARD_DRAFT) return fail(c, FARD_EINVAL, "which");
   Model& m = c->mdl[which];
   if (layer < 0 || layer >= m.c.n_layers) return fail(c, FARD_EINVAL, "layer");
@@ -1384,7 +1465,7 @@ int spec_kv_load(fard_ctx* c, int32_t which, int32_t layer, const void* k, const
 }
 
 int spec_kv_lengths(fard_ctx* c, int32_t which, int32_t* out_host, int32_t B) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if ((which != FARD_TARGET && which != FARD_DRAFT) || !out_host) return fail(c, FARD_EINVAL, "which/out");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   // all max_batch lengths come back: the host's upper bound (which a round can only raise by K + 1, whatever was
@@ -1393,6 +1474,7 @@ int spec_kv_lengths(fard_ctx* c, int32_t which, int32_t* out_host, int32_t B) {
   std::vector<int32_t> all((size_t)c->cfg.max_batch);
   HIPCHK(c, hipMemcpyAsync(all.data(), m.len, all.size() * 4, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  if (int e = enter(c)) return e;          // (what the stream did up to here)
   int hi = 0;
   for (int32_t v : all) hi = std::max(hi, (int)v);
   if (m.written == 0) m.len_hi = hi;       // (between a draft / verify and its commit the bound covers uncommitted rows)
@@ -1401,7 +1483,7 @@ int spec_kv_lengths(fard_ctx* c, int32_t which, int32_t* out_host, int32_t B) {
 }
 
 int spec_kv_commit(fard_ctx* c, int32_t which, const int32_t* n_accept, int32_t B) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (!n_accept) return fail(c, FARD_EINVAL, "n_accept");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (B == 0) return FARD_OK;
@@ -1423,7 +1505,7 @@ int spec_kv_commit(fard_ctx* c, int32_t which, const int32_t* n_accept, int32_t 
 
 int spec_forward(fard_ctx* c, int32_t which, const float* x_in, const int32_t* cond_id, const int32_t* n_q, int32_t nq_max,
                  int32_t B, int32_t M, int32_t commit, void* z_out, float* shallow_out, float* h_attn_out) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (which != FARD_TARGET && which != FARD_DRAFT) return fail(c, FARD_EINVAL, "which");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (M < 0 || M > c->m_rows) return fail(c, FARD_ECAPACITY, "M beyond the workspace rows");
@@ -1478,7 +1560,7 @@ int spec_forward(fard_ctx* c, int32_t which, const float* x_in, const int32_t* c
 
 int spec_prefill(fard_ctx* c, int32_t which, const float* x, const int32_t* first_id, const int32_t* n, int32_t n_max,
                  int32_t B, void* z_last) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (which != FARD_TARGET && which != FARD_DRAFT) return fail(c, FARD_EINVAL, "which");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (n_max < 0) return fail(c, FARD_EINVAL, "n_max < 0");
@@ -1533,7 +1615,7 @@ static int loss_scratch(fard_ctx* c, size_t bytes) {
 
 int spec_entropy_loss(fard_ctx* c, const void* q, const void* k, int32_t B, int32_t H, int32_t H_kv, int32_t R, int32_t d_head,
                       float* loss, float* h_rows, float* dq, float* dk) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (!c->bf16) return fail(c, FARD_ESTATE, "spec_entropy_loss needs a bf16 context");
   if (B < 1 || H < 1 || H_kv < 1 || R < 1 || H % H_kv != 0) return fail(c, FARD_ESHAPE, "B, H, H_kv, R >= 1 and H % H_kv == 0 required");
   if (d_head != 32 && d_head != 64 && d_head != 128) return fail(c, FARD_ESHAPE, "d_head must be 32, 64 or 128");
@@ -1551,7 +1633,7 @@ int spec_entropy_loss(fard_ctx* c, const void* q, const void* k, int32_t B, int3
 }
 
 int spec_smooth_l1(fard_ctx* c, const void* pred, const void* target, int64_t n, float beta, float* loss, float* dpred) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (n < 1) return fail(c, FARD_ESHAPE, "n >= 1 required");
   if (!(beta > 0.f)) return fail(c, FARD_EINVAL, "beta > 0 required");
   if (!pred || !target || !loss) return fail(c, FARD_EINVAL, "null argument");
@@ -1565,7 +1647,7 @@ int spec_smooth_l1(fard_ctx* c, const void* pred, const void* target, int64_t n,
 
 int entropy_prefilter(fard_ctx* c, const void* feat, int32_t B, int32_t K, int32_t L, float tau, float* H, uint8_t* keep,
                       int32_t* n_keep, int32_t* surv_idx, int32_t* n_surv) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (B < 0 || K < 0 || L < 1) return fail(c, FARD_ESHAPE, "B, K >= 0 and L >= 1 required");
   if (!n_surv) return fail(c, FARD_EINVAL, "null n_surv");
   if ((long)B * K == 0) {
@@ -1624,7 +1706,7 @@ int entropy_prefilter_static(const void* feat, int32_t dtype, int32_t B, int32_t
 }
 
 int diffhead_decode(fard_ctx* c, const void* z, const int32_t* n_rows, int32_t n_max, const float* eps, float* mu, float* x) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (n_max < 0 || n_max > c->m_max) return fail(c, FARD_ECAPACITY, "n_max > max_batch*(K+1)");
   if (n_max == 0) return FARD_OK;
   if (!z || !eps || !mu || !x) return fail(c, FARD_EINVAL, "null argument");
@@ -1634,7 +1716,7 @@ int diffhead_decode(fard_ctx* c, const void* z, const int32_t* n_rows, int32_t n
 int spec_accept(fard_ctx* c, const float* x_draft, const float* mu_p, const float* mu_q, const float* r, const int32_t* n_keep,
                 float log_sigma_factor, float sigma_p, float sigma_q, int32_t B, int32_t* n_accept, float* log_ratio,
                 uint8_t* acc) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (B < 0) return fail(c, FARD_ESHAPE, "B < 0");
   if (B == 0) return FARD_OK;
   if (!x_draft || !mu_p || !mu_q || !r || !n_keep || !n_accept || !log_ratio || !acc) return fail(c, FARD_EINVAL, "null argument");
@@ -1721,7 +1803,7 @@ static int draft_checks(fard_ctx* c, const float* x_first, const int32_t* id, co
 
 int spec_draft(fard_ctx* c, const float* x_pending, const int32_t* pending_id, const float* eps, float tau, int32_t B,
                float* H, uint8_t* keep, int32_t* n_keep, float* x_draft, float* mu_q) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (B == 0) return FARD_OK;
   int rc = draft_checks(c, x_pending, pending_id, eps, B, H, keep, n_keep, x_draft, mu_q, c->cfg.K);
   if (rc) return rc;
@@ -1739,7 +1821,7 @@ int spec_draft(fard_ctx* c, const float* x_pending, const int32_t* pending_id, c
 
 int spec_draft_step(fard_ctx* c, int32_t i, const float* x_prev, const int32_t* prev_id, const float* eps, float tau, int32_t B,
                     float* H, uint8_t* keep, int32_t* n_keep, float* x_draft, float* mu_q) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (i < 0 || i >= c->cfg.K) return fail(c, FARD_EINVAL, "step index outside [0, K)");
   if (B == 0) return FARD_OK;
   const int K = c->cfg.K, D = c->mdl[FARD_DRAFT].c.d_latent;
@@ -1756,7 +1838,7 @@ int spec_draft_step(fard_ctx* c, int32_t i, const float* x_prev, const int32_t* 
 int spec_verify(fard_ctx* c, const float* x_pending, const int32_t* pending_id, const float* x_draft, const float* mu_q,
                 const int32_t* n_keep, const float* r, const float* eps, float log_sigma_factor, float sigma_p, float sigma_q,
                 int32_t B, int32_t* n_accept, float* log_ratio, float* mu_p, void* z_p) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (B == 0) return FARD_OK;
   if (!x_pending || !x_draft || !mu_q || !n_keep || !r || !eps || !n_accept || !log_ratio || !mu_p)
@@ -1824,7 +1906,7 @@ static int round_capacity(fard_ctx* c) {
 }
 
 int spec_graph_enable(fard_ctx* c, int32_t on) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (on && c->stream == nullptr) return fail(c, FARD_ESTATE, "rounds on the default stream cannot be captured");
   c->rgraph.drop();
   c->ggraph.drop();
@@ -1835,7 +1917,7 @@ int spec_graph_enable(fard_ctx* c, int32_t on) {
 int spec_round(fard_ctx* c, const float* x_pending, const int32_t* pending_id, const float* eps, const float* r, float tau,
                float log_sigma_factor, float sigma_p, float sigma_q, int32_t B, float* H, uint8_t* keep, int32_t* n_keep,
                float* x_draft, float* mu_q, int32_t* n_accept, float* log_ratio, float* mu_p) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   RoundGraph& g = c->rgraph;
   auto eager = [&]() {
     return round_eager(c, x_pending, pending_id, eps, r, tau, log_sigma_factor, sigma_p, sigma_q, B, H, keep, n_keep, x_draft,
@@ -1906,7 +1988,7 @@ int spec_round(fard_ctx* c, const float* x_pending, const int32_t* pending_id, c
 int spec_resample(fard_ctx* c, const float* mu_p, const float* mu_q, const float* eps, const int32_t* n_accept,
                   const int32_t* n_keep, const float* eps_res, const float* u_res, float log_sigma_factor, float sigma_p,
                   float sigma_q, int32_t B, int32_t J, float* x_next, int32_t* tries) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (J < 1) return fail(c, FARD_EINVAL, "J >= 1 required");
   if (!(sigma_p > 0.f) || !(sigma_q > 0.f)) return fail(c, FARD_EINVAL, "sigma_p, sigma_q > 0 required");
@@ -2011,7 +2093,7 @@ int spec_generate(fard_ctx* c, const float* x_first, const int32_t* first_id, co
                   const float* eps_res, const float* u_res, float tau, float log_sigma_factor, float sigma_p, float sigma_q,
                   int32_t B, int32_t R, int32_t J, float* tokens, int32_t* n_tokens, float* H, int32_t* n_keep,
                   int32_t* n_accept, int32_t* tries) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (R < 0 || J < 1) return fail(c, FARD_EINVAL, "R >= 0 and J >= 1 required");
   if (B == 0 || R == 0) return FARD_OK;
@@ -2053,7 +2135,7 @@ int spec_generate(fard_ctx* c, const float* x_first, const int32_t* first_id, co
 }
 
 int spec_gemm(fard_ctx* c, const void* A, const void* W, const float* bias, int32_t M, int32_t K, int32_t N, int32_t act, void* out) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (M < 0 || K < 1 || N < 1) return fail(c, FARD_ESHAPE, "M >= 0, K, N >= 1 required");
   if (M == 0) return FARD_OK;
   if (!A || !W || !out) return fail(c, FARD_EINVAL, "null argument");
@@ -2086,7 +2168,7 @@ int spec_gemm_tile_variant(int32_t M, int32_t K, int32_t N, int32_t epi, int32_t
 
 int spec_gemm_tile(fard_ctx* c, const void* A, const void* W, const float* bias, const float* gate, int32_t M, int32_t K, int32_t N,
                    int32_t epi, int32_t act, int32_t variant, void* out) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (!c->bf16) return fail(c, FARD_EINVAL, "spec_gemm_tile needs a bf16 context");
   if (M < 0 || K < 1 || N < 1) return fail(c, FARD_ESHAPE, "M >= 0, K, N >= 1 required");
   if (M == 0) return FARD_OK;
@@ -2116,7 +2198,7 @@ int spec_gemm_tile(fard_ctx* c, const void* A, const void* W, const float* bias,
 
 int spec_gemm_narrow(fard_ctx* c, const void* A, const void* W, const float* bias, const float* gate, int32_t M,
                      int32_t K, int32_t N, int32_t epi, int32_t act, void* out, void* out_bf16) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (!c->bf16) return fail(c, FARD_EINVAL, "spec_gemm_narrow needs a bf16 context");
   if (M < 0 || K < 1 || N < 1) return fail(c, FARD_ESHAPE, "M >= 0, K, N >= 1 required");
   if (M == 0) return FARD_OK;
@@ -2147,7 +2229,7 @@ int spec_gemm_narrow(fard_ctx* c, const void* A, const void* W, const float* bia
 
 int spec_gemm_norm(fard_ctx* c, const void* x, const void* W, const float* g, const float* beta, const float* bias, int32_t M,
                    int32_t K, int32_t N, int32_t norm_type, float eps, int32_t act, void* out) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (!c->bf16) return fail(c, FARD_EINVAL, "spec_gemm_norm needs a bf16 context");
   if (M < 0 || K < 1 || N < 1) return fail(c, FARD_ESHAPE, "M >= 0, K, N >= 1 required");
   if (M == 0) return FARD_OK;
@@ -2185,7 +2267,7 @@ int spec_gemm_norm(fard_ctx* c, const void* x, const void* W, const float* g, co
 
 int spec_peak_probe(fard_ctx* c, int32_t kind, const void* buf, int64_t bytes, int32_t iters, int32_t reps, float* ms_per_launch,
                     double* units_per_launch) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (kind != 0 && kind != 1) return fail(c, FARD_EINVAL, "kind must be 0 (read) or 1 (MFMA)");
   if (reps < 1 || reps > 1000) return fail(c, FARD_EINVAL, "1 <= reps <= 1000 required");
   if (!ms_per_launch || !units_per_launch) return fail(c, FARD_EINVAL, "null argument");
@@ -2219,7 +2301,7 @@ int spec_peak_probe(fard_ctx* c, int32_t kind, const void* buf, int64_t bytes, i
 }
 
 int spec_profile_enable(fard_ctx* c, int32_t enable) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->prof.on = enable != 0;
   c->prof.used = 0;
@@ -2228,7 +2310,7 @@ int spec_profile_enable(fard_ctx* c, int32_t enable) {
 }
 
 int spec_profile_read(fard_ctx* c, int32_t kernel_class, float* total_ms, int64_t* launches, double* flops, double* bytes) {
-  if (check_ctx(c)) return FARD_EINVAL;
+  if (int e = enter(c)) return e;
   if (kernel_class < 0 || kernel_class >= CLS_COUNT) return fail(c, FARD_EINVAL, "kernel_class");
   HIPCHK(c, hipStreamSynchronize(c->stream));
   float tot = 0.f;

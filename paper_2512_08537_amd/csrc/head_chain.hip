@@ -19,9 +19,11 @@
 // first block's rows are whole in memory when the launch starts: every workgroup takes their statistics itself and passes on
 // the normalised rows.
 //
-// All workgroups of the launch have to be resident together; head_chain_fits keeps the grid so small that this holds with a
-// launch of every hardware queue on the chip at once.  Every wait is bounded: past the limit the workgroup stops waiting
-// and the rows come out as NaN.
+// All workgroups of the launch have to be resident together: head_chain_tiles keeps the grid so small that this holds with a
+// given number of such launches on the chip at once, and the context takes this path only on streams that have the whole chip
+// and share the counted hardware queues (api.hip).  Where the count is wrong all the same (more processes on the GPU than it was
+// told of), every wait is bounded in time: a workgroup that gives up marks the state, so that those which start after it and
+// every later launch do not wait, and a word in host memory, which the context's next call returns as an error; the rows are NaN.
 #include "kernels.h"
 
 namespace fard {
@@ -39,7 +41,8 @@ __device__ __forceinline__ void store_agent(__amdgpu_buffer_rsrc_t r, unsigned v
   __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, AUX_AGENT);
 }
 
-constexpr int SPIN_LIMIT = 16000000;                       // reads of one exchange: ten seconds
+// low word of the steady counter, as a scalar
+__device__ __forceinline__ unsigned steady_now() { return __builtin_amdgcn_readfirstlane((unsigned)__builtin_readsteadycounter()); }
 
 // R: rows that a launch reads per 16-row group (4, 8 or 16).  What bounds a read of an exchange is the compute unit's 64
 // bytes a clock from the vector cache: rows that are not there are not read, and up to 8 rows go through LDS (a wave stores
@@ -63,7 +66,9 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
   const int n = eff_rows(a.n, a.n_dev);
   if ((int)m0 >= n) return;                                // (uniform over the workgroups of a row group)
   const unsigned rows = (unsigned)n - m0 < (unsigned)R ? (unsigned)n - m0 : (unsigned)R;
-  const unsigned tag0 = *a.epoch * 4096u + (unsigned)a.tag_base;
+  const unsigned t_start = steady_now();
+  const unsigned tag0 = __builtin_amdgcn_readfirstlane(a.state->decodes) * 4096u + (unsigned)a.tag_base;
+  bool dead = __builtin_amdgcn_readfirstlane(a.state->gave_up) != 0;   // (an earlier launch has given up)
 
   // this row group's exchange area: rows in, a2 (4 R w bytes each: [32-k step][half][k group][row] pieces of 4 columns),
   // moments (R w bytes: [row][16-column tile])
@@ -113,12 +118,11 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
   // An exchange's words, read until all are there.  The waves that do not write wait 64 x 20-24 cycles first: the words
   // cannot be there sooner, and their reads would stand in the way of the writers' stores (w = 1536, 8 rows, a block: 5.7 us
   // without that wait, 5.35 with 8, 4.8 with 20, 5.0 with 28).
-  bool dead = false;
   u32x4 x[NP], xm[NM];
   auto get = [&](unsigned base, unsigned tag, bool moments) {
     bool ok = dead;
     if (!out_wave) __builtin_amdgcn_s_sleep(R < 16 ? 20 : 24);
-    for (int it = 0;; ++it) {
+    for (unsigned it = 0;; ++it) {
       if (it > 0) __builtin_amdgcn_s_sleep(1);
       asm volatile("" ::: "memory");                       // (every turn reads memory again)
       if (!ok) {
@@ -140,7 +144,7 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
         ok = bad == 0;
       }
       if (__all(ok)) break;
-      if (it >= SPIN_LIMIT) { dead = true; break; }
+      if ((it & 255u) == 255u && steady_now() - t_start >= a.limit) { dead = true; break; }
     }
   };
   f32x4 acc[CT];
@@ -330,6 +334,11 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
     blk = next;
   }
   if (mine) *(f32x4*)(a.hh + (size_t)gr * W_COLS + col) = h;
+  if (dead) {
+    // (workgroups that only start when this one makes room see it; all lanes store the same words)
+    __hip_atomic_store(&a.state->gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.state->host_gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // Rows that the kernel is compiled for per 16-row group: the smallest that holds a launch of n.
@@ -339,23 +348,24 @@ int head_chain_rows(int n) { return n <= 4 ? 4 : (n <= 8 ? 8 : 16); }
 
 size_t head_chain_bytes(int rows, int w) { return (size_t)((rows + 15) / 16) * 16 * 9 * w; }
 
-// Every workgroup has to be resident while any of them waits: two fit a compute unit (registers), and as many launches as
-// there are hardware queues may be on the chip side by side.  Workgroups of one 16-column tile while that holds, else of
+// Every workgroup has to be resident while any of them waits: two fit a compute unit (registers), and `launches` of them may be
+// on the chip side by side.  Workgroups of one 16-column tile while that holds, else of
 // two, which read as much of the exchange for twice the columns (a decode of 2 steps, launch per product -> resident: 33 rows of
 // 6 x 1024 140 -> 103 us, 64 rows 144 -> 105; 17 rows of 8 x 1280 183 -> 138, 48 rows 196 -> 151; one tile at 32 and 16 rows of
 // these 97 and 128).  At a width of 1536 two tiles do not fit the registers.
-int head_chain_tiles(int n, int w, int n_blocks, int n_steps, int compute_units, int queues) {
+int head_chain_tiles(int n, int w, int n_blocks, int n_steps, int compute_units, int launches) {
   if (w != 1024 && w != 1280 && w != 1536) return 0;
-  if (n < 1 || n_blocks < 1 || n_steps < 1 || (long)2 * n_blocks * n_steps >= 4095) return 0;
-  const long one = (long)(w / 16) * ((n + 15) / 16) * queues;
+  if (n < 1 || n_blocks < 1 || n_steps < 1 || (long)2 * n_blocks * n_steps >= 4095 || launches < 1) return 0;
+  const long one = (long)(w / 16) * ((n + 15) / 16) * launches;
   if (one <= 2L * compute_units) return 1;
   return w <= 1280 && one <= 4L * compute_units ? 2 : 0;
 }
 
-hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w, int tiles) {
-  if (a.n < 1 || a.n_blocks < 1 || a.tag_base < 1 || a.tag_base + 2 * a.n_blocks > 4096) return hipErrorInvalidValue;
+hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w, int tiles, bool short_of_one) {
+  if (a.n < 1 || a.n_blocks < 1 || a.tag_base < 1 || a.tag_base + 2 * a.n_blocks > 4096 || a.state == nullptr)
+    return hipErrorInvalidValue;
   if (tiles != 1 && (tiles != 2 || w > 1280)) return hipErrorInvalidValue;
-  const dim3 grid(w / (16 * tiles), (a.n + 15) / 16);
+  const dim3 grid(w / (16 * tiles) - (short_of_one ? 1 : 0), (a.n + 15) / 16);
   const int R = head_chain_rows(a.n);
 #define FARD_HC(NSV)                                                                \
   case 128 * NSV:                                                                   \

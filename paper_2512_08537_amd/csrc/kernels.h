@@ -192,19 +192,26 @@ struct HeadBlockW {                   // one block's packed weights [w, w] and b
   const void *w1, *w2;
   const float *b1, *b2;
 };
+struct HeadChainState {               // device memory
+  unsigned decodes;                   // advanced by head_prep before every decode
+  unsigned gave_up;                   // 1: a launch has given up, later ones do not wait
+  int* host_gave_up;                  // host memory: set with gave_up
+};
 struct HeadChainArgs {
   float* hh;
   const HeadBlockW* blocks; int n_blocks;            // device table
   const float* mod; int ldm, fold_base;              // the step's modulation rows: shift, scale, gate of block j at 3 w j; c0, c1 at fold_base + 2 w j
   void* xch;                                         // head_chain_bytes(n, w) bytes, zeroed once
-  const unsigned* epoch;                             // advanced by head_prep before every decode
+  HeadChainState* state;
+  unsigned limit;                                    // ticks of the steady counter that a workgroup waits at most
   int tag_base;                                      // >= 1; a decode's steps use disjoint ranges of 2 n_blocks below 4096
   int n; const int* n_dev;
 };
 size_t head_chain_bytes(int rows, int w);
-// 16-column tiles of a workgroup with which a launch of n rows may wait for itself, 0 for none
-int head_chain_tiles(int n, int w, int n_blocks, int n_steps, int compute_units, int queues);
-hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w, int tiles);
+// 16-column tiles of a workgroup with which a launch of n rows may wait for itself while `launches` such are on the chip, 0 for none
+int head_chain_tiles(int n, int w, int n_blocks, int n_steps, int compute_units, int launches);
+// short_of_one: one column workgroup less than the rows need, whose words never come (tests of the give-up)
+hipError_t launch_head_chain(hipStream_t s, const HeadChainArgs& a, int w, int tiles, bool short_of_one);
 
 // out[n] = act(sum_k in[k] W[k, n] + b[n]) for one fp32 vector (time embedding at init).
 hipError_t launch_matvec(hipStream_t s, int is_bf16, const float* in, const void* W, const float* b,

@@ -586,6 +586,11 @@ def test_diffhead_decode_of_72_rows_in_tile_order():
     ctx.close()
 
 
+def _resident_tiles(w, n):
+    one, two = {1024: (32, 64), 1280: (16, 48), 1536: (16, 16)}[w]
+    return 1 if n <= one else (2 if n <= two else 0)
+
+
 @pytest.mark.parametrize("w,n,live", [(1024, 1, 1), (1024, 4, 3), (1024, 5, 5), (1024, 8, 1), (1024, 9, 9), (1024, 16, 16),
                                       (1024, 17, 17), (1024, 32, 16), (1280, 3, 3), (1280, 8, 7), (1280, 16, 13), (1280, 17, 17),
                                       (1536, 2, 2), (1536, 8, 8), (1536, 9, 0), (1536, 16, 16), (1536, 17, 17)])
@@ -599,6 +604,7 @@ def test_diffhead_decode_with_resident_blocks(w, n, live):
                   entropy_layer=1, batch=4, n_ctx=8)
     case = build_case(rc, seed=9)
     ctx = make_ctx(case)
+    assert ctx.spec_resident_tiles(n) == _resident_tiles(w, n)
     D, S = rc.head.d_latent, rc.head.n_steps
     z = gen.normal(17, f"z{w}.{n}", (n, rc.head.d_cond), 1.0, rc.dtype)
     eps = gen.noise(17, f"e{w}.{n}", (S + 1, n, D))
@@ -628,6 +634,7 @@ def test_diffhead_decode_with_resident_blocks_of_two_tiles(w, n, live):
                   entropy_layer=1, batch=4, n_ctx=8)
     case = build_case(rc, seed=10)
     ctx = make_ctx(case)
+    assert ctx.spec_resident_tiles(n) == _resident_tiles(w, n)
     D, S = rc.head.d_latent, rc.head.n_steps
     z = gen.normal(19, f"z{w}.{n}", (n, rc.head.d_cond), 1.0, rc.dtype)
     eps = gen.noise(19, f"e{w}.{n}", (S + 1, n, D))
