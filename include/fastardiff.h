@@ -126,8 +126,9 @@ int spec_round_destroy(fard_ctx* ctx);
  *   launches >= 0: the new count (more rows than init reserved are never taken); < 0: as it is
  *   give_up_s > 0: the new limit, at most 20 s; 0 (tests): 1 ms, and launches lack a workgroup, so that they give up;
  *   < 0: as it is
+ *   decodes >= 0 (tests): the count of decodes, modulo 2^32, that the launches' tags go on from; < 0: as it is
  * Drops the graphs of spec_graph_enable, which record themselves again. */
-int spec_resident(fard_ctx* ctx, int32_t launches, float give_up_s);
+int spec_resident(fard_ctx* ctx, int32_t launches, float give_up_s, int64_t decodes);
 /* How a head decode of n rows runs: 16-column tiles (1 or 2) of a resident launch's workgroup, 0: a launch per product. */
 int spec_resident_tiles(fard_ctx* ctx, int32_t n);
 

@@ -53,7 +53,7 @@ _vp, _i32, _f32 = C.c_void_p, C.c_int32, C.c_float
 _SIGS = {
     "spec_round_init": [C.POINTER(RoundCfg), C.POINTER(Tensor), _i32, _vp, C.POINTER(_vp)],
     "spec_round_destroy": [_vp],
-    "spec_resident": [_vp, _i32, _f32],
+    "spec_resident": [_vp, _i32, _f32, C.c_int64],
     "spec_resident_tiles": [_vp, _i32],
     "spec_kv_reset": [_vp, _i32, _vp, _i32],
     "spec_kv_restore": [_vp, _i32, _vp, _i32, _i32],
@@ -218,9 +218,10 @@ class Context:
         self.torch.cuda.synchronize(self.dev)
 
     # ------------------------------------------------------------------ C ABI, one method per entry point
-    def spec_resident(self, launches=-1, give_up_s=-1.0):
-        """Resident launches that may be on the GPU at once, over all processes (0: a launch per product); seconds a launch waits."""
-        self._chk(lib.spec_resident(self.h, int(launches), float(give_up_s)))
+    def spec_resident(self, launches=-1, give_up_s=-1.0, decodes=-1):
+        """Resident launches that may be on the GPU at once, over all processes (0: a launch per product); seconds a launch waits;
+        the decode count their tags go on from (tests)."""
+        self._chk(lib.spec_resident(self.h, int(launches), float(give_up_s), int(decodes)))
 
     def spec_resident_tiles(self, n):
         tiles = lib.spec_resident_tiles(self.h, int(n))

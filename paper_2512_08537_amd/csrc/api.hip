@@ -873,6 +873,8 @@ int alloc_workspace(fard_ctx* c) {
       HIPCHK(c, hipHostMalloc((void**)&c->chain_gave_up, sizeof(int), hipHostMallocMapped));
       *c->chain_gave_up = 0;
       HeadChainState st{};
+      st.xch = (unsigned*)c->xch;
+      st.xch_words = (unsigned)words;
       HIPCHK(c, hipHostGetDevicePointer((void**)&st.host_gave_up, c->chain_gave_up, 0));
       HIPCHK(c, hipMemcpyAsync(c->chain_state, &st, sizeof(st), hipMemcpyHostToDevice, c->stream));
       HIPCHK(c, hipStreamSynchronize(c->stream));          // (the host struct goes away)
@@ -1206,7 +1208,7 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
   const bool chain = n <= c->chain_rows;
   { Bracket br(c, CLS_OTHER);
     HIPCHK(c, launch_head_prep(s, c->bf16, eps, emap, hc.temperature, D, hw.in_w, hw.in_b, c->cz, hw.temb, S, c->hh, c->sc,
-                               c->xt, w, n, n_dev, chain ? &c->chain_state->decodes : nullptr, len, row_pos)); }
+                               c->xt, w, n, n_dev, chain ? c->chain_state : nullptr, len, row_pos)); }
   // From the second block of a step on the modulated norm has no launch of its own when the rows are few (the launch
   // is then the cost; measured: a gain up to 64 rows, none above): the gate-residual GEMM of block j - 1 leaves
   // v = bf16(h (1 + scale_j)) and the tile moments of h, and block j's first GEMM multiplies v and applies mean, rstd,
@@ -1390,7 +1392,7 @@ int spec_round_destroy(fard_ctx* c) {
   return FARD_OK;
 }
 
-int spec_resident(fard_ctx* c, int32_t launches, float give_up_s) {
+int spec_resident(fard_ctx* c, int32_t launches, float give_up_s, int64_t decodes) {
   if (int e = enter(c)) return e;
   if (!(give_up_s <= 20.f)) return fail(c, FARD_EINVAL, "give_up_s beyond 20");
   if (launches >= 0) c->launches = launches;
@@ -1399,6 +1401,7 @@ int spec_resident(fard_ctx* c, int32_t launches, float give_up_s) {
     c->chain_short = give_up_s == 0.f;
     c->chain_limit = (unsigned)((c->chain_short ? 1e-3 : (double)give_up_s) * 1000.0 * c->clock_khz);
   }
+  if (decodes >= 0 && c->chain_state != nullptr) HIPCHK(c, launch_fill_i32(c->stream, (int*)&c->chain_state->decodes, (int)(uint32_t)decodes, 1));
   c->rgraph.drop();                                        // (they hold the launches of before)
   c->ggraph.drop();
   return FARD_OK;

@@ -10,8 +10,8 @@
 // number of the exchange), written and read at agent scope, so that a reader knows from the word alone whether it is fresh
 // and simply reads again.  Two buffers alternate (rows v in, hidden rows a2 out of a block's first product): a workgroup
 // writes an exchange only after all its waves have read the previous one, and that needs every workgroup's words of it, so
-// no word is overwritten before its last reader is through.  Tags go on from an epoch that the kernel before this one
-// advances: words of earlier launches never match.
+// no word is overwritten before its last reader is through.  Tags go on from a count of decodes that the kernel before this one
+// advances; where they start over, after 2^20 decodes, it clears the words: words of earlier launches never match.
 //
 // From the second block on the modulated norm is folded around the first product as in narrow_exact.hip (NM_ADA_SILU,
 // NM_ADA_GATE): v = (h - m)(1 + scale), tile moments of h beside it, rstd, mean - m, c1 and c0 applied in the epilogue; m is the
@@ -66,9 +66,8 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
   const int n = eff_rows(a.n, a.n_dev);
   if ((int)m0 >= n) return;                                // (uniform over the workgroups of a row group)
   const unsigned rows = (unsigned)n - m0 < (unsigned)R ? (unsigned)n - m0 : (unsigned)R;
-  const unsigned t_start = steady_now();
-  const unsigned tag0 = __builtin_amdgcn_readfirstlane(a.state->decodes) * 4096u + (unsigned)a.tag_base;
-  bool dead = __builtin_amdgcn_readfirstlane(a.state->gave_up) != 0;   // (an earlier launch has given up)
+  const unsigned st_decodes = a.state->decodes, st_gave_up = a.state->gave_up;   // (used behind the first loads)
+  bool dead = false;
 
   // this row group's exchange area: rows in, a2 (4 R w bytes each: [32-k step][half][k group][row] pieces of 4 columns),
   // moments (R w bytes: [row][16-column tile])
@@ -121,6 +120,7 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
   u32x4 x[NP], xm[NM];
   auto get = [&](unsigned base, unsigned tag, bool moments) {
     bool ok = dead;
+    unsigned since = 0;
     if (!out_wave) __builtin_amdgcn_s_sleep(R < 16 ? 20 : 24);
     for (unsigned it = 0;; ++it) {
       if (it > 0) __builtin_amdgcn_s_sleep(1);
@@ -144,7 +144,11 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
         ok = bad == 0;
       }
       if (__all(ok)) break;
-      if ((it & 255u) == 255u && steady_now() - t_start >= a.limit) { dead = true; break; }
+      if ((it & 255u) == 255u) {
+        const unsigned now = steady_now();
+        if (it == 255u) since = now;
+        else if (now - since >= a.limit) { dead = true; break; }
+      }
     }
   };
   f32x4 acc[CT];
@@ -251,6 +255,8 @@ __global__ __launch_bounds__(256, 2) void head_chain_kernel(HeadChainArgs a) {
       }
     }
   }
+  const unsigned tag0 = __builtin_amdgcn_readfirstlane(st_decodes) * 4096u + (unsigned)a.tag_base;
+  dead = __builtin_amdgcn_readfirstlane(st_gave_up) != 0;  // (an earlier launch has given up)
   __syncthreads();
   if (out_wave) {
     centre = rowstat[er * 2];

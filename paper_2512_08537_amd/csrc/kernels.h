@@ -159,14 +159,23 @@ hipError_t launch_final_step(hipStream_t s, int is_bf16, const float* h, int d, 
 hipError_t launch_stage_begin(hipStream_t s, const int* len, int* len_base, int* alive, int* n_keep, int B, float* z0, float* z1,
                               size_t nz);
 
+// What the resident launches of a context's head share (head_chain.hip).
+struct HeadChainState {               // device memory
+  unsigned decodes;                   // advanced by head_prep before every decode; times 4096 the tags' base
+  unsigned gave_up;                   // 1: a launch has given up, later ones do not wait
+  int* host_gave_up;                  // host memory: set with gave_up
+  unsigned* xch;                      // the exchange words: cleared where the tags start over
+  unsigned xch_words, pad;            // multiple of 4
+};
+
 // Head pieces.
 // hh[r, :] = x_t[r, :] W_in + b_in ; sc[k n + r, :] = T(silu(cz[r, :] + temb[k, :])) for the S sampler
-// times k.  x_t comes from xsrc[xmap ? xmap[r] : r] * xscale.  epoch (optional): one more decode begins (launch_head_chain).
+// times k.  x_t comes from xsrc[xmap ? xmap[r] : r] * xscale.  chain (optional): one more decode begins (launch_head_chain).
 // len, row_pos (optional, n rows): every sample's length, and with it its position, moves on by one.
 hipError_t launch_head_prep(hipStream_t s, int is_bf16, const float* xsrc, const int* xmap, float xscale,
                             int D, const void* w_in, const float* b_in, const float* cz,
                             const float* temb, int S, float* hh, void* sc, float* xt_out, int w, int n,
-                            const int* n_dev, unsigned* epoch = nullptr, int* len = nullptr, int* row_pos = nullptr);
+                            const int* n_dev, HeadChainState* chain = nullptr, int* len = nullptr, int* row_pos = nullptr);
 
 struct HeadStepArgs {
   const float* hh; int w;            // residual stream of the head [n, w]
@@ -191,11 +200,6 @@ hipError_t launch_head_out(hipStream_t s, int is_bf16, const HeadStepArgs& a);
 struct HeadBlockW {                   // one block's packed weights [w, w] and biases [w]
   const void *w1, *w2;
   const float *b1, *b2;
-};
-struct HeadChainState {               // device memory
-  unsigned decodes;                   // advanced by head_prep before every decode
-  unsigned gave_up;                   // 1: a launch has given up, later ones do not wait
-  int* host_gave_up;                  // host memory: set with gave_up
 };
 struct HeadChainArgs {
   float* hh;

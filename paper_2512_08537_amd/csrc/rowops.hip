@@ -1154,9 +1154,10 @@ __global__ __launch_bounds__(256) void head_prep_kernel(const float* __restrict_
                                                         int n, int D, int S, const float* __restrict__ xsrc,
                                                         const int* __restrict__ xmap, float xscale, float* __restrict__ hh,
                                                         T* __restrict__ sc, float* __restrict__ xt_out, const int* n_dev,
-                                                        unsigned* __restrict__ epoch, int* __restrict__ len,
+                                                        HeadChainState* chain, int* __restrict__ len,
                                                         int* __restrict__ row_pos) {
-  if (epoch != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *epoch += 1;
+  const bool counts = chain != nullptr && (blockIdx.x | blockIdx.y) == 0 && threadIdx.x < 64;   // (one wave: reads before it writes)
+  const unsigned before = counts ? chain->decodes : 0;
   if (len != nullptr && (blockIdx.x | threadIdx.x) == 0) row_pos[blockIdx.y] = ++len[blockIdx.y];
   const int r = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * 4, cc = c < w ? c : 0;
   const f32x4 czv = *(const f32x4*)(cz + (size_t)r * w + cc);
@@ -1164,6 +1165,12 @@ __global__ __launch_bounds__(256) void head_prep_kernel(const float* __restrict_
 #pragma unroll
   for (int k = 0; k < 16; ++k) wv[k] = load4f<T>(w_in + (size_t)(k < D ? k : 0) * w + cc);
   const int ne = eff_rows(n, n_dev);
+  if (counts) {
+    if (threadIdx.x == 0) chain->decodes = before + 1;
+    if (__builtin_expect(((before + 1) & 0xFFFFFu) == 0, 0)) {   // the tags, 4096 a decode, start over
+      for (unsigned i = threadIdx.x * 4; i < chain->xch_words; i += 256) *(f32x4*)(chain->xch + i) = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
   if (r >= ne) return;
   const float* xr = xsrc + (size_t)(xmap ? xmap[r] : r) * D;
   float xv[16];
@@ -1702,16 +1709,17 @@ hipError_t launch_entropy_step(hipStream_t s, const float* ent_heads, int n_head
 
 hipError_t launch_head_prep(hipStream_t s, int is_bf16, const float* xsrc, const int* xmap, float xscale, int D,
                             const void* w_in, const float* b_in, const float* cz, const float* temb, int S, float* hh,
-                            void* sc, float* xt_out, int w, int n, const int* n_dev, unsigned* epoch, int* len, int* row_pos) {
+                            void* sc, float* xt_out, int w, int n, const int* n_dev, HeadChainState* chain, int* len,
+                            int* row_pos) {
   if (n <= 0) return hipSuccess;
   if (w % 4 != 0 || D > 16) return hipErrorInvalidValue;
   dim3 grid((w + 1023) / 1024, n);
   if (is_bf16)
     head_prep_kernel<bf16><<<grid, 256, 0, s>>>(cz, (const bf16*)w_in, b_in, temb, w, n, D, S, xsrc, xmap, xscale, hh, (bf16*)sc,
-                                                xt_out, n_dev, epoch, len, row_pos);
+                                                xt_out, n_dev, chain, len, row_pos);
   else
     head_prep_kernel<float><<<grid, 256, 0, s>>>(cz, (const float*)w_in, b_in, temb, w, n, D, S, xsrc, xmap, xscale, hh, (float*)sc,
-                                                 xt_out, n_dev, epoch, len, row_pos);
+                                                 xt_out, n_dev, chain, len, row_pos);
   return hipGetLastError();
 }
 

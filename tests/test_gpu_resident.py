@@ -15,9 +15,9 @@ from tests.harness import build_case, make_ctx, rel_inf
 pytestmark = pytest.mark.gpu
 
 
-def _case(w, seed=9):
+def _case(w, seed=9, blocks=3, steps=2):
     tf = TfCfg(n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, d_head=64, d_ff=256, max_pos=32)
-    rc = RoundCfg(name="resident", target=tf, draft=tf, head=HeadCfg(3, w, 128, n_steps=2), K=8, max_batch=16, max_ctx=32,
+    rc = RoundCfg(name="resident", target=tf, draft=tf, head=HeadCfg(blocks, w, 128, n_steps=steps), K=8, max_batch=16, max_ctx=32,
                   entropy_layer=1, batch=4, n_ctx=8)
     return build_case(rc, seed=seed)
 
@@ -134,6 +134,24 @@ def test_contexts_on_streams_of_their_own_decode_at_once(w, n):
         ctx.spec_kv_lengths(binding.TARGET, 4)             # (nothing gave up)
         z, eps = _inputs(case, n, seed=case.seed)
         _check(case, [t.cpu().numpy() for t in alone[i]], z, eps)
+        ctx.close()
+
+
+@pytest.mark.parametrize("w", [1024, 1280, 1536])
+@pytest.mark.parametrize("n,between", [(8, 1), (16, 3), (4, 16), (16, 8)])
+def test_tags_that_start_over_match_no_word_of_before(w, n, between):
+    """A head of one block and one step uses every exchange buffer once a decode, so its words stay with their first tags.  A decode
+    of n rows, one of another row count in which the count of decodes passes a multiple of 2^20, and a decode of other values
+    whose tags are those of the first."""
+    case = _case(w, blocks=1, steps=1)
+    first, mid, last = _inputs(case, n, seed=1), _inputs(case, between, seed=2), _inputs(case, n, seed=3)
+    for turn in (1, 4096):                                 # (the second: the count itself wraps)
+        ctx = make_ctx(case)
+        ctx.spec_resident(decodes=(turn - 1) << 20)
+        _check(case, _decode(ctx, *first), *first)
+        ctx.spec_resident(decodes=(turn << 20) - 1)
+        _check(case, _decode(ctx, *mid), *mid)
+        _check(case, _decode(ctx, *last), *last)
         ctx.close()
 
 
