@@ -45,10 +45,11 @@ template <bool BF16 = false>
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erf_as<BF16>(x * 0.70710678118654752f)); }
 template <bool BF16 = false>
 __device__ __forceinline__ float silu(float x) {
-  const float d = 1.0f + __expf(-x);
-  if constexpr (!BF16) return x / d;
-  const float t = __builtin_amdgcn_rcpf(d), t1 = fmaf(t, fmaf(-d, t, 1.0f), t);
-  return x * (d < 1e38f ? t1 : t);                         // (an infinite d has no Newton step: x / inf)
+  const float e = __expf(-x);
+  if constexpr (!BF16) return x / (1.0f + e);
+  // a quarter of the denominator: the reciprocal flushes denormals, which those of finite d / 4 are not (x down to -88.7)
+  const float d4 = fmaf(e, 0.25f, 0.25f), t = __builtin_amdgcn_rcpf(d4), t1 = fmaf(t, fmaf(-d4, t, 1.0f), t);
+  return (0.25f * x) * (d4 < INFINITY ? t1 : t);           // (an infinite d has no Newton step: x / inf)
 }
 template <bool BF16 = false>
 __device__ __forceinline__ float apply_act(float x, int act) {
