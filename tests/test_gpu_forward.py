@@ -223,3 +223,71 @@ def test_forward_of_72_rows_with_a_split_k_residual_product():
         print(f"72 rows, split-K residual product, n_q {n_q.tolist()}: z {ez:.2e} shallow {es:.2e}")
         assert ez < 2e-2 and es < 2e-2
     ctx.close()
+
+
+def _f32_case(max_ctx, dh, norm, bias, seed=33):
+    from synth.configs import HeadCfg, RoundCfg, TfCfg
+    t = TfCfg(n_layers=2, d_model=256, n_heads=256 // dh, n_kv_heads=256 // dh, d_head=dh, d_ff=512, norm=norm, has_bias=bias, max_pos=max_ctx)
+    return build_case(RoundCfg(name="f32-bits", target=t, draft=t, head=HeadCfg(2, 256, 256, n_steps=2), K=4, max_batch=40, max_ctx=max_ctx,
+                               entropy_layer=1, dtype=DT_F32, batch=2, n_ctx=70), seed=seed)
+
+
+def _f32_forward(case, ctx, n_q):
+    """Sample 0's rows first, n_q[0] of them, whatever follows; sample 1 holds another prefix."""
+    from tests.harness import load_caches
+    load_caches(ctx, case)
+    lens = np.zeros(len(n_q), np.int32)
+    lens[:min(2, len(n_q))] = case.n_ctx
+    ctx.spec_kv_reset(0, lens)
+    x = np.random.default_rng(6).normal(size=(int(np.sum(n_q)), 16)).astype(np.float32)
+    z, sh, ha = ctx.spec_forward(0, ctx.dev_f32(x), np.asarray(n_q, np.int32), commit=False, want_shallow=True, want_h_attn=True)
+    ctx.sync()
+    return [t.cpu().numpy()[:n_q[0]] for t in (z, sh, ha)]
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("norm,bias", [(0, 1), (0, 0), (1, 1)])
+def test_f32_rows_do_not_depend_on_the_rows_beside_them(dh, norm, bias):
+    """Few rows: the norms ride in the products behind them; many: launches of their own, and products of other tiles.  Every sum is
+    taken in the same order: the same bits."""
+    case = _f32_case(96, dh, norm, bias)
+    ctx = make_ctx(case)
+    alone = _f32_forward(case, ctx, [5])                   # (5 rows: 48 and 32 column groups of 16 x 2 row groups of 4)
+    for n_q in ([5, 3], [5, 1] + [5] * 30):                # (156 rows: far beyond 256 workgroups)
+        assert all(np.array_equal(a, b) for a, b in zip(alone, _f32_forward(case, ctx, n_q)))
+    ctx.close()
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("n_q", [[1], [5, 4], [9, 70]])
+def test_f32_attention_kernels_give_the_same_bits(dh, n_q):
+    """Caches of up to 7936 positions: a workgroup per row and head that also appends; longer ones: a wave per row and head behind
+    an append of its own."""
+    out = []
+    for max_ctx in (160, 8000):
+        case = _f32_case(max_ctx, dh, 0, 1)
+        if out:
+            case.W["target.pos"][:160] = pos
+        pos = case.W["target.pos"][:160].copy()
+        ctx = make_ctx(case)
+        out.append(_f32_forward(case, ctx, n_q))
+        ctx.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+def test_f32_head_rows_do_not_depend_on_the_rows_beside_them():
+    """Up to 64 rows of a 256-wide head the modulated norm is taken inside the block's first product, from 65 on by a launch."""
+    case = _f32_case(96, 64, 0, 1)
+    ctx = make_ctx(case)
+    h = case.rc.head
+    z = gen.normal(21, "zf", (120, h.d_cond), 1.0, DT_F32)
+    eps = gen.noise(21, "ef", (h.n_steps + 1, 120, h.d_latent))
+    out = []
+    for n in (1, 64, 65, 120):
+        mu, x = ctx.diffhead_decode(ctx.dev_f32(z[:n]), ctx.dev_f32(np.ascontiguousarray(eps[:, :n])))
+        ctx.sync()
+        out.append((mu.cpu().numpy(), x.cpu().numpy()))
+    for a, b in zip(out, out[1:]):
+        n = len(a[0])
+        assert np.array_equal(a[0], b[0][:n]) and np.array_equal(a[1], b[1][:n])
+    ctx.close()
