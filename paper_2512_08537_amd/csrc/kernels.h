@@ -88,7 +88,7 @@ hipError_t launch_rope_append(hipStream_t s, void* qkv, int ld, int n_heads, KvG
                               const int* m_dev);
 
 // The same with the rows still in the K-slice planes of the QKV product (fp32 [n_parts][M, ld], plane p at
-// parts + p * part_stride): the planes are summed, q and k rotated in fp32 (tab; nullptr: no rotation); q goes to qkv as bf16
+// parts + p * part_stride): the planes are summed, q and k rotated in fp32 (angles from tab); q goes to qkv as bf16
 // (the k and v columns of qkv are not written), k and v to the cache.  bf16 caches only.
 hipError_t launch_rope_append_planes(hipStream_t s, const float* parts, int n_parts, size_t part_stride, void* qkv, int ld,
                                      int n_heads, KvGeom kv, const float* tab, const RowMaps& maps, int M, const int* m_dev);

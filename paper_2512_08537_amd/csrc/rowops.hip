@@ -625,7 +625,7 @@ __global__ __launch_bounds__(256) void rope_append_planes_kernel(const float* __
   if (r >= Me) return;
   const int b = row_sample[r], pos = row_pos[r];
   const bool is_v = hd >= n_heads + Hk;
-  if (tab != nullptr && !is_v) {
+  if (!is_v) {
     const f32x4 cs = *(const f32x4*)(tab + (size_t)pos * dh + c), sn = *(const f32x4*)(tab + (size_t)pos * dh + half + c);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1553,7 +1553,8 @@ hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M,
   if (ent != nullptr && (scale != nullptr || in_map != nullptr)) return hipErrorInvalidValue;
   if (d % 4 != 0 || d > NORM_MAX_D || ldm % 4 != 0 || (out_tiled && (!is_bf16 || d % 32 != 0))) return hipErrorInvalidValue;
   const bool mod = scale != nullptr;
-  if (mod && (g != nullptr || b != nullptr || shift == nullptr)) return hipErrorInvalidValue;   // (one or the other: as every caller has it)
+  // (one or the other, modulated rows without planes: as every caller has it)
+  if (mod && (g != nullptr || b != nullptr || shift == nullptr || n_parts != 0)) return hipErrorInvalidValue;
   const float *ga = mod ? scale : g, *be = mod ? shift : b;
   const int n4 = d >> 2;
   // up to 512 threads with one piece each, then two
@@ -1564,8 +1565,7 @@ hipError_t launch_norm(hipStream_t s, int is_bf16, const float* h, int d, int M,
                                                         h_wb, rms, eps, out_tiled, ent)
 #define FARD_NORM_P(TV, VPT)                                    \
   do {                                                          \
-    if (mod && n_parts == 0) FARD_NORM_L(TV, VPT, true, 0);     \
-    else if (mod) FARD_NORM_L(TV, VPT, true, -1);               \
+    if (mod) FARD_NORM_L(TV, VPT, true, 0);                     \
     else if (n_parts == 0) FARD_NORM_L(TV, VPT, false, 0);      \
     else if (n_parts == 4) FARD_NORM_L(TV, VPT, false, 4);      \
     else if (n_parts == 5) FARD_NORM_L(TV, VPT, false, 5);      \
@@ -1635,7 +1635,7 @@ hipError_t launch_rope_append_planes(hipStream_t s, const float* parts, int n_pa
   if (M <= 0) return hipSuccess;
   const int dh = kv.d_head;
   // a head's first half in groups of 4 dims; 16-byte loads of the planes, 8-byte stores of q and k
-  if (!kv.is_bf16 || n_parts < 1 || dh % 16 != 0 || dh > 2048 || 256 % (dh / 8) != 0 || ld % 4 != 0 || part_stride % 4 != 0 ||
+  if (!kv.is_bf16 || tab == nullptr || n_parts < 1 || dh % 16 != 0 || dh > 2048 || 256 % (dh / 8) != 0 || ld % 4 != 0 || part_stride % 4 != 0 ||
       (((uintptr_t)parts) & 15) != 0 || (((uintptr_t)qkv) & 7) != 0)
     return hipErrorInvalidValue;
   const int hpw = 256 / (dh / 8);
