@@ -1490,8 +1490,8 @@ int spec_kv_commit(fard_ctx* c, int32_t which, const int32_t* n_accept, int32_t 
   if (!n_accept) return fail(c, FARD_EINVAL, "n_accept");
   if (B < 0 || B > c->cfg.max_batch) return fail(c, FARD_ECAPACITY, "B > max_batch");
   if (B == 0) return FARD_OK;
-  // (with both models the one that has nothing to commit is refused before the other is touched only if it comes first: as
-  // two calls would)
+  // Both models in one launch.  The errors are those of a call for the target and then one for the draft: with nothing to commit
+  // for the target nothing is done; with nothing for the draft the target is committed and the call fails all the same.
   const int w0 = which == -1 ? 0 : which, n = which == -1 ? 2 : 1;
   if (which != -1 && which != 0 && which != 1) return FARD_OK;
   const bool second = n == 2 && c->mdl[1].written >= 1;

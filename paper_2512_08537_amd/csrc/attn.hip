@@ -16,7 +16,8 @@
 // With learned positions (no RoPE) the kernel also appends the new rows' K and V to the cache, so a layer
 // needs no separate append launch.
 //
-// fp32 path: one wave per (row, head), scores staged in LDS; for the small fp32 configuration.
+// fp32 path, for the small fp32 configuration: a workgroup per (row, head) for head dims 32, 64 and 128 and caches of up to 7936
+// positions, which also appends; one wave per (row, head) otherwise; scores in LDS.
 #include "kernels.h"
 
 #include <algorithm>

@@ -358,7 +358,8 @@ size_t head_chain_bytes(int rows, int w) { return (size_t)((rows + 15) / 16) * 1
 // on the chip side by side.  Workgroups of one 16-column tile while that holds, else of
 // two, which read as much of the exchange for twice the columns (a decode of 2 steps, launch per product -> resident: 33 rows of
 // 6 x 1024 140 -> 103 us, 64 rows 144 -> 105; 17 rows of 8 x 1280 183 -> 138, 48 rows 196 -> 151; one tile at 32 and 16 rows of
-// these 97 and 128).  At a width of 1536 two tiles do not fit the registers.
+// these 97 and 128).  At a width of 1536 two tiles do not fit the registers.  The widths are those it was measured at; others keep
+// a launch per product.
 int head_chain_tiles(int n, int w, int n_blocks, int n_steps, int compute_units, int launches) {
   if (w != 1024 && w != 1280 && w != 1536) return 0;
   if (n < 1 || n_blocks < 1 || n_steps < 1 || (long)2 * n_blocks * n_steps >= 4095 || launches < 1) return 0;

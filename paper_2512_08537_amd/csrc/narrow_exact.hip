@@ -12,6 +12,8 @@
 //   - nothing branches before the operands, the epilogue's operands and the device-side row count are all requested: absent
 //     bias or row count is a select on a loaded value;
 //   - only the waves that write (MT NT of the four) request the epilogue's operands.
+// K shares: 1024, 1280 and 1536 are the model widths this was measured at, 2048 the share of a wave's 16 steps, the most that
+// the tiles hold.  A further share is 18 to 29 instances more; other multiples of 128 stay with the general kernel, unmeasured.
 // Measured over whole rounds, general kernel -> this one: one sample of 24 layers of 1024 3.31 -> 2.97 ms (566 launches), eight
 // samples of 40 layers of 5120 with its 12-block head 16.8 -> 15.5 ms, four rounds of 32 samples of 1024 16.0 -> 14.2 ms.
 #include "gemm.h"
