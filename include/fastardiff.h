@@ -122,7 +122,7 @@ int spec_round_destroy(fard_ctx* ctx);
  * number here, or 0 to use a launch per product (the same results up to rounding).
  * Where the count is wrong all the same, a launch gives up after give_up_s (10 s by default): its rows are NaN, and the next
  * call on the context, or the spec_kv_lengths that waits for it, returns FARD_EHIP once; the context goes on with a launch per
- * product.  Caches and tokens written since then hold NaN: restart those samples.
+ * product.  Tokens and caches written since then are of no use (the cached values' NaN are cleared to zero): restart those samples.
  *   launches >= 0: the new count (more rows than init reserved are never taken); < 0: as it is
  *   give_up_s > 0: the new limit, at most 20 s; 0 (tests): 1 ms, and launches lack a workgroup, so that they give up;
  *   < 0: as it is

@@ -1294,19 +1294,21 @@ int run_head(fard_ctx* c, const void* z, int n, const int* n_dev, const float* e
   return FARD_OK;
 }
 
-// A resident head launch has given up (head_chain.hip): the rows of every decode since then are NaN.  Reported once; the
-// context goes on with a launch per product.
+// A resident head launch has given up (head_chain.hip): the rows of every decode since then are NaN.  Reported once (again where
+// it was first seen under capture, which allows none of this); the context goes on with a launch per product.  Values cached
+// since then are cleared of NaN: past a cache's length they meet probabilities of zero, in a product.
 int chain_gave_up(fard_ctx* c) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (c->stream != nullptr) (void)hipStreamIsCapturing(c->stream, &cap);   // (the default stream cannot be captured)
+  c->chain_rows = 0;
   if (cap == hipStreamCaptureStatusNone) {
     HIPCHK(c, hipStreamSynchronize(c->stream));            // (launches behind it mark the word again)
     HIPCHK(c, launch_fill_i32(c->stream, (int*)&c->chain_state->gave_up, 0, 1));
+    for (Model& m : c->mdl) HIPCHK(c, launch_clear_nan_bf16(c->stream, m.vc, m.layer_elems * m.c.n_layers));
+    __atomic_store_n(c->chain_gave_up, 0, __ATOMIC_RELAXED);
+    c->rgraph.drop();
+    c->ggraph.drop();
   }
-  __atomic_store_n(c->chain_gave_up, 0, __ATOMIC_RELAXED);
-  c->chain_rows = 0;
-  c->rgraph.drop();
-  c->ggraph.drop();
   return fail(c, FARD_EHIP, "a head decode waited too long for its own workgroups (is the GPU shared by other processes? see "
                             "spec_resident): its rows and all that was computed from them are NaN; later decodes use a launch per product");
 }

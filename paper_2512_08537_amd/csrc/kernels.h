@@ -241,6 +241,8 @@ hipError_t launch_catchup_pack(hipStream_t s, const int* n_accept, const float* 
 hipError_t launch_len_add(hipStream_t s, int* cache_len, const int* n, int base, int B);
 hipError_t launch_fill_i32(hipStream_t s, int* p, int v, int n);
 hipError_t launch_fill_f32(hipStream_t s, float* p, float v, size_t n);
+// p[i] = 0 where it is NaN (n % 8 == 0, 16-byte aligned)
+hipError_t launch_clear_nan_bf16(hipStream_t s, void* p, size_t n);
 // copy rows: dst[dmap ? dmap[r] : r, :] = src[r, :] for r < n (fp32 or storage type by elem_size)
 hipError_t launch_scatter_rows(hipStream_t s, const void* src, void* dst, const int* dmap, int width,
                                int elem_size, int n, const int* n_dev);

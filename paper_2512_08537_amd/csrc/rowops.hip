@@ -1363,6 +1363,18 @@ __global__ void len_add_kernel(int* cache_len, const int* n, int base, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b < B) cache_len[b] += base + (n ? n[b] : 0);
 }
+__global__ __launch_bounds__(256) void clear_nan_kernel(bf16x8* p, size_t n8) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (size_t)gridDim.x * 256) {
+    bf16x8 v = p[i];
+    bool any = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float f = (float)v[e];
+      if (f != f) { v[e] = (bf16)0.f; any = true; }
+    }
+    if (any) p[i] = v;
+  }
+}
 __global__ void fill_i32_kernel(int* p, int v, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -1784,6 +1796,12 @@ hipError_t launch_len_add(hipStream_t s, int* cache_len, const int* n, int base,
 hipError_t launch_fill_i32(hipStream_t s, int* p, int v, int n) {
   if (n <= 0) return hipSuccess;
   fill_i32_kernel<<<(n + 255) / 256, 256, 0, s>>>(p, v, n);
+  return hipGetLastError();
+}
+hipError_t launch_clear_nan_bf16(hipStream_t s, void* p, size_t n) {
+  if (n == 0) return hipSuccess;
+  if (n % 8 != 0 || (((uintptr_t)p) & 15) != 0) return hipErrorInvalidValue;
+  clear_nan_kernel<<<(unsigned)std::min<size_t>((n / 8 + 255) / 256, 4096), 256, 0, s>>>((bf16x8*)p, n / 8);
   return hipGetLastError();
 }
 hipError_t launch_fill_f32(hipStream_t s, float* p, float v, size_t n) {

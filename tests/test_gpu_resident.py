@@ -10,7 +10,7 @@ from oracle import head as ohd
 from paper_2512_08537_amd import binding
 from synth import gen
 from synth.configs import HeadCfg, RoundCfg, TfCfg
-from tests.harness import build_case, make_ctx, rel_inf
+from tests.harness import build_case, gpu_inputs, make_ctx, rel_inf, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -100,6 +100,44 @@ def test_launch_that_waits_in_vain_is_reported(w, n):
     assert ctx.spec_resident_tiles(n) > 0
     again = _decode(ctx, z, eps)
     assert np.array_equal(again[0], good[0]) and np.array_equal(again[1], good[1])
+    ctx.close()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_rounds_after_a_launch_that_waited_in_vain(graph):
+    """A round whose head launches give up fails, or the call behind it; the next round on restored caches is that of a context
+    without resident launches, and with them allowed again that of before, also recorded and replayed."""
+    case = _case(1024)
+    ctx = make_ctx(case, stream=torch.cuda.Stream())
+    inp = gpu_inputs(ctx, case)
+    torch.cuda.synchronize()
+
+    def one():
+        for which in (binding.TARGET, binding.DRAFT):
+            ctx.spec_kv_reset(which, np.full(case.B, case.n_ctx, dtype=np.int32))
+        out = ctx.spec_round(inp["pending"], inp["eps"], inp["r"], 0.0, out=bufs)
+        ctx.sync()
+        return to_np(out)
+
+    bufs = ctx._round_bufs(case.B)
+    if graph:
+        ctx.spec_graph_enable(True)
+    with_path = [one() for _ in range(4)]
+    ctx.spec_resident(launches=0)
+    without = [one() for _ in range(4)]
+    ctx.spec_resident(launches=4, give_up_s=0.0)
+    with pytest.raises(binding.FardError) as e:
+        one()
+        ctx.spec_kv_lengths(binding.TARGET, case.B)
+    assert e.value.code == -5
+    ctx.sync()
+    after = [one() for _ in range(4)]
+    ctx.spec_resident(launches=4, give_up_s=10.0)
+    again = [one() for _ in range(4)]
+    for key in ("mu_p", "x_draft", "n_accept", "log_ratio"):
+        assert np.isfinite(with_path[0][key]).all()
+        assert all(np.array_equal(a[key], with_path[0][key]) for a in with_path + again)
+        assert all(np.array_equal(a[key], without[0][key]) for a in without + after)
     ctx.close()
 
 
