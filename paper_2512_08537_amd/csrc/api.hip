@@ -294,6 +294,7 @@ struct fard_ctx {
   uint8_t* acc_tmp = nullptr;
   float *cz = nullptr, *hh = nullptr, *mod = nullptr, *xt = nullptr;
   void *sc = nullptr, *a1 = nullptr, *a2 = nullptr;
+  int draft_b = 0;               // most samples that a step of the present draft stage had
   int *alive = nullptr, *act_idx = nullptr, *n_act = nullptr, *emap = nullptr, *omap = nullptr;
   int* ent_blk = nullptr;
   void* gemm_tmp = nullptr;
@@ -1738,6 +1739,7 @@ static int draft_begin(fard_ctx* c, int B, int32_t* n_keep, float* x_draft, floa
   const int K = c->cfg.K, D = m.c.d_latent;
   hipStream_t s = c->stream;
   Bracket br(c, CLS_OTHER);
+  c->draft_b = B;
   // (dropped drafts keep finite values: they still travel through the dense draft rows)
   HIPCHK(c, launch_stage_begin(s, m.len, m.len_base, c->alive, n_keep, B, x_draft, mu_q, (size_t)B * K * D));
   m.written = 0;
@@ -1775,6 +1777,11 @@ static int draft_step(fard_ctx* c, int i, const float* xs, int ldx, const int32_
   if ((rc = run_layers(c, FARD_DRAFT, ls, m.c.n_layers, B, B, 1, nullptr, 0, false, in_norm ? c->h_row : nullptr))) return rc;
   int* alive_in = c->alive + (i & 1) * c->cfg.max_batch;
   int* alive_out = c->alive + ((i + 1) & 1) * c->cfg.max_batch;
+  if (B < c->draft_b) {                                    // samples that sit this step out keep their flags
+    copy_i32_kernel<<<(c->draft_b - B + 255) / 256, 256, 0, s>>>(alive_in + B, alive_out + B, c->draft_b - B);
+    HIPCHK(c, hipGetLastError());
+  }
+  c->draft_b = std::max(c->draft_b, B);
   // only samples that are still speculating reach the head
   if (in_final) {
     EntStep st{c->h_row, alive_in, alive_out, tau, K, i, H, keep, n_keep, c->act_idx, c->n_act, c->emap, c->omap};

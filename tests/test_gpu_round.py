@@ -370,6 +370,28 @@ def test_config0_full_round_fp32():
     ctx.close()
 
 
+def test_samples_that_sit_a_draft_step_out_keep_their_flags():
+    """Steps over all samples, the first two, and all again: samples dropped in the first step stay dropped, those of a stage in
+    which nothing was dropped all go on."""
+    case = build_case("mid-bf16", seed=37)
+    B, K = case.B, case.rc.K
+    assert B > 2 and K >= 3
+    ctx = make_ctx(case)
+    gi = gpu_inputs(ctx, case)
+    few = gi["eps"][:, :2].contiguous()
+    for tau0, alive in ((1e9, 0), (-1.0, 1)):
+        out = ctx._round_bufs(B)
+        x = gi["pending"]
+        ctx.spec_draft_step(0, x, gi["eps"], tau0, out)
+        ctx.spec_draft_step(1, x[:2].contiguous(), few, -1.0, {k: v[:2] for k, v in out.items()})
+        ctx.spec_draft_step(2, x, gi["eps"], -1.0, out)
+        ctx.sync()
+        got = to_np(out)
+        assert (got["keep"][:, 2] == alive).all()
+        assert (got["n_keep"][:2] == 3 * alive).all() and (got["n_keep"][2:] == 2 * alive).all()
+    ctx.close()
+
+
 def test_draft_steps_one_by_one_equal_spec_draft_and_lengths_restore_from_device():
     """spec_draft_step K times (tokens taken from the library's own previous drafts) is spec_draft bit for bit, with
     other calls on the context in between; spec_kv_restore rewinds the lengths from device memory and clamps them to
