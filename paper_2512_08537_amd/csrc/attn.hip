@@ -38,6 +38,20 @@ constexpr float LN2 = 0.6931471805599453f, LOG2E = 1.4426950408889634f;
 // probability 0.
 constexpr float T_MIN = -16384.f;
 
+// An exponent is one fused s sc2 - m sc2 whose second product is rounded on its own: all exponents of a row are off by the same
+// half of its last place, which cancels in the division by their sum.  For products beyond 2^24 it would be whole powers of
+// two, up to an overflow: there the scores are subtracted first.  With x for m in one case and y for m sc2 in the other, the rest
+// zero, an exponent is (s - x) sc2 - y.
+struct Ref { float x, y; };
+__device__ __forceinline__ Ref reference(float m, float sc2) {
+#pragma clang fp contract(off)
+  const float y = m * sc2;
+  const bool big = fabsf(y) > 16777216.f;
+  return Ref{big ? m : 0.f, big ? 0.f : y};
+}
+// the distance of two references
+__device__ __forceinline__ float ref_distance(Ref a, Ref b, float sc2) { return fmaf(a.x - b.x, sc2, a.y - b.y); }
+
 // c / nq for column indexes (c < 64)
 __device__ __forceinline__ int col_head(int c, float inv_nq) { return (int)(((float)c + 0.5f) * inv_nq); }
 
@@ -192,18 +206,18 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
     bmax = xor32_max(bmax);
     const float m_new = fmaxf(m_run[qb], bmax);
     const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // (no key with a score above -inf so far)
+    const Ref ref = reference(m_ref, sc2);
     float psum = 0.f, asum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      // (not one fused s sc2 - m_ref sc2: the second product is rounded, for scores of 1e9 and more by whole powers of two)
-      const float t = (s[e] - m_ref) * sc2;
+      const float t = fmaf(s[e] - ref.x, sc2, -ref.y);
       const float p = __builtin_amdgcn_exp2f(t);
       psum += p;
       if constexpr (ENT) asum = fmaf(p, fmaxf(t, T_MIN), asum);
       pf[e >> 3][e & 7] = (bf16)p;
     }
     psum = xor32_sum(psum);
-    const float dl = fmaxf((m_run[qb] - m_ref) * sc2, T_MIN), corr = __builtin_amdgcn_exp2f(dl);
+    const float dl = fmaxf(ref_distance(reference(m_run[qb], sc2), ref, sc2), T_MIN), corr = __builtin_amdgcn_exp2f(dl);
     if constexpr (ENT) a_run[qb] = fmaf(corr, fmaf(dl, l_run[qb], a_run[qb]), xor32_sum(asum));
     l_run[qb] = fmaf(corr, l_run[qb], psum);
     m_run[qb] = m_new;
@@ -296,7 +310,7 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
   };
   float f_me[NQB];
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) f_me[qb] = __builtin_amdgcn_exp2f(fmaxf((m_run[qb] - top(cl + 32 * qb)) * sc2, T_MIN));
+  for (int qb = 0; qb < NQB; ++qb) f_me[qb] = __builtin_amdgcn_exp2f(fmaxf(ref_distance(reference(m_run[qb], sc2), reference(top(cl + 32 * qb), sc2), sc2), T_MIN));
   // every wave lays its rescaled partial O^T down in its own slab: one barrier, no read-modify-write rounds
   float* slab = s_o + (size_t)wave * DH * OLD;
 #pragma unroll
@@ -318,7 +332,7 @@ __global__ __launch_bounds__(256, ATTN_MIN_WG(DH, NQB)) void attn_bf16_kernel(co
     float lstar = 0.f, astar = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float dl = fmaxf((s_m[w][c] - mstar) * sc2, T_MIN), f = __builtin_amdgcn_exp2f(dl);
+      const float dl = fmaxf(ref_distance(reference(s_m[w][c], sc2), reference(mstar, sc2), sc2), T_MIN), f = __builtin_amdgcn_exp2f(dl);
       lstar = fmaf(f, s_l[w][c], lstar);
       if constexpr (ENT) astar = fmaf(f, fmaf(dl, s_l[w][c], s_a[w][c]), astar);
     }
@@ -386,7 +400,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnSplit sp, int n_hea
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (s >= sp.n || t[s][1] == 0.f) continue;
-      const float dl = fmaxf((t[s][0] - mstar) * sc2, T_MIN), f = __builtin_amdgcn_exp2f(dl);
+      const float dl = fmaxf(ref_distance(reference(t[s][0], sc2), reference(mstar, sc2), sc2), T_MIN), f = __builtin_amdgcn_exp2f(dl);
       lstar += f * t[s][1];
       astar += f * (t[s][2] + dl * t[s][1]);
 #pragma unroll
